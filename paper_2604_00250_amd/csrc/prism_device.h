@@ -201,97 +201,53 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 9 special functions: log I0e(z) and 1 - I1(z)/I0(z) for z >= 0
+// Eq. 9 special functions: -log I0e(z) and 1 - I1(z)/I0(z) for z >= 0
 // ---------------------------------------------------------------------------
+// The table of bessel_fit.h as the kernels read it, rows in LDS: entry i is the
+// two float4 (z0, c0, c1, c2) at [i] and (c3, c4, c5, c6) at [kBesselEntries + i]
+// (two arrays rather than rows of 32 bytes, so that the lanes' rows start at all
+// sixteen groups of four banks).  The table is read per lane: the alternative,
+// closed forms for small and for large z, runs both in nearly every wave (about
+// 115 instructions, against 18 here and two LDS reads; a 16^3 patch's iteration,
+// N = 288, K = 3: 66.3 -> 53.4 us, 512 mixed patches 1671 -> 1204 us).
+constexpr int kBesselRows = 2 * kBesselEntries;   // float4 rows of LDS (4.9 KB)
 
-template <int N>
-__device__ __forceinline__ float horner(const float (&c)[N], float x) {
-  float acc = c[N - 1];
-#pragma unroll
-  for (int i = N - 2; i >= 0; --i) acc = fmaf(acc, x, c[i]);
-  return acc;
-}
-
-// The small-argument branch's polynomials sum_i c_i x^i, |x| <= 1: the four
-// lowest terms in float64 from a table in constant memory, the rest (weight
-// x^4, coefficients below 0.015) in float32 with the coefficients as
-// instruction literals, added in float64.  The float64 table is read where the
-// branch runs: its offset passes through an empty asm statement there, so the
-// compiler cannot hoist the coefficients' scalar registers out of the
-// measurement loop (float64 operands cannot be instruction literals on this
-// architecture).  The float32 part is evaluated by Estrin's scheme
-// (coefficient pairs, then pairs of pairs with x^2, x^4, x^8), so the longest
-// dependent chain is about five operations instead of N - 1: this branch runs
-// for a few lanes of most waves, and its latency, not its work, is what the
-// measurement loop waits on.
-__device__ __forceinline__ double low4_d(const double* c, double x, double x2) {
-  int off = 0;
-  asm volatile("" : "+s"(off));
-  c += off;
-  return fma(fma(c[3], x, c[2]), x2, fma(c[1], x, c[0]));
-}
-template <int N>
-__device__ __forceinline__ float estrin_f(const float (&c)[N], float x, float x2, float x4, float x8) {
-  static_assert(N >= 2 && N <= 16, "Estrin evaluation of degree 1..15");
-  constexpr int N1 = (N + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2;
-  float p1[N1], p2[N2], p3[N3];
-#pragma unroll
-  for (int i = 0; i < N1; ++i) p1[i] = 2 * i + 1 < N ? fmaf(c[2 * i + 1], x, c[2 * i]) : c[2 * i];
-#pragma unroll
-  for (int i = 0; i < N2; ++i) p2[i] = 2 * i + 1 < N1 ? fmaf(p1[2 * i + 1], x2, p1[2 * i]) : p1[2 * i];
-#pragma unroll
-  for (int i = 0; i < N3; ++i) p3[i] = 2 * i + 1 < N2 ? fmaf(p2[2 * i + 1], x4, p2[2 * i]) : p2[2 * i];
-  return N3 == 1 ? p3[0] : fmaf(p3[1], x8, p3[0]);
+// every thread of the block; the caller synchronises
+__device__ __forceinline__ void stage_bessel(float4* tab) {
+  for (int i = threadIdx.x; i < kBesselEntries; i += blockDim.x) {
+    tab[i] = make_float4(kBesselZ0[i], kBesselC0[i], kBesselC1[i], kBesselC2[i]);
+    tab[kBesselEntries + i] = make_float4(kBesselC3[i], kBesselC4[i], kBesselC5[i], kBesselC6[i]);
+  }
 }
 
-// Eq. 9 terms for z >= 0: returns log I0e(z) = log I0(z) - z and writes
-// 1 - R(z) (R = I1/I0) to omr and q = 2z (1 - R(z)) to q.  Each is within
-// 1.5e-7 relative of the exact value over [0, 1e5] (host emulation of this
-// algorithm; the tests measure the device).
-//   z < 3.75: polynomials in t = z^2 (log I0(z) = t G(t), R(z) = z rho(t)),
-//             float64 with a float32 tail, one rounding to float32 per result;
-//   z >= 3.75: float32 rational functions u P(x)/Q(x), x = 2u - 1, u = 3.75/z,
-//             of l = log(sqrt(2 pi z) I0e(z)) and d = q - 1 (for z > 2000 d is
-//             w/4 + w^2/4 + 25w^3/64, w = 1/z), so that
-//             log I0e = (l - log(2 pi)/2) - log(z)/2, q = 1 + d and
-//             1 - R = d r + r with r = 1/(2z) from the hardware reciprocal
-//             refined by one Newton step.
-// the branch below the split (z < kBesselSplit)
-__device__ __forceinline__ float log_i0e_small(float z, float& omr, float& q) {
-  const double zd = (double)z;
-  const double x = fma(zd * zd, 2.0 / ((double)kBesselSplit * (double)kBesselSplit), -1.0);
-  const double x2 = x * x, x4 = x2 * x2;
-  const float xf = (float)x, xf2 = xf * xf, xf4 = xf2 * xf2, xf8 = xf4 * xf4;
-  static_assert(PRISM_SMALL_G_N - 4 <= 16 && PRISM_SMALL_RHO_N - 4 <= 16 && PRISM_SMALL_G_N - 4 > 8 &&
-                PRISM_SMALL_RHO_N - 4 > 8, "Estrin levels for the small-argument tails");
-  const double G = fma(x4, (double)estrin_f(kSmallGHi, xf, xf2, xf4, xf8), low4_d(kSmallG, x, x2));
-  const double rho = fma(x4, (double)estrin_f(kSmallRhoHi, xf, xf2, xf4, xf8), low4_d(kSmallRho, x, x2));
-  const double w = fma(-zd, rho, 1.0);
-  omr = (float)w;
-  q = (float)(2.0 * zd * w);
-  return (float)fma(zd * zd, G, -zd);
-}
-// the branch from the split up (z >= kBesselSplit)
-__device__ __forceinline__ float log_i0e_large(float z, float& omr, float& q) {
-  const float iz0 = rcp(z);
-  const float iz = fmaf(fmaf(-z, iz0, 1.0f), iz0, iz0);
-  const float x = fmaf(2.0f * kBesselSplit, iz, -1.0f);
-  const float u = kBesselSplit * iz;
-  const float l = (u * horner(kLargeLP, x)) * rcp(horner(kLargeLQ, x));
-  // d: its rational up to z = 2000, the large-argument expansion above
-  const float d_asym = iz * fmaf(iz, fmaf(iz, 25.0f / 64.0f, 0.25f), 0.25f);
-  const float d_rat = (u * horner(kLargeDP, x)) * rcp(horner(kLargeDQ, x));
-  const float d = z > kAsymZ ? d_asym : d_rat;
-  const float r = 0.5f * iz;
-  omr = fmaf(d, r, r);
-  q = 1.0f + d;
-  return fmaf(-kHalfLn2, lg2(z), l - kHalfLog2Pi);
-}
-// (a branch per lane: computing both for every lane and selecting, so that the
-// two dependent chains overlap, measured slower)
-__device__ __forceinline__ float log_i0e(float z, float& omr, float& q) {
-  if (z < kBesselSplit) return log_i0e_small(z, omr, q);
-  return log_i0e_large(z, omr, q);
+// nli = -log I0e(z) = z - log I0(z) and omr = 1 - I1(z)/I0(z), each within 1e-7
+// relative over [0, 1e5] (host emulation of this algorithm; the tests measure the
+// device).  omr is the derivative of nli, so one polynomial in d = z - z0 of the
+// argument's interval gives both:
+//   nli = c0 + d (c1 + d s),  omr = c1 + d (2 s + d s'),  s = c2 + ... + c6 d^4.
+// z >= kBesselSplit (any size; z NaN gives NaN): the large-argument expansions.
+__device__ __forceinline__ void rician_terms(float z, const float4* tab, float& nli, float& omr) {
+  // the interval from the float's bits, clamped into the table (negative bits, a
+  // negative NaN, too)
+  const int bits = min(max(__builtin_bit_cast(int, z), kBesselBitsLo), kBesselBitsHi);
+  const int i = (bits - kBesselBitsLo) >> kBesselShift;
+  const float4 a = tab[i], b = tab[kBesselEntries + i];
+  const float d = z - a.x;
+  float s = fmaf(b.w, d, b.z), ds = fmaf(b.w, d, s);
+  s = fmaf(s, d, b.y);
+  ds = fmaf(ds, d, s);
+  s = fmaf(s, d, b.x);
+  ds = fmaf(ds, d, s);
+  s = fmaf(s, d, a.w);
+  omr = fmaf(d, fmaf(d, ds, s + s), a.z);
+  nli = fmaf(d, fmaf(d, s, a.z), a.y);
+  if (z >= kBesselSplit) {
+    const float iz0 = rcp(z);
+    const float iz = fmaf(fmaf(-z, iz0, 1.0f), iz0, iz0);
+    const float r = 0.5f * iz;
+    omr = fmaf(0.25f * iz, r, r);
+    nli = fmaf(kHalfLn2, lg2(z), fmaf(-0.125f, iz, kHalfLog2Pi));
+  }
 }
 
 }  // namespace prism

@@ -223,7 +223,7 @@ std::vector<std::pair<int, int>> staggered_cut(const prism_problem* h, const pri
   const int waves = pass_waves_per_simd(g.K, g.mode, g.learn_d, 1);
   // the four-way split's cross-wave buffer must not cost the variant a block per CU
   constexpr size_t kLdsPerCu = 160 * 1024;
-  if (pass_lds_per_block(g.N, 3, g.K, g.learn_d, 1) * (size_t)waves > kLdsPerCu) return cut;
+  if (pass_lds_per_block(g.N, 3, g.K, g.mode, g.learn_d, 1) * (size_t)waves > kLdsPerCu) return cut;
   const int per_xcd = cus / kXcd, nq = per_xcd / 2, nh = per_xcd - nq;
   const int64_t head = (int64_t)kXcd * (nq * 64 + nh * 128);
   const int64_t full = (g.V - head) / 256, part = (g.V - head) % 256;

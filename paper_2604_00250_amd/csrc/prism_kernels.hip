@@ -659,12 +659,17 @@ hipError_t launch_rprop(float* p, const float* g, float* prev, float* step, int6
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_rician_terms(const float* z, float* li, float* omr, float* q,
                                                       int64_t n) {
+  __shared__ float4 bes[kBesselRows];
+  stage_bessel(bes);
+  __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    float o, qq;
-    li[i] = log_i0e(z[i], o, qq);
+    const float zi = z[i];
+    float nli, o;
+    rician_terms(zi, bes, nli, o);
+    li[i] = -nli;
     omr[i] = o;
-    q[i] = qq;
+    q[i] = (zi + zi) * o;
   }
 }
 

@@ -270,7 +270,8 @@ __device__ __forceinline__ void load_voxel(const PassArgs& A, const GroupDev& g,
 // per-measurement sums and the (unstored) adjoint all drop it.
 template <int MODE>
 __device__ __forceinline__ void data_term(float S, float gain, float beta, float yv, float valid,
-                                          float inv_s2, float& t_loss, float& t_sig, float& seed) {
+                                          float inv_s2, const float4* bes, float& t_loss, float& t_sig,
+                                          float& seed) {
   if (MODE == kMSE) {
     const float r = fmaf(gain, S, beta - yv) * valid;
     seed = r;
@@ -280,11 +281,12 @@ __device__ __forceinline__ void data_term(float S, float gain, float beta, float
     const float yh = fmaf(gain, S, beta);
     const float ay = fabsf(yv), ah = fabsf(yh);
     const float z = ay * ah * inv_s2;
-    float omr, qz;
-    const float li = log_i0e(z, omr, qz);
+    float nli, omr;
+    rician_terms(z, bes, nli, omr);
     const float dd = ah - ay;
-    t_loss = fmaf(dd * dd, 0.5f * inv_s2, -li) * valid;
-    t_sig = fmaf(dd * dd, inv_s2, qz) * valid;  // qz = 2z (1 - R(z))
+    const float q = dd * dd * inv_s2;
+    t_loss = fmaf(0.5f, q, nli) * valid;
+    t_sig = fmaf(z + z, omr, q) * valid;        // + 2z (1 - R(z))
     const float sd = fmaf(ay, omr, dd) * inv_s2 * valid;
     seed = yh < 0.0f ? -sd : sd;          // sgn(yhat) [(|yhat|-|y|) + |y|(1-R)] / s^2
   }
@@ -297,8 +299,9 @@ __device__ __forceinline__ void data_term(float S, float gain, float beta, float
 // per-measurement sum of sq times exp(alpha_n) is the alpha_n adjoint.
 template <int MODE>
 __device__ __forceinline__ void pair_b0(float Fsum, float& dS0, float yv, float valid, const float4 c,
-                                        float inv_s2, float& t_loss, float& t_sig, float& sq, float& seed) {
-  data_term<MODE>(Fsum, c.x, c.y, yv, valid, inv_s2, t_loss, t_sig, seed);
+                                        float inv_s2, const float4* bes, float& t_loss, float& t_sig, float& sq,
+                                        float& seed) {
+  data_term<MODE>(Fsum, c.x, c.y, yv, valid, inv_s2, bes, t_loss, t_sig, seed);
   sq = seed * Fsum;
   dS0 = fmaf(seed, c.x, dS0);
 }
@@ -306,7 +309,7 @@ __device__ __forceinline__ void pair_b0(float Fsum, float& dS0, float yv, float 
 template <int K, int MODE, bool LD>
 __device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float yv, float valid,
                                      const float4 a, const float4 b, const float4 c, float inv_s2,
-                                     float& t_loss, float& t_sig, float& sq, float& seed) {
+                                     const float4* bes, float& t_loss, float& t_sig, float& sq, float& seed) {
   using AC = Acc<K, LD>;
   // fixed D: (gx, gy, gz) = s g and cc = s cos (see stage_acquisition)
   const float gx = a.x, gy = a.y, gz = a.z;
@@ -326,7 +329,7 @@ __device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float
     S = fmaf(x.Fa[k], e1[k], S);          // Eq. 3 with Eq. 5: F_k (f_in e1 + (1 - f_in) e12)
     S = fmaf(x.Fb[k], e12[k], S);
   }
-  data_term<MODE>(S, c.x, c.y, yv, valid, inv_s2, t_loss, t_sig, seed);
+  data_term<MODE>(S, c.x, c.y, yv, valid, inv_s2, bes, t_loss, t_sig, seed);
   sq = seed * S;
   // dS = dL/dS / B: the F_c carry B, so dS F_c is the adjoint of compartment c's signal
   const float dS = seed * c.x;
@@ -378,7 +381,7 @@ __device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<
                                                  const float* yg, int64_t V, const int (&vox)[VL],
                                                  const float (&valid)[VL],
                                                  const float4* __restrict__ acq,
-                                                 int nb, int ne, int nb0, int N, float inv_s2, int lane,
+                                                 const float4* __restrict__ bes, int nb, int ne, int nb0, int N, float inv_s2, int lane,
                                                  float* wacc, double& dloss, double& dsig) {
   uint32_t voff[VL];  // byte offsets of the lane's voxels in a row of y
 #pragma unroll
@@ -407,7 +410,7 @@ __device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<
 #pragma unroll
     for (int j = 0; j < VL; ++j) {
       float tl, ts, sq, sd;
-      pair<K, MODE, LD>(x[j], acc[j], slot[j], FULL ? 1.0f : valid[j], a, b, c, inv_s2, tl, ts, sq, sd);
+      pair<K, MODE, LD>(x[j], acc[j], slot[j], FULL ? 1.0f : valid[j], a, b, c, inv_s2, bes, tl, ts, sq, sd);
       lacc += tl;
       if (MODE == kNLL) sacc += ts;
       pa = j == 0 ? sq : pa + sq;
@@ -445,7 +448,7 @@ __device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<
 #pragma unroll
     for (int j = 0; j < VL; ++j) {
       float tl, ts, sq, sd;
-      pair_b0<MODE>(Fsum[j], dS0[j], slot[j], FULL ? 1.0f : valid[j], c, inv_s2, tl, ts, sq, sd);
+      pair_b0<MODE>(Fsum[j], dS0[j], slot[j], FULL ? 1.0f : valid[j], c, inv_s2, bes, tl, ts, sq, sd);
       lacc += tl;
       if (MODE == kNLL) sacc += ts;
       pa = j == 0 ? sq : pa + sq;
@@ -511,49 +514,31 @@ __device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<
 #pragma unroll
       for (int cc = 0; cc < 3 + 2 * K; ++cc) acc[j].r[cc] += dS0[j];  // e1 = e12 = 1
   }
-  if (MODE == kMSE) {
-    // whole tiles: every path into the loop has the ring's loads in flight in slot
-    // order, so each wait is for exactly one slot
-    for (; n0 + kTile <= ne; n0 += kTile) {
-      tile_begin();
+  // whole tiles: every path into the loop has the ring's loads in flight in slot
+  // order, so each wait is for exactly one slot
+  for (; n0 + kTile <= ne; n0 += kTile) {
+    tile_begin();
 #pragma unroll 1
-      for (int t0 = 0; t0 < kTile; t0 += kPf) group(t0);
-      tile_end(kTile);
-    }
-    if (n0 < ne) {  // the range's last, partial tile
-      const int cnt = ne - n0;
-      const int full = cnt & ~(kPf - 1);  // cnt > 0
-      tile_begin();
+    for (int t0 = 0; t0 < kTile; t0 += kPf) group(t0);
+    tile_end(kTile);
+  }
+  if (n0 < ne) {  // the range's last, partial tile
+    const int cnt = ne - n0;
+    const int full = cnt & ~(kPf - 1);  // cnt > 0
+    tile_begin();
 #pragma unroll 1
-      for (int t0 = 0; t0 < full; t0 += kPf) group(t0);
-      if (full < cnt) {
+    for (int t0 = 0; t0 < full; t0 += kPf) group(t0);
+    if (full < cnt) {
 #pragma unroll
-        for (int u = 0; u < kPf; ++u) {
-          if (full + u < cnt)
-            body(full + u, u, yr[u]);
-          else
-            body_none(u);
-        }
-        group_end(full);
+      for (int u = 0; u < kPf; ++u) {
+        if (full + u < cnt)
+          body(full + u, u, yr[u]);
+        else
+          body_none(u);
       }
-      tile_end(cnt);
+      group_end(full);
     }
-  } else {
-    for (; n0 < ne; n0 += kTile) {
-      const int cnt = min(kTile, ne - n0);
-      tile_begin();
-      for (int t0 = 0; t0 < cnt; t0 += kPf) {
-#pragma unroll
-        for (int u = 0; u < kPf; ++u) {
-          if (t0 + u < cnt)
-            body(t0 + u, u, yr[u]);
-          else
-            body_none(u);
-        }
-        group_end(t0);
-      }
-      tile_end(cnt);
-    }
+    tile_end(cnt);
   }
 }
 
@@ -567,8 +552,10 @@ struct PassShared {
 
 // The fused pass over one work item (a run of one group's voxels).
 template <int K, int MODE, bool LD, int VL>
+// bes: the Eq. 9 table in LDS (NLL; stage_bessel was called, this function
+// synchronises before the first read); smem4: the rest of the dynamic LDS.
 __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __restrict__ acq_global,
-                                          const ItemDev& it, float4* smem4, PassShared& sh) {
+                                          const ItemDev& it, const float4* bes, float4* smem4, PassShared& sh) {
   auto& wrec = sh.wrec;
   constexpr int C = K + 3;
   constexpr int NACC = Acc<K, LD>::N;
@@ -628,10 +615,10 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
 
     // a chunk that lies wholly inside the item runs the loop without validity factors
     if (cb + chunk <= it.nv)
-      measurement_loop<K, MODE, LD, VL, true>(x, acc, yg, V, vox, valid, acq_tab, nb, ne, g.nb0, N, inv_s2, lane,
+      measurement_loop<K, MODE, LD, VL, true>(x, acc, yg, V, vox, valid, acq_tab, bes, nb, ne, g.nb0, N, inv_s2, lane,
                                               wacc, dloss, dsig);
     else
-      measurement_loop<K, MODE, LD, VL, false>(x, acc, yg, V, vox, valid, acq_tab, nb, ne, g.nb0, N, inv_s2, lane,
+      measurement_loop<K, MODE, LD, VL, false>(x, acc, yg, V, vox, valid, acq_tab, bes, nb, ne, g.nb0, N, inv_s2, lane,
                                                wacc, dloss, dsig);
 
     // combine the per-voxel accumulators of the waves that split this row over n
@@ -993,7 +980,8 @@ __global__ __launch_bounds__(kBlock, pass_min_waves(K, MODE, LD, VL)) void k_pas
   extern __shared__ float4 smem4[];
   __shared__ PassShared sh;
   const ItemDev it = A.items[A.item_base + xcd_item(blockIdx.x, gridDim.x)];
-  pass_item<K, MODE, LD, VL>(A, acq_global, it, smem4, sh);
+  if (MODE == kNLL) stage_bessel(smem4);
+  pass_item<K, MODE, LD, VL>(A, acq_global, it, smem4, smem4 + (MODE == kNLL ? kBesselRows : 0), sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -1039,17 +1027,19 @@ __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// dynamic LDS: acquisition table, per-wave measurement sums and the cross-wave
-// buffer of the worst measurement split in the launch (xsplit = max rows*(WN-1): 0, 2 or 3)
-inline size_t pass_lds_bytes(int maxN, int xsplit, int nacc_, int vpl) {
+// dynamic LDS: the Eq. 9 table (launches with NLL items), the acquisition table,
+// per-wave measurement sums and the cross-wave buffer of the worst measurement split
+// in the launch (xsplit = max rows*(WN-1): 0, 2 or 3)
+inline size_t pass_lds_bytes(int maxN, int xsplit, int nacc_, int vpl, bool nll) {
   size_t b = (PRISM_ACQ_SMEM ? 0 : (size_t)maxN * 3 * sizeof(float4)) + (size_t)8 * maxN * sizeof(float);
+  if (nll) b += (size_t)kBesselRows * sizeof(float4);
   b += (size_t)xsplit * nacc_ * 64 * vpl * sizeof(float);
   return b;
 }
 
 template <int K, int MODE, bool LD, int VL>
 static hipError_t launch_pass_t(const PassArgs& a, hipStream_t s, int maxN) {
-  const size_t lds = pass_lds_bytes(maxN, a.n_split, acc_count(K, LD), VL);
+  const size_t lds = pass_lds_bytes(maxN, a.n_split, acc_count(K, LD), VL, MODE == kNLL);
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)k_pass<K, MODE, LD, VL>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -18,12 +18,13 @@ __device__ __forceinline__ int item_kind(int K, int mode, int ld) { return ((K -
 
 template <int K>
 __device__ __forceinline__ void dispatch_item(const PassArgs& A, const float4* __restrict__ acq_global,
-                                              const ItemDev& it, float4* smem4, PassShared& sh) {
+                                              const ItemDev& it, const float4* bes, float4* smem4,
+                                              PassShared& sh) {
   switch (it.kind & 3) {
-    case 0: pass_item<K, kMSE, false, 1>(A, acq_global, it, smem4, sh); break;
-    case 1: pass_item<K, kMSE, true, 1>(A, acq_global, it, smem4, sh); break;
-    case 2: pass_item<K, kNLL, false, 1>(A, acq_global, it, smem4, sh); break;
-    default: pass_item<K, kNLL, true, 1>(A, acq_global, it, smem4, sh); break;
+    case 0: pass_item<K, kMSE, false, 1>(A, acq_global, it, bes, smem4, sh); break;
+    case 1: pass_item<K, kMSE, true, 1>(A, acq_global, it, bes, smem4, sh); break;
+    case 2: pass_item<K, kNLL, false, 1>(A, acq_global, it, bes, smem4, sh); break;
+    default: pass_item<K, kNLL, true, 1>(A, acq_global, it, bes, smem4, sh); break;
   }
 }
 
@@ -31,9 +32,11 @@ __device__ __forceinline__ void dispatch_item(const PassArgs& A, const float4* _
 template <int KLO, int KHI, int MINW>
 __global__ __launch_bounds__(kBlock, MINW) void k_pass_persistent(PassArgs A, const float4* __restrict__ acq_global,
                                                                   int32_t* counter) {
-  extern __shared__ float4 smem4[];
+  extern __shared__ float4 lds4[];
+  float4 *bes = lds4, *smem4 = lds4 + kBesselRows;
   __shared__ PassShared sh;
   __shared__ int next;
+  stage_bessel(bes);   // once per block; the loop's first barrier orders it
   for (;;) {
     __syncthreads();  // the previous item's LDS reads are done
     if (threadIdx.x == 0) next = atomicAdd(counter, 1);
@@ -42,12 +45,12 @@ __global__ __launch_bounds__(kBlock, MINW) void k_pass_persistent(PassArgs A, co
     if (i >= A.n_items) break;
     const ItemDev it = A.items[A.item_base + i];
     switch ((it.kind >> 2) + 1) {
-      case 1: if (KLO <= 1 && 1 <= KHI) dispatch_item<1>(A, acq_global, it, smem4, sh); break;
-      case 2: if (KLO <= 2 && 2 <= KHI) dispatch_item<2>(A, acq_global, it, smem4, sh); break;
-      case 3: if (KLO <= 3 && 3 <= KHI) dispatch_item<3>(A, acq_global, it, smem4, sh); break;
-      case 4: if (KLO <= 4 && 4 <= KHI) dispatch_item<4>(A, acq_global, it, smem4, sh); break;
-      case 5: if (KLO <= 5 && 5 <= KHI) dispatch_item<5>(A, acq_global, it, smem4, sh); break;
-      default: if (KLO <= 6 && 6 <= KHI) dispatch_item<6>(A, acq_global, it, smem4, sh); break;
+      case 1: if (KLO <= 1 && 1 <= KHI) dispatch_item<1>(A, acq_global, it, bes, smem4, sh); break;
+      case 2: if (KLO <= 2 && 2 <= KHI) dispatch_item<2>(A, acq_global, it, bes, smem4, sh); break;
+      case 3: if (KLO <= 3 && 3 <= KHI) dispatch_item<3>(A, acq_global, it, bes, smem4, sh); break;
+      case 4: if (KLO <= 4 && 4 <= KHI) dispatch_item<4>(A, acq_global, it, bes, smem4, sh); break;
+      case 5: if (KLO <= 5 && 5 <= KHI) dispatch_item<5>(A, acq_global, it, bes, smem4, sh); break;
+      default: if (KLO <= 6 && 6 <= KHI) dispatch_item<6>(A, acq_global, it, bes, smem4, sh); break;
     }
   }
 }
@@ -63,7 +66,7 @@ int persistent_class(int K) { return K <= 2 ? 0 : 1; }
 hipError_t launch_pass_persistent(const PassArgs& a, int cls, int maxN, int grid, int32_t* counter,
                                   hipStream_t s) {
   if (a.n_items <= 0) return hipSuccess;
-  const size_t lds = pass_lds_bytes(maxN, a.n_split, acc_count(kMaxK, true), 1);
+  const size_t lds = pass_lds_bytes(maxN, a.n_split, acc_count(kMaxK, true), 1, true);
   const void* fn = cls == 0 ? (const void*)k_pass_persistent<1, 2, 3>
                             : (const void*)k_pass_persistent<3, kMaxK, PRISM_PERSISTENT_MIN_WAVES>;
   if (lds > 65536) {
@@ -83,7 +86,7 @@ hipError_t launch_pass_persistent(const PassArgs& a, int cls, int maxN, int grid
 }
 
 int persistent_blocks_per_cu(int cls, int maxN, int xsplit) {
-  const size_t lds = pass_lds_bytes(maxN, xsplit, acc_count(kMaxK, true), 1);
+  const size_t lds = pass_lds_bytes(maxN, xsplit, acc_count(kMaxK, true), 1, true);
   const void* fn = cls == 0 ? (const void*)k_pass_persistent<1, 2, 3>
                             : (const void*)k_pass_persistent<3, kMaxK, PRISM_PERSISTENT_MIN_WAVES>;
   int nb = 0;
@@ -91,8 +94,8 @@ int persistent_blocks_per_cu(int cls, int maxN, int xsplit) {
   return nb > 0 ? nb : 1;
 }
 
-size_t pass_lds_per_block(int maxN, int xsplit, int K, int learn_d, int vpl) {
-  return sizeof(PassShared) + pass_lds_bytes(maxN, xsplit, acc_count(K, learn_d != 0), vpl);
+size_t pass_lds_per_block(int maxN, int xsplit, int K, int mode, int learn_d, int vpl) {
+  return sizeof(PassShared) + pass_lds_bytes(maxN, xsplit, acc_count(K, learn_d != 0), vpl, mode == kNLL);
 }
 
 int pass_waves_per_simd(int K, int mode, int learn_d, int vpl) {

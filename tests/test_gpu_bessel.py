@@ -47,6 +47,30 @@ def test_device_special_functions_meet_the_bound():
         assert e.max() <= 2e-7
 
 
+@pytest.mark.parametrize("z", [[0.125, 0.12499999], [65535.996, 65536.0, 65536.01], [1e6, 1e12, 1e30, 1e37], [0.0]])
+def test_device_special_functions_at_the_ends_of_the_table_and_beyond(z):
+    """Both sides of the table's first interval and of its end, and arguments far
+    past the range of a fit (to where 1 - R is still a normal float32): SciPy's i0e / i1e lose 1 - R beyond 1e5, where the
+    large-argument expansions are exact to float32.  The bound is that of the
+    sweep above."""
+    import torch
+    from paper_2604_00250_amd import _lib as L
+    dev = torch.tensor(z, dtype=torch.float32).cuda()
+    out = [torch.empty_like(dev) for _ in range(3)]
+    L.check(L.lib().prism_rician_terms(dev.data_ptr(), out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(),
+                                       len(z), None))
+    torch.cuda.synchronize()
+    zd = dev.cpu().numpy().astype(np.float64)
+    if zd.max() >= 1e5:
+        w = 1.0 / zd
+        ref = (-0.5 * np.log(2.0 * np.pi * zd) + w / 8, 0.5 * w * (1 + w / 4), 1 + w / 4)
+    else:
+        ref = _gen().reference(zd)
+    for got, want in zip(out, ref):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - want) <= 2e-7 * np.abs(want)), (got, want)
+
+
 def _z_range(g, th):
     prob = oracle_problem(g)
     yhat = O.synthesize(prob, theta32(th))
