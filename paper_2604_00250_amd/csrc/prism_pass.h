@@ -987,40 +987,86 @@ __global__ __launch_bounds__(kBlock, pass_min_waves(K, MODE, LD, VL)) void k_pas
 // ---------------------------------------------------------------------------
 // forward model only
 // ---------------------------------------------------------------------------
+// yhat of one (voxel, measurement) pair (Eq. 3-6)
+template <int K, bool LD>
+__device__ __forceinline__ float synth_pair(const Vox<K, LD>& x, const float4 a, const float4 b, const float4 c) {
+  float S = x.Fi[0] * b.y;
+  S = fmaf(x.Fi[1], b.z, S);
+  S = fmaf(x.Fi[2], b.w, S);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const float cc = fmaf(a.z, x.d[k][2], fmaf(a.y, x.d[k][1], a.x * x.d[k][0]));
+    const float c2 = cc * cc;
+    const float kp = LD ? a.w * x.dpar : 0.0f;
+    const float kq = LD ? b.x * x.dperp : b.x;
+    const float kd = LD ? kp - kq : c.z;
+    S = fmaf(x.Fa[k], ex2(LD ? kp * c2 : -c2), S);
+    S = fmaf(x.Fb[k], ex2(fmaf(kd, c2, kq)), S);
+  }
+  return fmaf(c.x, S, c.y);
+}
+
+// One work item: lane l of a wave has the voxels VL l .. VL l + VL - 1 of the wave's row
+// of 64 VL, stored as one vector; the block's four waves take the item's rows, or with
+// fewer rows share each row, every wave with a part of the measurements.  The stores
+// bound it: a row of V floats starts anywhere in a cache line, so each wave's piece of a
+// row has a partial line at either end.  Items in runs per XCD (neighbouring pieces meet
+// in one L2: 323 -> 301 us on 753k voxels, N = 288, K = 3) and two voxels per lane (twice
+// the bytes per piece: 274 us) make fewer of them; four voxels per lane, 278 us.  Without
+// the stores the same kernel takes 224 us, the stores alone as one fill 126 us.
+template <int K, bool LD, int VL>
+__device__ __forceinline__ void synth_item(const PassArgs& A, const GroupDev& g, const ItemDev& it,
+                                           const float4* acq, bool& zero_dir) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int rows = it.nv <= 64 * VL ? 1 : (it.nv <= 128 * VL ? 2 : 4), WN = 4 / rows;
+  const int row = wave / WN, split = wave - row * WN;
+  const int nb = (g.N * split) / WN, ne = (g.N * (split + 1)) / WN;
+  const int64_t V = g.V;
+  const uint32_t rowb = (uint32_t)V * 4u;
+  for (int cb = 64 * VL * row; cb < it.nv; cb += 64 * VL * rows) {
+    const int lv = cb + lane * VL;
+    if (lv >= it.nv) continue;
+    const bool whole = lv + VL <= it.nv;
+    Vox<K, LD> x[VL];
+#pragma unroll
+    for (int j = 0; j < VL; ++j) {
+      Derived dv;
+      load_voxel<K, LD>(A, g, it.v0 + min(lv + j, it.nv - 1), x[j], dv, zero_dir);
+    }
+    const uint32_t off = (uint32_t)(it.v0 + lv) * 4u;
+    float* out = A.yhat + g.y_off + (int64_t)nb * V;
+#pragma unroll 4
+    for (int n = nb; n < ne; ++n, out += V) {
+      const float4 a = acq[3 * n], b = acq[3 * n + 1], c = acq[3 * n + 2];
+      float r[VL];
+#pragma unroll
+      for (int j = 0; j < VL; ++j) r[j] = synth_pair<K, LD>(x[j], a, b, c);
+      if (whole) {
+        store_row_vec<VL>(out, rowb, off, r);
+      } else {
+#pragma unroll
+        for (int j = 0; j < VL; ++j)
+          if (lv + j < it.nv) store_row_f32(out, rowb, off + 4u * j, r[j]);
+      }
+    }
+  }
+}
+
 template <int K, bool LD>
 __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
   extern __shared__ float4 smem4[];
-  const ItemDev it = A.items[A.item_base + blockIdx.x];
+  const ItemDev it = A.items[A.item_base + xcd_item(blockIdx.x, gridDim.x)];
   const GroupDev g = A.groups[it.group];
   float4* acq = smem4;
   stage_acquisition(A, g, acq);
   __syncthreads();
-  const int64_t V = g.V;
-  float* out = A.yhat + g.y_off;
   bool zero_dir = false;
-  for (int lv = threadIdx.x; lv < it.nv; lv += kBlock) {
-    const int v = it.v0 + lv;
-    Vox<K, LD> x;
-    Derived dv;
-    load_voxel<K, LD>(A, g, v, x, dv, zero_dir);
-    for (int n = 0; n < g.N; ++n) {
-      const float4 a = acq[3 * n], b = acq[3 * n + 1], c = acq[3 * n + 2];
-      float S = x.Fi[0] * b.y;
-      S = fmaf(x.Fi[1], b.z, S);
-      S = fmaf(x.Fi[2], b.w, S);
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const float cc = fmaf(a.z, x.d[k][2], fmaf(a.y, x.d[k][1], a.x * x.d[k][0]));
-        const float c2 = cc * cc;
-        const float kp = LD ? a.w * x.dpar : 0.0f;
-        const float kq = LD ? b.x * x.dperp : b.x;
-        const float kd = LD ? kp - kq : c.z;
-        S = fmaf(x.Fa[k], ex2(LD ? kp * c2 : -c2), S);
-        S = fmaf(x.Fb[k], ex2(fmaf(kd, c2, kq)), S);
-      }
-      out[(int64_t)n * V + v] = fmaf(c.x, S, c.y);
-    }
-  }
+  // items of up to two rows (the cut of small and middling problems): one voxel per lane
+  // gives each row its own waves (128k voxels, N = 288: 26.3 us, two per lane 30.3)
+  if (it.nv > 128)
+    synth_item<K, LD, 2>(A, g, it, acq, zero_dir);
+  else
+    synth_item<K, LD, 1>(A, g, it, acq, zero_dir);
   if (zero_dir && A.status) atomicOr(A.status, (uint32_t)kStZeroDir);
 }
 
