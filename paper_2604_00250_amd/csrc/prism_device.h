@@ -75,15 +75,34 @@ __device__ __forceinline__ int32_t load_row_i32(const int32_t* row, uint32_t nby
   return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
 
-// Row `row` of a [rows][V] block, its base pinned in scalar registers where it
-// is used (an empty asm statement), so that the compiler builds each row's
-// buffer descriptor at its access instead of hoisting the descriptors of every
-// row (four scalar registers each) out of the loops around them, which spilled.
+// The rows of a [rows][V] block one after the other.  The row's base stays in
+// scalar registers and moves on by one addition per row; it passes through an
+// empty asm statement at each row, so the compiler can neither form the bases of
+// all rows early nor keep them across the measurement loop (formed as base + row V
+// they were hoisted out of the loop over an item's chunks and spilled: 368 scalar
+// registers of the K = 3 MSE pass, each access to one a v_readlane or v_writelane).
 template <typename T>
-__device__ __forceinline__ T* row_base(T* base, int64_t row, int64_t V) {
-  T* p = base + row * V;
-  asm volatile("" : "+s"(p));
-  return p;
+struct RowCursor {
+  T* p;
+  int64_t V;
+  __device__ __forceinline__ RowCursor(T* base, int64_t V_, int row = 0) : p(base + row * V_), V(V_) {}
+  __device__ __forceinline__ T* next() {
+    asm volatile("" : "+s"(p));
+    T* r = p;
+    p += V;
+    return r;
+  }
+};
+
+// The object at p (in memory that no kernel of the call writes) read again from here
+// on, by scalar loads: its fields are needed in the prologue and in the epilogue of an
+// item, and kept in scalar registers across the measurement loop they would spill.
+template <typename T>
+__device__ __forceinline__ const T& reread(const T* p) {
+  typedef const __attribute__((address_space(4))) T* Cp;
+  Cp c = (Cp)p;
+  asm volatile("" : "+s"(c));
+  return *(const T*)c;
 }
 
 // Work item of block b in a launch of n blocks.  The dispatcher deals blocks

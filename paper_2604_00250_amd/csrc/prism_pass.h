@@ -178,22 +178,25 @@ __device__ __forceinline__ float log_bias(const GroupDev& g, const float* cal, i
 // in the prologue (Vox for the measurement loop) and again in the epilogue
 // (Derived for the chain rule), so that nothing but Vox stays live across the
 // measurement loop.
-template <int K, bool LD>
+// PIN: the rows through a RowCursor (the fused pass, short of scalar registers).
+template <int K, bool LD, bool PIN = true>
 __device__ __forceinline__ void load_voxel(const PassArgs& A, const GroupDev& g, int v,
                                            Vox<K, LD>& x, Derived& dv, bool& zero_dir) {
   constexpr int C = K + 3;
   const float* th = A.th_micro + g.micro_off;
   const int64_t V = g.V;
   const uint32_t rowb = (uint32_t)V * 4u, off = (uint32_t)v * 4u;  // rows of V floats
-  auto at = [&](int row) { return load_row_f32(row_base(th, row, V), rowb, off); };
-  const float s = at(0);
+  RowCursor<const float> rows(th, V);                               // in the order of the block
+  int row = 0;
+  auto next = [&]() { return load_row_f32(PIN ? rows.next() : th + (row++) * V, rowb, off); };
+  const float s = next();
   dv.S0 = softplus_f(s);
   dv.sig_s = sigmoid_f(s);
   float lg[C];
   float m = -INFINITY;
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    lg[c] = at(row_logit(c));
+    lg[c] = next();
     m = fmaxf(m, lg[c]);
   }
   float sum = 0.0f;
@@ -210,9 +213,9 @@ __device__ __forceinline__ void load_voxel(const PassArgs& A, const GroupDev& g,
   for (int c = 0; c < C; ++c) dv.f[c] = lg[c] * inv;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const float vx = at(row_v(C, k, 0));
-    const float vy = at(row_v(C, k, 1));
-    const float vz = at(row_v(C, k, 2));
+    const float vx = next();
+    const float vy = next();
+    const float vz = next();
     const float n2 = fmaf(vx, vx, fmaf(vy, vy, vz * vz));
     float in = 0.0f;
     if (n2 > 0.0f) {
@@ -225,7 +228,7 @@ __device__ __forceinline__ void load_voxel(const PassArgs& A, const GroupDev& g,
     x.d[k][1] = vy * in;
     x.d[k][2] = vz * in;
   }
-  const float fin = sigmoid_f(at(row_fin(C, K)));
+  const float fin = sigmoid_f(next());
   const float omf = 1.0f - fin;
   dv.fin = fin;
   dv.omf = omf;
@@ -239,8 +242,8 @@ __device__ __forceinline__ void load_voxel(const PassArgs& A, const GroupDev& g,
     x.Fb[k] = F * omf;
   }
   if (LD) {
-    const float a = at(row_dpar(C, K));
-    const float b = at(row_dpar(C, K) + 1);
+    const float a = next();
+    const float b = next();
     x.dpar = softplus_f(a);
     x.dperp = softplus_f(b);
     dv.sig_dpar = sigmoid_f(a);
@@ -554,12 +557,13 @@ struct PassShared {
 template <int K, int MODE, bool LD, int VL>
 // bes: the Eq. 9 table in LDS (NLL; stage_bessel was called, this function
 // synchronises before the first read); smem4: the rest of the dynamic LDS.
-__device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __restrict__ acq_global,
+__device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __restrict__ acq_global,
                                           const ItemDev& it, const float4* bes, float4* smem4, PassShared& sh) {
   auto& wrec = sh.wrec;
   constexpr int C = K + 3;
   constexpr int NACC = Acc<K, LD>::N;
-  const GroupDev g = A.groups[it.group];
+  const PassArgs& A = reread(Ap);
+  const GroupDev g = reread(A.groups + it.group);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (scalar)
   const int WN = it.n_split, rows = 4 / WN;
@@ -585,8 +589,6 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
   const float* yg = A.y + g.y_off;
   const float* cal = A.th_cal + g.cal_off;
   const float inv_s2 = MODE == kNLL ? expf(-2.0f * cal[g.n_bias + 2 * N]) : 0.0f;
-  const float sdata = g.sdata;
-  const bool has_sp = (g.priors & kPriorSpatial) && g.nbh > 0;
   float* wacc = accab + wave * 2 * N;
 
   double dloss = 0.0, dsig = 0.0;
@@ -646,6 +648,11 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
 
     // epilogue: priors, chain rule to raw parameters, gradient store
     if (split == 0) {
+      const PassArgs& A = reread(Ap);
+      const GroupDev g = reread(A.groups + it.group);
+      const int64_t V = g.V;
+      const bool has_sp = (g.priors & kPriorSpatial) && g.nbh > 0;
+      const float sdata = g.sdata;
       // the chunk's epilogue terms per thread, summed over the wave after the chunk
       // (so that nothing of them is live across the measurement loop)
       double e_rep = 0.0, e_spa = 0.0;
@@ -709,11 +716,14 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
           // six neighbours per round trip: their table entries, then their weight
           // rows (an absent neighbour reads this voxel's row with factor 0)
           constexpr int kNb = 6;
+          RowCursor<const int32_t> nrows(nbr, V);
           for (int q0 = 0; q0 < g.nbh; q0 += kNb) {
             int u[kNb];
 #pragma unroll
-            for (int e = 0; e < kNb; ++e)
-              u[e] = q0 + e < g.nbh ? load_row_i32(row_base(nbr, q0 + e, V), vrowb, voff) : -1;
+            for (int e = 0; e < kNb; ++e) {
+              const int32_t* nrow = nrows.next();
+              u[e] = q0 + e < g.nbh ? load_row_i32(nrow, vrowb, voff) : -1;
+            }
             float t[kNb][C];
 #pragma unroll
             for (int e = 0; e < kNb; ++e) load_row<C>(wrow, u[e] >= 0 ? u[e] : v, C, t[e]);
@@ -856,15 +866,16 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
           // in two batches of parameters: each batch's loads are issued
           // together so that their latencies overlap, in few registers
           constexpr int kAdamBatch = (P + 1) / 2;
+          RowCursor<float> tl(th, V), ml(mm, V), vl(vv, V), ts(th, V), ms(mm, V), vs(vv, V);
 #pragma unroll
           for (int p0 = 0; p0 < P; p0 += kAdamBatch) {
             float pp[kAdamBatch], m1[kAdamBatch], v1[kAdamBatch];
 #pragma unroll
             for (int q = 0; q < kAdamBatch; ++q)
               if (p0 + q < P) {
-                pp[q] = load_row_f32(row_base(th, p0 + q, V), vrowb, voff);
-                m1[q] = load_row_f32(row_base(mm, p0 + q, V), vrowb, voff);
-                v1[q] = load_row_f32(row_base(vv, p0 + q, V), vrowb, voff);
+                pp[q] = load_row_f32(tl.next(), vrowb, voff);
+                m1[q] = load_row_f32(ml.next(), vrowb, voff);
+                v1[q] = load_row_f32(vl.next(), vrowb, voff);
               }
 #pragma unroll
             for (int q = 0; q < kAdamBatch; ++q)
@@ -872,17 +883,18 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
                 const int p = p0 + q;
                 if (!isfinite(gout[p])) bad_grad = true;
                 adam_one(pp[q], gout[p], m1[q], v1[q], A.b1, A.b2, A.eps, ss, ib);
-                store_row_f32(row_base(th, p, V), vrowb, voff, pp[q]);
-                store_row_f32(row_base(mm, p, V), vrowb, voff, m1[q]);
-                store_row_f32(row_base(vv, p, V), vrowb, voff, v1[q]);
+                store_row_f32(ts.next(), vrowb, voff, pp[q]);
+                store_row_f32(ms.next(), vrowb, voff, m1[q]);
+                store_row_f32(vs.next(), vrowb, voff, v1[q]);
               }
             __builtin_amdgcn_sched_barrier(0);
           }
         } else {
+          RowCursor<float> gs(gm, V);
 #pragma unroll
           for (int p = 0; p < P; ++p) {
             if (!isfinite(gout[p])) bad_grad = true;
-            store_row_f32(row_base(gm, p, V), vrowb, voff, gout[p]);
+            store_row_f32(gs.next(), vrowb, voff, gout[p]);
           }
         }
         // bias-field adjoint dL/dlogB(x)
@@ -896,15 +908,17 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
           const float lb0 = log_bias(g, cal, pc);
           const float B0 = D.B;
           float lt = 0.0f, gt = 0.0f;
+          RowCursor<const int32_t> frows(nbr, V);
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
             const int32_t step = 1 << (10 * a);
-            if (load_row_i32(row_base(nbr, 2 * a + 1, V), vrowb, voff) >= 0) {
+            const int32_t *below = frows.next(), *above = frows.next();
+            if (load_row_i32(above, vrowb, voff) >= 0) {
               const float dl = log_bias(g, cal, pc + step) - lb0;
               lt = fmaf(B0, fabsf(expm1f(dl)), lt);
               gt += dl > 0.0f ? -B0 : (dl < 0.0f ? B0 : 0.0f);
             }
-            if (load_row_i32(row_base(nbr, 2 * a, V), vrowb, voff) >= 0) {
+            if (load_row_i32(below, vrowb, voff) >= 0) {
               const float dl = lb0 - log_bias(g, cal, pc - step);
               gt += dl > 0.0f ? B0 : (dl < 0.0f ? -B0 : 0.0f);
             }
@@ -946,7 +960,9 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
   }
 
   // ---- item record: per-problem sums and per-measurement sums ----
-  double* rec = A.rec + g.rec_off + (int64_t)it.rec * g.rec_stride;
+  const PassArgs& Ar = reread(Ap);
+  const GroupDev& gr = reread(Ar.groups + it.group);
+  double* rec = Ar.rec + gr.rec_off + (int64_t)it.rec * gr.rec_stride;
   {
     const double sl = wave_sum_f64(dloss);
     const double ss = wave_sum_f64(dsig);
@@ -955,8 +971,8 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
       wrec[wave][7] = ss;
     }
   }
-  if (bad_grad) atomicOr(A.status, (uint32_t)kStNonfiniteGrad);
-  if (zero_dir) atomicOr(A.status, (uint32_t)kStZeroDir);
+  if (bad_grad) atomicOr(Ar.status, (uint32_t)kStNonfiniteGrad);
+  if (zero_dir) atomicOr(Ar.status, (uint32_t)kStZeroDir);
   __syncthreads();
   if (tid < kRecVals) {
     const double s = wrec[0][tid] + wrec[1][tid] + wrec[2][tid] + wrec[3][tid];
@@ -973,7 +989,13 @@ __device__ __forceinline__ void pass_item(const PassArgs& A, const float4* __res
   }
 }
 
-// One block per item of one kernel variant.
+// The launch's first argument where the launch put it (constant memory): read from
+// there field by field where they are used, not copied to registers at the start.
+__device__ __forceinline__ const PassArgs* kernel_args() {
+  return (const PassArgs*)(const __attribute__((address_space(4))) PassArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// One block per item of one kernel variant (A is read through kernel_args too).
 template <int K, int MODE, bool LD, int VL>
 __global__ __launch_bounds__(kBlock, pass_min_waves(K, MODE, LD, VL)) void k_pass(
     PassArgs A, const float4* __restrict__ acq_global) {
@@ -981,7 +1003,7 @@ __global__ __launch_bounds__(kBlock, pass_min_waves(K, MODE, LD, VL)) void k_pas
   __shared__ PassShared sh;
   const ItemDev it = A.items[A.item_base + xcd_item(blockIdx.x, gridDim.x)];
   if (MODE == kNLL) stage_bessel(smem4);
-  pass_item<K, MODE, LD, VL>(A, acq_global, it, smem4, smem4 + (MODE == kNLL ? kBesselRows : 0), sh);
+  pass_item<K, MODE, LD, VL>(kernel_args(), acq_global, it, smem4, smem4 + (MODE == kNLL ? kBesselRows : 0), sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -1031,7 +1053,7 @@ __device__ __forceinline__ void synth_item(const PassArgs& A, const GroupDev& g,
 #pragma unroll
     for (int j = 0; j < VL; ++j) {
       Derived dv;
-      load_voxel<K, LD>(A, g, it.v0 + min(lv + j, it.nv - 1), x[j], dv, zero_dir);
+      load_voxel<K, LD, false>(A, g, it.v0 + min(lv + j, it.nv - 1), x[j], dv, zero_dir);
     }
     const uint32_t off = (uint32_t)(it.v0 + lv) * 4u;
     float* out = A.yhat + g.y_off + (int64_t)nb * V;

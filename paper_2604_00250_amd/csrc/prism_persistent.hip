@@ -17,14 +17,14 @@ __global__ __launch_bounds__(256) void k_stage(PassArgs A) {
 __device__ __forceinline__ int item_kind(int K, int mode, int ld) { return ((K - 1) * 2 + mode) * 2 + ld; }
 
 template <int K>
-__device__ __forceinline__ void dispatch_item(const PassArgs& A, const float4* __restrict__ acq_global,
+__device__ __forceinline__ void dispatch_item(const PassArgs* Ap, const float4* __restrict__ acq_global,
                                               const ItemDev& it, const float4* bes, float4* smem4,
                                               PassShared& sh) {
   switch (it.kind & 3) {
-    case 0: pass_item<K, kMSE, false, 1>(A, acq_global, it, bes, smem4, sh); break;
-    case 1: pass_item<K, kMSE, true, 1>(A, acq_global, it, bes, smem4, sh); break;
-    case 2: pass_item<K, kNLL, false, 1>(A, acq_global, it, bes, smem4, sh); break;
-    default: pass_item<K, kNLL, true, 1>(A, acq_global, it, bes, smem4, sh); break;
+    case 0: pass_item<K, kMSE, false, 1>(Ap, acq_global, it, bes, smem4, sh); break;
+    case 1: pass_item<K, kMSE, true, 1>(Ap, acq_global, it, bes, smem4, sh); break;
+    case 2: pass_item<K, kNLL, false, 1>(Ap, acq_global, it, bes, smem4, sh); break;
+    default: pass_item<K, kNLL, true, 1>(Ap, acq_global, it, bes, smem4, sh); break;
   }
 }
 
@@ -45,12 +45,12 @@ __global__ __launch_bounds__(kBlock, MINW) void k_pass_persistent(PassArgs A, co
     if (i >= A.n_items) break;
     const ItemDev it = A.items[A.item_base + i];
     switch ((it.kind >> 2) + 1) {
-      case 1: if (KLO <= 1 && 1 <= KHI) dispatch_item<1>(A, acq_global, it, bes, smem4, sh); break;
-      case 2: if (KLO <= 2 && 2 <= KHI) dispatch_item<2>(A, acq_global, it, bes, smem4, sh); break;
-      case 3: if (KLO <= 3 && 3 <= KHI) dispatch_item<3>(A, acq_global, it, bes, smem4, sh); break;
-      case 4: if (KLO <= 4 && 4 <= KHI) dispatch_item<4>(A, acq_global, it, bes, smem4, sh); break;
-      case 5: if (KLO <= 5 && 5 <= KHI) dispatch_item<5>(A, acq_global, it, bes, smem4, sh); break;
-      default: if (KLO <= 6 && 6 <= KHI) dispatch_item<6>(A, acq_global, it, bes, smem4, sh); break;
+      case 1: if (KLO <= 1 && 1 <= KHI) dispatch_item<1>(kernel_args(), acq_global, it, bes, smem4, sh); break;
+      case 2: if (KLO <= 2 && 2 <= KHI) dispatch_item<2>(kernel_args(), acq_global, it, bes, smem4, sh); break;
+      case 3: if (KLO <= 3 && 3 <= KHI) dispatch_item<3>(kernel_args(), acq_global, it, bes, smem4, sh); break;
+      case 4: if (KLO <= 4 && 4 <= KHI) dispatch_item<4>(kernel_args(), acq_global, it, bes, smem4, sh); break;
+      case 5: if (KLO <= 5 && 5 <= KHI) dispatch_item<5>(kernel_args(), acq_global, it, bes, smem4, sh); break;
+      default: if (KLO <= 6 && 6 <= KHI) dispatch_item<6>(kernel_args(), acq_global, it, bes, smem4, sh); break;
     }
   }
 }
