@@ -726,7 +726,7 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
             }
             float t[kNb][C];
 #pragma unroll
-            for (int e = 0; e < kNb; ++e) load_row<C>(wrow, u[e] >= 0 ? u[e] : v, C, t[e]);
+            for (int e = 0; e < kNb; ++e) load_row<C>(wrow, u[e] >= 0 ? u[e] : v, t[e]);
 #pragma unroll
             for (int e = 0; e < kNb; ++e) {
               const float on = u[e] >= 0 ? 1.0f : 0.0f;
@@ -737,7 +737,7 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
           }
           const float fc = (float)cnt;
           float own[C];
-          load_row<C>(wrow, v, C, own);
+          load_row<C>(wrow, v, own);
 #pragma unroll
           for (int c = 0; c < C; ++c) gf[c] = fmaf(sc_sp, fmaf(own[c], fc, -sum[c]), gf[c]);
         }
