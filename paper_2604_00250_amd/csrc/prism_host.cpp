@@ -178,8 +178,17 @@ prism_launch group_launch(const prism_problem* h, const GroupDev& g) {
   return L;
 }
 
-// Voxels per work item of a group under its launch shape.
-int group_item_vox(const prism_problem* h, const prism_launch& L) {
+// Relative time of one voxel's pass: its measurements at the instructions a pair
+// takes (as issued; an exp counts two), and the prologue and epilogue, which do not
+// depend on N.
+int64_t voxel_cost(const GroupDev& g) {
+  const int pair = 19 * g.K + 20 + (g.mode == PRISM_RICIAN ? 35 : 0) + (g.learn_d ? 8 * g.K : 0);
+  return (int64_t)g.N * pair + 450 * g.K + 300;
+}
+
+// Voxels per work item of a group under its launch shape.  total: voxel_cost summed
+// over the problem.
+int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total) {
   const int vpl = L.vox_per_lane;
   const int base_chunk = 64 * vpl * 4;  // voxels per block chunk with n_split = 1
   if (L.item_vox > 0) return L.item_vox;
@@ -189,12 +198,17 @@ int group_item_vox(const prism_problem* h, const prism_launch& L) {
     // 2.4% faster than 512-voxel ones)
     return 64 * vpl * (4 / L.n_split);
   }
-  // split chosen per item: about six blocks per compute unit over the whole
-  // problem, whole chunks
-  const int64_t target = 256 * 6;
-  int64_t per = (h->n_vox + target - 1) / target;
-  per = ((per + base_chunk - 1) / base_chunk) * base_chunk;
-  return (int)std::max<int64_t>(base_chunk, std::min<int64_t>(per, 8 * base_chunk));
+  // split chosen per item: each block that the device holds at once (about two per
+  // compute unit for the mixed launches) gets about three items' worth of work, by
+  // cost: one chunk of an N = 288, K = 5 Rician group takes as long as twenty of an
+  // N = 33, K = 1 MSE group, and a launch is at least as long as its longest item.
+  // (Items of equal voxel count, six blocks per compute unit: 512 mixed patches 959 us,
+  // cut by cost 884 us.)
+  const int64_t target = total / (256 * 2 * 3);
+  const int64_t per = target / std::max<int64_t>(1, voxel_cost(g));
+  if (per < 2 * base_chunk / 4) return base_chunk / 4;   // one row, four waves on it
+  if (per < base_chunk) return base_chunk / 2;
+  return (int)std::min<int64_t>(per / base_chunk * base_chunk, 8 * base_chunk);
 }
 
 // Staggered first round (prism_launch.stagger).  All blocks of a launch of equal
@@ -258,10 +272,12 @@ int plan(prism_problem* h) {
   std::vector<int> item_vpl;
   bool keep_order = false;  // a staggered cut is launched in its own order
   std::vector<std::vector<int>> per_group(h->groups.size());
+  int64_t total = 0;
+  for (const GroupDev& g : h->groups) total += g.V * voxel_cost(g);
   for (size_t gi = 0; gi < h->groups.size(); ++gi) {
     GroupDev& g = h->groups[gi];
     const prism_launch Lg = group_launch(h, g);
-    const int item_vox = group_item_vox(h, Lg);
+    const int item_vox = group_item_vox(h, Lg, g, total);
     if (Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
       return fail(PRISM_E_INVALID, "group %d: item_vox %d is not a multiple of the block chunk %d", (int)gi,
                   item_vox, 64 * Lg.vox_per_lane * (4 / Lg.n_split));
@@ -283,7 +299,7 @@ int plan(prism_problem* h) {
     }
     g.item_count = rec;
   }
-  auto cost = [&](const ItemDev& a) { return (int64_t)a.nv * h->groups[a.group].N * (h->groups[a.group].K + 2); };
+  auto cost = [&](const ItemDev& a) { return a.nv * voxel_cost(h->groups[a.group]); };
   std::vector<Bucket> buckets;
   std::vector<ItemDev> ordered;
   ordered.reserve(items.size());
