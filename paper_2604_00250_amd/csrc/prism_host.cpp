@@ -77,12 +77,13 @@ struct prism_problem {
   std::vector<TileDev> tiles;
   std::vector<int32_t> tri_groups;
   std::vector<int32_t> acq_off;
-  int max_field_chunks = 0;
+  int n_tiles = 0;      // the first of `tiles`: k_reduce's; the rest: k_reduce_rows'
+  int max_records = 0;  // most records of a group that k_reduce reads
   int spatial_c = -1;  // C of every group with the Eq. 7 prior (-1: none yet, 0: they differ)
   int max_item_nv = 0;  // voxels of the plan's largest work item
   int persistent_grid = 0;
   int64_t n_vox = 0, n_micro = 0, n_cal = 0, n_y = 0;
-  size_t ws_rec = 0, ws_part = 0, ws_float = 0;  // element counts
+  size_t ws_rec = 0, ws_float = 0;  // element counts
   // device tables
   GroupDev* d_groups = nullptr;
   ItemDev* d_items = nullptr;
@@ -361,31 +362,26 @@ int plan(prism_problem* h) {
       load[st] += work[b];
     }
   }
-  // records and first-stage reduction tiles
-  std::vector<TileDev> tiles;
+  if (!ordered.empty()) ordered[0].first = 1;
+  // records and reduction tiles: 64 fields each for up to 32 records (four threads a
+  // column read up to eight records each), 8 fields for more
+  std::vector<TileDev> tiles, row_tiles;
   int64_t rec_off = 0;
-  int max_fc = 0;
+  int max_records = 0;
   for (size_t gi = 0; gi < h->groups.size(); ++gi) {
     GroupDev& g = h->groups[gi];
     g.rec_off = rec_off;
     rec_off += (int64_t)g.item_count * g.rec_stride;
-    const int nrr = (g.item_count + 63) / 64;
-    const int nfc = (g.rec_stride + 63) / 64;
-    max_fc = std::max(max_fc, nfc);
-    g.tile_begin = (int)tiles.size();
-    g.tile_count = nrr * nfc;
-    for (int fc = 0; fc < nfc; ++fc)
-      for (int rr = 0; rr < nrr; ++rr) {
-        TileDev t;
-        t.group = (int)gi;
-        t.r0 = rr * 64;
-        t.nr = std::min(64, g.item_count - rr * 64);
-        t.f0 = fc * 64;
-        t.nf = std::min(64, g.rec_stride - fc * 64);
-        t.out = (int)tiles.size() * 64;
-        tiles.push_back(t);
-      }
+    const bool runs = g.item_count > kReduceRowsFrom;
+    max_records = std::max(max_records, runs ? (g.item_count + kReduceRun - 1) / kReduceRun : g.item_count);
+    if (runs)
+      for (int r0 = 0; r0 < g.item_count; r0 += kReduceRun)
+        for (int f0 = 0; f0 < g.rec_stride; f0 += 64) row_tiles.push_back(TileDev{(int)gi, f0, 64, r0});
+    const int nf = g.item_count == 0 ? g.rec_stride : (g.item_count <= 32 ? 64 : 8);
+    for (int f0 = 0; f0 < g.rec_stride; f0 += nf) tiles.push_back(TileDev{(int)gi, f0, nf, 0});
   }
+  const int n_tiles = (int)tiles.size();
+  tiles.insert(tiles.end(), row_tiles.begin(), row_tiles.end());
   // the side streams and events (kept across plans; default priority)
   while ((int)h->side.size() < n_side) {
     hipStream_t st = nullptr;
@@ -406,9 +402,9 @@ int plan(prism_problem* h) {
   h->items = ordered;
   h->buckets = buckets;
   h->tiles = tiles;
-  h->max_field_chunks = max_fc;
+  h->n_tiles = n_tiles;
+  h->max_records = max_records;
   h->ws_rec = (size_t)rec_off;
-  h->ws_part = tiles.size() * 64;
   h->persistent_grid = 0;
   if (L.persistent && !h->buckets.empty()) {
     int cus = 0;
@@ -862,9 +858,9 @@ const char* prism_build_id(void) { return PRISM_SOURCE_HASH; }
 
 int32_t prism_workspace_bytes(const prism_problem* h, size_t* bytes) {
   if (!h || !bytes) return fail(PRISM_E_INVALID, "NULL argument");
-  *bytes = align256(h->ws_rec * sizeof(double)) + align256(h->ws_part * sizeof(double)) +
-           align256(h->ws_float * sizeof(float)) + align256(h->groups.size() * 3 * sizeof(double)) +
-           256;  // + the persistent launch's item counter
+  *bytes = align256(h->ws_rec * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
+           align256(h->groups.size() * 3 * sizeof(double)) +
+           512;  // + the persistent launches' item counters, the step's StepInfo
   return PRISM_OK;
 }
 
@@ -925,8 +921,8 @@ namespace {
 // Workspace carve-up and the pass: Eq. 7 weights, fused pass, reductions, the
 // trilinear bias adjoint.  `adam` (optional) turns on the fused update of the
 // per-voxel parameters in the pass epilogue; with `cal_adam` also set, the
-// calibration vector is updated where its gradient is written (k_reduce2,
-// k_bias_tri) and the step counter advances in the call's first kernel.
+// calibration vector is updated where its gradient is written (k_reduce,
+// k_bias_tri) and k_reduce advances the step counter.
 struct CalAdam {
   float* th;
   float* m;
@@ -941,7 +937,6 @@ struct History {
   double* ring;
   const int32_t* step;
   int32_t len;
-  int32_t adv;  // 1 when step[0] has already advanced when the loss rows are written
 };
 
 int run_pass(const prism_problem* h, const float* y, const float* theta_micro, const float* theta_cal,
@@ -949,21 +944,17 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
              hipStream_t s, const PassArgs* adam, const CalAdam* cal_adam = nullptr,
              const History* hist = nullptr) {
   char* ws = (char*)workspace;
-  const size_t o_part = align256(h->ws_rec * sizeof(double));
-  const size_t o_float = o_part + align256(h->ws_part * sizeof(double));
+  const size_t o_float = align256(h->ws_rec * sizeof(double));
   const size_t o_calsq = o_float + align256(h->ws_float * sizeof(float));
   const size_t o_counter = o_calsq + align256(h->groups.size() * 3 * sizeof(double));
   double* rec = (double*)ws;
-  double* part = (double*)(ws + o_part);
   float* wsp = (float*)(ws + o_float);
   double* calsq = (double*)(ws + o_calsq);
   int32_t* counter = (int32_t*)(ws + o_counter);
-  const bool have_items = !h->items.empty();
+  StepInfo* info = (StepInfo*)(ws + o_counter + 256);
   PassArgs a = pass_args(h, y, theta_micro, theta_cal, grad_micro, rec, wsp, status);
-  a.n_groups = (int)h->groups.size();
-  // the calibration prior's sums of squares come from the call's first kernel
-  // (before any parameter changes) whenever there is one
-  a.calsq = have_items ? calsq : nullptr;
+  a.calsq = calsq;
+  a.counters = counter;
   if (adam) {
     a.adam = 1;
     a.th_upd = adam->th_upd;
@@ -974,19 +965,18 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
     a.b1 = adam->b1;
     a.b2 = adam->b2;
     a.eps = adam->eps;
-    if (cal_adam) {
-      a.step_advance = cal_adam->step;
-      a.step_ready = 1;
-    }
+    if (cal_adam) a.info = info;
   }
   hipError_t e = launch_stage(a, (int)h->groups.size(), s);
   if (e != hipSuccess) return hip_fail(e, "acquisition staging launch");
-  if (!h->items.empty()) {
+  if (!h->items.empty() && h->spatial_c >= 0) {  // some group has the Eq. 7 prior
     a.item_base = 0;
     a.n_items = (int)h->items.size();
-    e = launch_spatial(a, (int)h->items.size(), std::max(h->spatial_c, 0), h->max_item_nv, s);
-    a.step_advance = nullptr;  // advanced once, by the first kernel
+    e = launch_spatial(a, (int)h->items.size(), h->spatial_c, h->max_item_nv, s);
     if (e != hipSuccess) return hip_fail(e, "spatial-prior launch");
+  } else if (h->launch.persistent) {
+    e = launch_counter_reset(counter, s);
+    if (e != hipSuccess) return hip_fail(e, "counter launch");
   }
   // concurrent variant launches fork from the caller's stream and join it again
   const int n_side = h->n_side_used;
@@ -1027,7 +1017,6 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   r.groups = h->d_groups;
   r.tiles = h->d_tiles;
   r.rec = rec;
-  r.part = part;
   r.th_cal = theta_cal;
   r.g_cal = grad_cal;
   r.loss = loss;
@@ -1036,15 +1025,20 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   r.coords = h->d_coords;
   r.status = status;
   r.model = h->model;
-  r.n_tiles = (int)h->tiles.size();
+  r.n_tiles = h->n_tiles;
+  r.row_tiles = h->d_tiles + h->n_tiles;
+  r.n_row_tiles = (int)h->tiles.size() - h->n_tiles;
   r.n_groups = (int)h->groups.size();
-  r.calsq = a.calsq;
+  r.calsq = calsq;
+  if (cal_adam) {
+    r.step = cal_adam->step;
+    r.info = info;
+  }
   if (cal_adam && cal_adam->update) {
     r.cal_adam = 1;
     r.th_cal_upd = cal_adam->th;
     r.m_cal = cal_adam->m;
     r.v_cal = cal_adam->v;
-    r.step = cal_adam->step;
     r.lr = cal_adam->lr;
     r.b1 = cal_adam->b1;
     r.b2 = cal_adam->b2;
@@ -1054,9 +1048,8 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
     r.hist = hist->ring;
     r.hist_step = hist->step;
     r.hist_len = hist->len;
-    r.hist_adv = hist->adv;
   }
-  e = launch_reduce(r, h->max_field_chunks, s);
+  e = launch_reduce(r, h->max_records, s);
   if (e != hipSuccess) return hip_fail(e, "reduction launch");
   e = launch_bias_trilinear(r, h->d_tri, (int)h->tri_groups.size(), s);
   if (e != hipSuccess) return hip_fail(e, "trilinear-bias launch");
@@ -1132,9 +1125,8 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
   for (const GroupDev& g : h->groups)
     if ((g.priors & PRISM_PRIOR_CONTINUITY) && g.nbh > 0) fuse = false;
   if (fuse && !h->items.empty()) {
-    // one call: the step counter advances in the first kernel, the per-voxel
-    // parameters are updated in the fused pass, the calibration vector where
-    // its gradient is written
+    // one call: the per-voxel parameters are updated in the fused pass, the
+    // calibration vector where its gradient is written, the step counter after both
     PassArgs ad{};
     ad.th_upd = theta_micro;
     ad.m_micro = m_micro;
@@ -1145,7 +1137,7 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
     ad.b2 = beta2;
     ad.eps = eps;
     CalAdam ca{theta_cal, m_cal, v_cal, step, lr, beta1, beta2, eps, update_cal ? 1 : 0};
-    const History hi{loss_history, step, history_len, 1};  // the first kernel advanced step[0]
+    const History hi{loss_history, step, history_len};
     return run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, &ad, &ca,
                     &hi);
   }
@@ -1159,12 +1151,12 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
     ad.b1 = beta1;
     ad.b2 = beta2;
     ad.eps = eps;
-    const History hi{loss_history, step, history_len, 0};  // advanced by the Adam launch below
+    const History hi{loss_history, step, history_len};
     rc = run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, &ad, nullptr,
                   &hi);
     if (rc != PRISM_OK) return rc;
   } else {
-    const History hi{loss_history, step, history_len, 0};
+    const History hi{loss_history, step, history_len};
     rc = run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, nullptr,
                   nullptr, &hi);
     if (rc != PRISM_OK) return rc;

@@ -53,7 +53,6 @@ struct GroupDev {
   int32_t nb0;        // measurements with b = 0 at the start of the acquisition
   int32_t rec_stride; // float64 fields per record
   int32_t item_begin, item_count;
-  int32_t tile_begin, tile_count;  // first-stage reduction tiles of this group
   float invM;         // 1/|M| (0 when the group is empty)
   // per-group float constants of the fused pass, formed once on the host (the
   // device has no scalar float unit: formed in the kernel they would sit in
@@ -73,11 +72,24 @@ struct ItemDev {
   int32_t rec;      // record index within the group
   int32_t n_split;  // waves sharing one voxel row of the block (1, 2 or 4)
   int32_t kind;     // kernel variant ((K-1)*2 + mode)*2 + learned-D, for the persistent launch
+  int32_t first;    // 1 for one item of the problem: its block leaves the call's StepInfo
 };
 
-// first-stage reduction tile: records [r0, r0+nr) of one group, fields [f0, f0+nf)
+// reduction tile: fields [f0, f0 + nf) of a group's records, one block each; nf is a power
+// of two up to 64 (the block's threads in nf columns), the last tile of a group cut at the
+// record's end; an empty group has one tile over all its fields
 struct TileDev {
-  int32_t group, r0, nr, f0, nf, out;  // out: float64 offset of the tile's partial row
+  int32_t group, f0, nf;
+  int32_t r0;       // k_reduce_rows: the run's first record (nf is 64)
+};
+constexpr int kReduceRowsFrom = 1500;  // more records than this: summed in runs first
+constexpr int kReduceRun = 64;
+
+// What the fused iteration's reductions need of the step counter, left in the workspace
+// by the fused pass, so that the reduction may advance the counter
+struct StepInfo {
+  float step_size, ibc2;   // Adam's factors for this step
+  int32_t index;           // steps completed before this one
 };
 
 struct ModelDev {
@@ -116,19 +128,18 @@ struct PassArgs {
   float* v_micro;
   const int32_t* step;
   float lr, b1, b2, eps;
-  // set by prism_iteration_adam when the step counter advances at the start of
-  // the call (k_fractions, block 0): the Adam updates then use t = step[0]
-  int32_t* step_advance;   // the counter to advance (nullptr: no advance here)
-  int32_t step_ready;      // 1: step[0] already counts this step
-  double* calsq;           // [n_groups][3] sums of squares of alpha, beta, bias (nullptr: not needed)
-  int32_t n_groups;
+  StepInfo* info;          // left by the first item's block (nullptr: not needed)
+  double* calsq;           // [n_groups][3] sums of squares of alpha, beta, bias, left by the block
+                           // of each group's first item
+  int32_t* counters;       // the persistent launches' item counters, cleared by k_fractions
 };
 
 struct ReduceArgs {
   const GroupDev* groups;
   const TileDev* tiles;
-  const double* rec;
-  double* part;            // first-stage partial rows
+  const TileDev* row_tiles;  // of k_reduce_rows
+  int32_t n_row_tiles;
+  double* rec;
   const float* th_cal;
   float* g_cal;
   double* loss;
@@ -140,19 +151,20 @@ struct ReduceArgs {
   int32_t n_tiles;
   int32_t n_groups;
   // calibration Adam applied where each gradient entry is written (fused
-  // iteration): theta_cal, moments and hyper-parameters; t = step[0]
+  // iteration): theta_cal, moments and hyper-parameters
   int32_t cal_adam;
   float* th_cal_upd;       // the same buffer as th_cal
   float* m_cal;
   float* v_cal;
-  const int32_t* step;
+  int32_t* step;           // fused iteration: advanced by k_reduce (nullptr: not here)
+  const StepInfo* info;    // fused iteration: Adam's factors and the iteration's index
   float lr, b1, b2, eps;
-  const double* calsq;     // precomputed [n_groups][3] (the cal prior's loss) or nullptr
+  const double* calsq;     // [n_groups][3] of the groups that have items (the cal prior's loss)
   // loss-history ring [hist_len][n_groups][terms] (or nullptr): the loss rows also go
-  // to slot (hist_step[0] - hist_adv) mod hist_len, the iteration's index
+  // to slot (iteration's index) mod hist_len; the index is info's, else hist_step[0]
   double* hist;
   const int32_t* hist_step;
-  int32_t hist_len, hist_adv;
+  int32_t hist_len;
 };
 
 struct StitchArgs {
@@ -169,6 +181,8 @@ struct StitchArgs {
 // spatial_c: the C shared by every group with the Eq. 7 prior (0: none, or they differ)
 // max_nv: voxels of the largest work item
 hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, hipStream_t s);
+// the persistent launches' counters, for calls without the kernels above
+hipError_t launch_counter_reset(int32_t* counters, hipStream_t s);
 hipError_t launch_stage(const PassArgs& a, int n_groups, hipStream_t s);
 // persistent launch of one register class (persistent_class(K) of its items)
 int persistent_class(int K);
@@ -184,7 +198,8 @@ template <int K>
 hipError_t launch_pass_k(const PassArgs& a, int mode, int learn_d, int vpl, int maxN, hipStream_t s);
 hipError_t launch_pass_maxn(const PassArgs& a, int K, int mode, int learn_d, int vpl, int maxN,
                             hipStream_t s);
-hipError_t launch_reduce(const ReduceArgs& a, int max_tile_fields, hipStream_t s);
+// max_records: most records of a group
+hipError_t launch_reduce(const ReduceArgs& a, int max_records, hipStream_t s);
 hipError_t launch_bias_trilinear(const ReduceArgs& a, const int32_t* tri_groups, int n_tri,
                                  hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr,

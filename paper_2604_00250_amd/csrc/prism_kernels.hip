@@ -4,8 +4,8 @@
 //
 // k_fractions, k_spatial  Eq. 7: softmax fractions, then the residual weights
 //             rho'(r)/|N| per voxel and compartment.
-// k_reduce1/2 deterministic two-stage reduction of per-item records into the
-//             calibration gradient and the loss terms.
+// k_reduce    deterministic reduction of per-item records into the calibration
+//             gradient and the loss terms.
 // k_bias_tri  gradient of the 8^3 trilinear log-bias grid.
 // k_stitch    blend of per-slab maps into whole-volume maps (slab fitting).
 // k_adam, k_rprop  optimiser steps.
@@ -60,38 +60,10 @@ __device__ __forceinline__ void fractions_item(const PassArgs& A, const GroupDev
   }
 }
 
-// The first kernel of a call also does two small jobs of the fused iteration
-// before anything reads or changes the parameters: block 0 advances the step
-// counter, and blocks n_items.. (one per group) sum the squares of the group's
-// calibration parameters for the calibration prior's loss.
 template <int CT>
 __global__ __launch_bounds__(kAuxBlock) void k_fractions(PassArgs A) {
-  if (blockIdx.x == 0 && threadIdx.x == 0 && A.step_advance) {
-    A.step_advance[0] = A.step_advance[0] + 1;
-    A.step_advance[1] = 0;
-  }
-  if ((int)blockIdx.x >= A.n_items) {
-    // one wave, fixed order (the same bits whatever the launch's block size)
-    if (threadIdx.x >= 64) return;
-    const int gi = blockIdx.x - A.n_items;
-    const GroupDev g = A.groups[gi];
-    const float* cal = A.th_cal + g.cal_off;
-    double sa = 0.0, sb = 0.0, sw = 0.0;
-    for (int i = threadIdx.x; i < g.n_bias; i += 64) sw += (double)cal[i] * cal[i];
-    for (int i = threadIdx.x; i < g.N; i += 64) {
-      sa += (double)cal[g.n_bias + i] * cal[g.n_bias + i];
-      sb += (double)cal[g.n_bias + g.N + i] * cal[g.n_bias + g.N + i];
-    }
-    sa = wave_sum_f64(sa);
-    sb = wave_sum_f64(sb);
-    sw = wave_sum_f64(sw);
-    if (threadIdx.x == 0) {
-      A.calsq[3 * gi + 0] = sa;
-      A.calsq[3 * gi + 1] = sb;
-      A.calsq[3 * gi + 2] = sw;
-    }
-    return;
-  }
+  // the persistent launches' counters, before either starts
+  if (blockIdx.x == 0 && threadIdx.x < 2) A.counters[32 * threadIdx.x] = 0;
   const ItemDev it = A.items[xcd_item(blockIdx.x, A.n_items)];
   const GroupDev g = A.groups[it.group];
   if (!((g.priors & kPriorSpatial) && g.nbh > 0)) return;
@@ -159,9 +131,9 @@ __global__ __launch_bounds__(kAuxBlock) void k_spatial(PassArgs A) {
   const ItemDev it = A.items[xcd_item(blockIdx.x, gridDim.x)];
   const GroupDev g = A.groups[it.group];
   const int tid = threadIdx.x;
+  if (!((g.priors & kPriorSpatial) && g.nbh > 0)) return;  // the fused pass writes the record's 0
   double lsum = 0.0;
-  if ((g.priors & kPriorSpatial) && g.nbh > 0)
-    with_C<CT>(g.C, [&](auto c) { lsum = spatial_item<decltype(c)::value>(A, g, it); });
+  with_C<CT>(g.C, [&](auto c) { lsum = spatial_item<decltype(c)::value>(A, g, it); });
   lsum = wave_sum_f64(lsum);
   if ((tid & 63) == 0) red[tid >> 6] = lsum;
   __syncthreads();
@@ -267,148 +239,167 @@ __global__ __launch_bounds__(256) void k_stitch(StitchArgs S) {
 }
 
 // ---------------------------------------------------------------------------
-// deterministic two-stage reduction of the item records
+// deterministic reduction of the item records
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_reduce1(ReduceArgs R) {
+// One block per tile of nf fields: its threads in nf columns, each thread of a column
+// over every (block / nf)-th record with eight loads in flight, then a tree over the
+// column in LDS (a fixed order, so the result is reproducible).  The time is the loads'
+// latency, so few records take wide tiles (64 fields, four threads a column) and many
+// take narrow ones (8 fields: still a 64-byte piece of each record) in larger blocks.
+// One launch where two stages of 64 x 64 tiles took two: 64 records of 595 fields
+// 9.4 -> 4.7 us.
+constexpr int kReduceBlock = 256, kReduceWide = 1024;
+
+// From kReduceRowsFrom records up the narrow tiles are too few compute units for the
+// bytes (3102 records of 595 fields: 14.9 us on 75 of them), so each run of kReduceRun
+// records is first summed in place into its first record, by one block per run and 64
+// fields.
+__global__ __launch_bounds__(kReduceBlock) void k_reduce_rows(ReduceArgs R) {
   __shared__ double part[4][64];
-  const TileDev t = R.tiles[blockIdx.x];
+  const TileDev t = R.row_tiles[blockIdx.x];
   const GroupDev g = R.groups[t.group];
   const int f = threadIdx.x & 63, s = threadIdx.x >> 6;
+  const int64_t st = g.rec_stride;
+  const int n = min(kReduceRun, g.item_count - t.r0);
+  double* base = R.rec + g.rec_off + (int64_t)t.r0 * st + t.f0 + f;
+  const bool on = t.f0 + f < g.rec_stride;
   double acc = 0.0;
-  if (f < t.nf) {
-    // records r0 + s, r0 + s + 4, ...; eight loads in flight per step
-    const double* base = R.rec + g.rec_off + t.f0 + f;
-    const int64_t st = g.rec_stride;
-    const int r1 = t.r0 + t.nr;
-    int r = t.r0 + s;
-    for (; r + 28 < r1; r += 32) {
-      double a[8];
+  if (on) {
+    double a[kReduceRun / 4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = base[(int64_t)(r + 4 * i) * st];
-      acc += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    }
-    for (; r < r1; r += 4) acc += base[(int64_t)r * st];
+    for (int i = 0; i < kReduceRun / 4; ++i) a[i] = base[(int64_t)min(s + 4 * i, n - 1) * st];
+#pragma unroll
+    for (int i = 0; i < kReduceRun / 4; ++i) acc += s + 4 * i < n ? a[i] : 0.0;
   }
   part[s][f] = acc;
   __syncthreads();
-  if (s == 0) R.part[(int64_t)t.out + f] = part[0][f] + part[1][f] + part[2][f] + part[3][f];
+  if (s == 0 && on) base[0] = (part[0][f] + part[1][f]) + (part[2][f] + part[3][f]);
 }
 
-__global__ __launch_bounds__(256) void k_reduce2(ReduceArgs R) {
-  __shared__ double part[4][64];
-  __shared__ double calsq[3][4];
-  const int gi = blockIdx.y, fc = blockIdx.x;
-  const GroupDev g = R.groups[gi];
-  const int nf_total = g.rec_stride;
-  const int nfc = (nf_total + 63) / 64;
-  if (fc >= nfc) return;
-  const int f = threadIdx.x & 63, s = threadIdx.x >> 6;
-  const int nrr = g.item_count > 0 ? (g.item_count + 63) / 64 : 0;
-  double acc = 0.0;
-  {
-    // partial rows s, s + 4, ...; four loads in flight per step
-    const double* pb = R.part + (int64_t)(g.tile_begin + fc * nrr) * 64 + f;
-    int rr = s;
-    for (; rr + 12 < nrr; rr += 16) {
-      const double a0 = pb[(int64_t)rr * 64], a1 = pb[(int64_t)(rr + 4) * 64];
-      const double a2 = pb[(int64_t)(rr + 8) * 64], a3 = pb[(int64_t)(rr + 12) * 64];
-      acc += (a0 + a1) + (a2 + a3);
-    }
-    for (; rr < nrr; rr += 4) acc += pb[(int64_t)rr * 64];
-  }
-  part[s][f] = acc;
+__global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
+  __shared__ double part[kReduceWide];
+  __shared__ double sq[3][kReduceWide / 64];
+  const TileDev t = R.tiles[blockIdx.x];
+  const GroupDev g = R.groups[t.group];
+  const int tid = threadIdx.x, nt = blockDim.x;
+  // the columns; an empty group has no records (and one tile, so no other block updates
+  // its calibration vector while this one sums its squares)
+  const bool empty = g.item_count == 0;
+  const int T = empty ? 1 : nt / t.nf;
   const float* cal = R.th_cal + g.cal_off;
-  float* gc = R.g_cal + g.cal_off;
   const int N = g.N, nb = g.n_bias;
   const bool cal_on = (g.priors & kPriorCal) != 0;
-  // read before any thread of this block updates the calibration vector in place
-  const float sigma_log = cal[nb + 2 * N];
-  __shared__ float adam_sc[2];
-  if (R.cal_adam && threadIdx.x == 0) adam_factors(R.step, R.lr, R.b1, R.b2, adam_sc[0], adam_sc[1], 1);
-  // calibration L2 (Sec. 2.4) on block 0 of the group (precomputed when the
-  // calibration vector is updated here)
-  if (fc == 0 && !R.calsq) {
+  if (!empty) {
+    const int f = tid & (t.nf - 1), s = tid / t.nf;
+    double acc = 0.0;
+    if (t.f0 + f < g.rec_stride) {
+      const double* base = R.rec + g.rec_off + t.f0 + f;
+      // (of a group that k_reduce_rows went over: the first record of each run)
+      const bool rows = g.item_count > kReduceRowsFrom;
+      const int64_t st = rows ? (int64_t)kReduceRun * g.rec_stride : g.rec_stride;
+      const int n = rows ? (g.item_count + kReduceRun - 1) / kReduceRun : g.item_count;
+      // rounds of eight loads (past the end: the last record again, times 0)
+      for (int r = s; r < n; r += 8 * T) {
+        double a[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = base[(int64_t)min(r + i * T, n - 1) * st];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc += r + i * T < n ? a[i] : 0.0;
+      }
+    }
+    part[f * T + s] = acc;
+    for (int w = T >> 1; w > 0; w >>= 1) {
+      __syncthreads();
+      if (s < w) part[f * T + s] += part[f * T + s + w];
+    }
+  } else if (cal_on) {
     double sa = 0.0, sb = 0.0, sw = 0.0;
-    for (int i = threadIdx.x; i < nb; i += 256) sw += (double)cal[i] * cal[i];
-    for (int i = threadIdx.x; i < N; i += 256) {
+    for (int i = tid; i < nb; i += nt) sw += (double)cal[i] * cal[i];
+    for (int i = tid; i < N; i += nt) {
       sa += (double)cal[nb + i] * cal[nb + i];
       sb += (double)cal[nb + N + i] * cal[nb + N + i];
     }
     sa = wave_sum_f64(sa);
     sb = wave_sum_f64(sb);
     sw = wave_sum_f64(sw);
-    if ((threadIdx.x & 63) == 0) {
-      calsq[0][s] = sa;
-      calsq[1][s] = sb;
-      calsq[2][s] = sw;
+    if ((tid & 63) == 0) {
+      sq[0][tid >> 6] = sa;
+      sq[1][tid >> 6] = sb;
+      sq[2][tid >> 6] = sw;
     }
   }
+  // read before any thread of this block updates the calibration vector in place
+  const float sigma_log = cal[nb + 2 * N];
   __syncthreads();
-  if (s != 0) return;
-  const int field = fc * 64 + f;
-  if (field >= nf_total) return;
-  const double tot = part[0][f] + part[1][f] + part[2][f] + part[3][f];
+  auto total = [&](int f) { return empty ? 0.0 : part[f * T]; };   // field t.f0 + f
   const double M = g.V;
   const double sdata = g.mode == kMSE ? 2.0 * (double)g.invM : 1.0;
-  float out = 0.0f;
-  bool write = false;
-  int dst = -1;
-  if (field == kRecSigma) {
-    dst = nb + 2 * N;
-    out = g.mode == kNLL ? (float)(2.0 * N * M - tot) : 0.0f;
-    write = true;
-  } else if (field >= kRecBias && field < kRecBias + 10) {
-    const int j = field - kRecBias;
-    if (g.bias == 1) {
-      dst = j;
-      out = (float)(tot + (cal_on ? 2.0 * (double)R.model.lam_bias * cal[j] : 0.0));
-      write = true;
+  for (int f = tid; f < t.nf && t.f0 + f < g.rec_stride; f += nt) {
+    const int field = t.f0 + f;
+    const double tot = total(f);
+    float out = 0.0f;
+    int dst = -1;
+    if (field == kRecSigma) {
+      dst = nb + 2 * N;
+      out = g.mode == kNLL ? (float)(2.0 * N * M - tot) : 0.0f;
+    } else if (field >= kRecBias && field < kRecBias + 10) {
+      const int j = field - kRecBias;
+      if (g.bias == 1) {
+        dst = j;
+        out = (float)(tot + (cal_on ? 2.0 * (double)R.model.lam_bias * cal[j] : 0.0));
+      }
+    } else if (field >= kRecAlpha && field < kRecAlpha + N) {
+      const int n = field - kRecAlpha;
+      dst = nb + n;
+      out = (float)(sdata * tot + (cal_on ? 2.0 * (double)R.model.lam_alpha * cal[nb + n] : 0.0));
+    } else if (field >= kRecAlpha + N) {
+      const int n = field - kRecAlpha - N;
+      dst = nb + N + n;
+      out = (float)(sdata * tot + (cal_on ? 2.0 * (double)R.model.lam_beta * cal[nb + N + n] : 0.0));
     }
-  } else if (field >= kRecAlpha && field < kRecAlpha + N) {
-    const int n = field - kRecAlpha;
-    dst = nb + n;
-    out = (float)(sdata * tot + (cal_on ? 2.0 * (double)R.model.lam_alpha * cal[nb + n] : 0.0));
-    write = true;
-  } else if (field >= kRecAlpha + N && field < kRecAlpha + 2 * N) {
-    const int n = field - kRecAlpha - N;
-    dst = nb + N + n;
-    out = (float)(sdata * tot + (cal_on ? 2.0 * (double)R.model.lam_beta * cal[nb + N + n] : 0.0));
-    write = true;
-  }
-  if (write) {
-    gc[dst] = out;
-    if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
-    if (R.cal_adam) {
-      float p = R.th_cal_upd[g.cal_off + dst], m = R.m_cal[g.cal_off + dst], v = R.v_cal[g.cal_off + dst];
-      adam_one(p, out, m, v, R.b1, R.b2, R.eps, adam_sc[0], adam_sc[1]);
-      R.th_cal_upd[g.cal_off + dst] = p;
-      R.m_cal[g.cal_off + dst] = m;
-      R.v_cal[g.cal_off + dst] = v;
+    if (dst >= 0) {
+      R.g_cal[g.cal_off + dst] = out;
+      if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
+      if (R.cal_adam) {
+        float p = R.th_cal_upd[g.cal_off + dst], m = R.m_cal[g.cal_off + dst], v = R.v_cal[g.cal_off + dst];
+        adam_one(p, out, m, v, R.b1, R.b2, R.eps, R.info->step_size, R.info->ibc2);
+        R.th_cal_upd[g.cal_off + dst] = p;
+        R.m_cal[g.cal_off + dst] = m;
+        R.v_cal[g.cal_off + dst] = v;
+      }
     }
   }
-  if (fc == 0 && f == 0) {
-    // loss terms from fields 0-7 of the LDS partials of this (first) field chunk
-    auto part_sum = [&](int fld) { return part[0][fld] + part[1][fld] + part[2][fld] + part[3][fld]; };
-    const double data = g.mode == kMSE
-                            ? part_sum(kRecData) * (double)g.invM
-                            : part_sum(kRecData) + 2.0 * (double)sigma_log * (double)N * M;
-    const double sp = part_sum(kRecSpatial) * (double)R.model.lam_sp * g.invM;
-    const double rp = part_sum(kRecRep) * (double)R.model.lam_rep * g.invM;
-    const double sa = part_sum(kRecSparse) * (double)R.model.lam_sparse * g.invM;
-    const double orp = part_sum(kRecOrphan) * (double)R.model.lam_orphan * g.invM;
-    const double cnt = part_sum(kRecCont) * (double)R.model.lam_cont * g.invM;
-    const double ord = part_sum(kRecOrder) * (double)R.model.lam_order * g.invM;
-    const double tv = part_sum(kRecTV) * (double)R.model.lam_tv * g.invM;
+  // the step counter: no other block of this launch reads it (they read R.info)
+  if (R.step && blockIdx.x == 0 && tid == 0) {
+    R.step[0] = R.step[0] + 1;
+    R.step[1] = 0;
+  }
+  if (t.f0 == 0 && tid == 0) {
+    // loss terms from fields 0-7 (every tile holds at least eight fields)
+    const double data = g.mode == kMSE ? total(kRecData) * (double)g.invM
+                                       : total(kRecData) + 2.0 * (double)sigma_log * (double)N * M;
+    const double sp = total(kRecSpatial) * (double)R.model.lam_sp * g.invM;
+    const double rp = total(kRecRep) * (double)R.model.lam_rep * g.invM;
+    const double sa = total(kRecSparse) * (double)R.model.lam_sparse * g.invM;
+    const double orp = total(kRecOrphan) * (double)R.model.lam_orphan * g.invM;
+    const double cnt = total(kRecCont) * (double)R.model.lam_cont * g.invM;
+    const double ord = total(kRecOrder) * (double)R.model.lam_order * g.invM;
+    const double tv = total(kRecTV) * (double)R.model.lam_tv * g.invM;
     double cl = 0.0;
     if (cal_on) {
-      const double* pre = R.calsq ? R.calsq + 3 * gi : nullptr;
-      const double qa = pre ? pre[0] : calsq[0][0] + calsq[0][1] + calsq[0][2] + calsq[0][3];
-      const double qb = pre ? pre[1] : calsq[1][0] + calsq[1][1] + calsq[1][2] + calsq[1][3];
-      const double qw = pre ? pre[2] : calsq[2][0] + calsq[2][1] + calsq[2][2] + calsq[2][3];
-      cl = (double)R.model.lam_alpha * qa + (double)R.model.lam_beta * qb +
-           (double)R.model.lam_bias * qw;
+      double q[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        if (!empty) {
+          q[i] = R.calsq[3 * t.group + i];
+        } else {
+          q[i] = 0.0;
+          for (int w = 0; w < nt / 64; ++w) q[i] += sq[i][w];
+        }
+      }
+      cl = (double)R.model.lam_alpha * q[0] + (double)R.model.lam_beta * q[1] + (double)R.model.lam_bias * q[2];
     }
-    double* L = R.loss + (int64_t)gi * kLossTerms;
+    double* L = R.loss + (int64_t)t.group * kLossTerms;
     L[0] = data;
     L[1] = sp;
     L[2] = rp;
@@ -421,9 +412,9 @@ __global__ __launch_bounds__(256) void k_reduce2(ReduceArgs R) {
     L[9] = data + sp + rp + sa + orp + cnt + ord + cl + tv;
     if (!isfinite(L[9])) atomicOr(R.status, (uint32_t)kStNonfiniteLoss);
     if (R.hist) {
-      int slot = (R.hist_step[0] - R.hist_adv) % R.hist_len;
+      int slot = (R.info ? R.info->index : R.hist_step[0]) % R.hist_len;
       if (slot < 0) slot += R.hist_len;
-      double* H = R.hist + ((int64_t)slot * R.n_groups + gi) * kLossTerms;
+      double* H = R.hist + ((int64_t)slot * R.n_groups + t.group) * kLossTerms;
 #pragma unroll
       for (int i = 0; i < kLossTerms; ++i) H[i] = L[i];
     }
@@ -484,8 +475,7 @@ __global__ __launch_bounds__(256) void k_bias_tri(ReduceArgs R, const int32_t* t
     R.g_cal[g.cal_off + cp] = out;
     if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
     if (R.cal_adam) {
-      float ss, ib;
-      adam_factors(R.step, R.lr, R.b1, R.b2, ss, ib, 1);
+      const float ss = R.info->step_size, ib = R.info->ibc2;
       const int64_t i = g.cal_off + cp;
       float p = R.th_cal_upd[i], m = R.m_cal[i], v = R.v_cal[i];
       adam_one(p, out, m, v, R.b1, R.b2, R.eps, ss, ib);
@@ -593,15 +583,13 @@ hipError_t launch_pass_maxn(const PassArgs& a, int K, int mode, int learn_d, int
 
 template <int CT>
 static void launch_spatial_t(const PassArgs& a, dim3 grid, dim3 block, hipStream_t s) {
-  const dim3 fgrid(grid.x + (a.calsq ? a.n_groups : 0));
-  hipLaunchKernelGGL(k_fractions<CT>, fgrid, block, 0, s, a);
+  hipLaunchKernelGGL(k_fractions<CT>, grid, block, 0, s, a);
   hipLaunchKernelGGL(k_spatial<CT>, grid, block, 0, s, a);
 }
 
 hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  // whole waves, one thread per voxel of the largest item, at most kAuxBlock;
-  // k_spatial also writes each item's (zero) record when no group has the prior
+  // whole waves, one thread per voxel of the largest item, at most kAuxBlock
   const dim3 grid(n_items), block(std::min(kAuxBlock, std::max(64, (max_nv + 63) / 64 * 64)));
   switch (spatial_c) {
     case 4: launch_spatial_t<4>(a, grid, block, s); break;
@@ -615,12 +603,13 @@ hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const ReduceArgs& a, int max_field_chunks, hipStream_t s) {
-  if (a.n_tiles > 0) hipLaunchKernelGGL(k_reduce1, dim3(a.n_tiles), dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.n_groups > 0 && max_field_chunks > 0)
-    hipLaunchKernelGGL(k_reduce2, dim3(max_field_chunks, a.n_groups), dim3(256), 0, s, a);
+hipError_t launch_reduce(const ReduceArgs& a, int max_records, hipStream_t s) {
+  if (a.n_tiles <= 0) return hipSuccess;
+  if (a.n_row_tiles > 0) hipLaunchKernelGGL(k_reduce_rows, dim3(a.n_row_tiles), dim3(kReduceBlock), 0, s, a);
+  // narrow tiles of up to 256 records: one round of loads with 32 threads a column; of
+  // more: 128 threads a column
+  const int block = max_records > 256 ? kReduceWide : kReduceBlock;
+  hipLaunchKernelGGL(k_reduce, dim3(a.n_tiles), dim3(block), 0, s, a);
   return hipGetLastError();
 }
 

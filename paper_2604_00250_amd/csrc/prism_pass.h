@@ -581,7 +581,28 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
 #endif
   for (int i = tid; i < 8 * N; i += kBlock) accab[i] = 0.0f;
   if (lane < kRecVals) wrec[wave][lane] = 0.0;
-  if (A.adam && tid == 0) adam_factors(A.step, A.lr, A.b1, A.b2, sh.adam_sc[0], sh.adam_sc[1], A.step_ready);
+  if (A.adam && tid == 0) {
+    adam_factors(A.step, A.lr, A.b1, A.b2, sh.adam_sc[0], sh.adam_sc[1]);
+    if (it.first && A.info) *A.info = StepInfo{sh.adam_sc[0], sh.adam_sc[1], A.step[0]};
+  }
+  if (it.rec == 0) {
+    // the group's first item: the squares of its calibration parameters, before
+    // anything changes them (one wave, a fixed order)
+    if (wave == 3) {
+      const float* cal = A.th_cal + g.cal_off;
+      double s[3] = {0.0, 0.0, 0.0};
+      for (int i = lane; i < g.n_bias; i += 64) s[2] += (double)cal[i] * cal[i];
+      for (int i = lane; i < N; i += 64) {
+        s[0] += (double)cal[g.n_bias + i] * cal[g.n_bias + i];
+        s[1] += (double)cal[g.n_bias + N + i] * cal[g.n_bias + N + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const double t = wave_sum_f64(s[i]);
+        if (lane == 0) A.calsq[3 * it.group + i] = t;
+      }
+    }
+  }
   __syncthreads();
 
   const int nb = (N * split) / WN, ne = (N * (split + 1)) / WN;
@@ -981,6 +1002,7 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
                       : kRecBias + (tid - 8);
     rec[field] = s;
   }
+  if (tid == kBlock - 1 && !((gr.priors & kPriorSpatial) && gr.nbh > 0)) rec[kRecSpatial] = 0.0;
   for (int n = tid; n < N; n += kBlock) {
     rec[kRecAlpha + n] = (double)accab[n] + (double)accab[2 * N + n] + (double)accab[4 * N + n] +
                          (double)accab[6 * N + n];

@@ -12,7 +12,8 @@ __global__ __launch_bounds__(256) void k_stage(PassArgs A) {
 }
 
 // Persistent launch over items of every variant: each block pops the next item
-// (largest first) from a device counter and runs that item's variant.  Every
+// (largest first) from a device counter, cleared earlier in the call, and runs that
+// item's variant.  Every
 // block leaves the loop once the counter passes the last item.
 __device__ __forceinline__ int item_kind(int K, int mode, int ld) { return ((K - 1) * 2 + mode) * 2 + ld; }
 
@@ -54,8 +55,13 @@ __global__ __launch_bounds__(kBlock, MINW) void k_pass_persistent(PassArgs A, co
     }
   }
 }
-__global__ void k_counter_reset(int32_t* counter) {
-  if (threadIdx.x == 0) counter[0] = 0;
+__global__ void k_counter_reset(int32_t* counters) {
+  if (threadIdx.x < 2) counters[32 * threadIdx.x] = 0;
+}
+
+hipError_t launch_counter_reset(int32_t* counters, hipStream_t s) {
+  hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, s, counters);
+  return hipGetLastError();
 }
 
 // The two register classes of the persistent launch: items with K <= 3 in a
@@ -73,9 +79,6 @@ hipError_t launch_pass_persistent(const PassArgs& a, int cls, int maxN, int grid
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, s, counter);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   if (cls == 0)
     hipLaunchKernelGGL((k_pass_persistent<1, 2, 3>), dim3(grid), dim3(kBlock), lds, s, a,
                        reinterpret_cast<const float4*>(a.wsp), counter);

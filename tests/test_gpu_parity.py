@@ -228,3 +228,22 @@ def test_workspace_smaller_than_required_is_rejected():
                                  None, need, st.status.data_ptr(), None)
     assert rc == L.PRISM_E_INVALID
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n_items", [1, 32, 33, 256, 257, 1500, 1501])
+def test_record_reduction_at_the_edges_of_its_tiles(n_items):
+    """Items of 64 voxels, the last one short: the reduction's wide and narrow tiles,
+    its two block sizes and the runs summed first, against the oracle."""
+    V = 64 * n_items - 5
+    shape = (5, -(-V // 500), 100)
+    mask = np.zeros(5 * shape[1] * 100, dtype=bool)
+    mask[:V] = True
+    rng = np.random.default_rng(n_items)
+    bval = np.array([0.0, 0.0, 1.0, 1.0, 2.0, 2.0, 3.0])
+    acq = I.Acquisition(bval=bval, bvec=I.uniform_sphere(bval.size, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=1, mode="mse", bias="poly2", neighbourhood=0,
+                priors=("rep", "sparse", "cal"))
+    g.y = rng.uniform(0.1, 1.0, size=(acq.n, V)).astype(np.float32)
+    g = with_theta(g, I.perturb_theta(I.init_theta(V, 1, acq.n, 10, rng), rng))
+    r = _check_groups(f"{n_items} items", [g], launch=dict(vox_per_lane=1, n_split=4, item_vox=64))
+    assert r["prob"].plan_info()["items"] == n_items
