@@ -58,6 +58,7 @@ struct Bucket {
   int vpl;     // voxels per lane of the launch (1 for the persistent launch)
   int stream;  // 0: the caller's stream; s > 0: the problem's side stream s - 1
   int cls;     // persistent launch: register class of its items (persistent_class)
+  int ls;      // lane groups per wave of the split kernel (prism_split.h); 0: the fused pass's own
   int grid;    // persistent launch: blocks
 };
 
@@ -179,18 +180,54 @@ prism_launch group_launch(const prism_problem* h, const GroupDev& g) {
   return L;
 }
 
-// Relative time of one voxel's pass: its measurements at the instructions a pair
-// takes (as issued; an exp counts two), and the prologue and epilogue, which do not
-// depend on N.
-int64_t voxel_cost(const GroupDev& g) {
+// Instructions of one voxel's measurements, as issued; an exp counts two.
+int64_t loop_cost(const GroupDev& g) {
   const int pair = 19 * g.K + 20 + (g.mode == PRISM_RICIAN ? 35 : 0) + (g.learn_d ? 8 * g.K : 0);
-  return (int64_t)g.N * pair + 450 * g.K + 300;
+  return (int64_t)g.N * pair;
+}
+// ... of its prologue and epilogue, which do not depend on N; together the relative time
+// of one voxel's pass.
+int64_t fixed_cost(const GroupDev& g) { return 450 * g.K + 300; }
+int64_t voxel_cost(const GroupDev& g) { return loop_cost(g) + fixed_cost(g); }
+
+
+// Lane groups per wave (1, 2 or 4) with which a group's items run in the split kernel
+// (prism_split.h: one row of 64, 32 or 16 voxels per block, the measurements shared by 4,
+// 8 or 16 slots), or 0: the fused pass's kernels.  It serves the four-way split of items
+// of one row; 32-bit offsets into a group's block must reach its end.  The automatic cut
+// takes the shortest rows whose blocks are all resident at once: 16 voxels up to one block
+// per compute unit, 32 up to two, since shorter rows repeat the voxels' transforms more
+// often (32 also only up to one where the measurements are less than four times that:
+// K = 1, MSE, N = 33, 12167 voxels, 24.6 us by the fused pass, 25.6 with two).  One
+// iteration, K = 3, MSE, N = 160 / K = 5, NLL, N = 288, us:
+//   voxels   fused pass     64 voxels     32            16
+//    4096   34.4 /  53.3  32.7 /  51.5  27.5 / 37.9   26.8 / 33.7
+//    8000   34.5 /  53.9  32.8 /  52.7  29.0 / 39.7   30.8 / 41.1
+//   16250   35.7 /  55.3  34.4 /  55.6  33.4 / 50.6   37.8 / 62.6
+//   32768   41.2 /  69.4  40.6 /  94.8  41.6 / 81.1   52.7 / 103
+// (K = 5 NLL blocks are resident one per compute unit: 64 voxels end at 16384.)
+int group_split(const prism_problem* h, const prism_launch& L, const GroupDev& g) {
+  if (L.persistent || L.vox_per_lane != 1 || L.n_split != 4 || (L.item_vox != 0 && L.item_vox != 64)) return 0;
+  if ((int64_t)g.V * std::max(g.N, g.P) * 4 >= ((int64_t)1 << 31)) return 0;
+  if (L.item_vox == 64) return 1;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) return 0;
+  for (int ls = 4; ls >= 1; ls /= 2) {
+    int64_t blocks = 0;
+    for (const GroupDev& q : h->groups) blocks += (q.V + 64 / ls - 1) / (64 / ls);
+    const int most = ls == 2 && loop_cost(g) < 4 * fixed_cost(g) ? 1 : 4 / ls;
+    const int64_t per_cu = std::min(most, split_blocks_per_cu(g.K, g.mode, g.learn_d, ls, g.N));
+    if (blocks <= cus * per_cu) return ls;
+  }
+  return 0;
 }
 
 // Voxels per work item of a group under its launch shape.  total: voxel_cost summed
 // over the problem.
 int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total) {
   const int vpl = L.vox_per_lane;
+  const int ls = group_split(h, L, g);
+  if (ls > 0) return 64 / ls;
   const int base_chunk = 64 * vpl * 4;  // voxels per block chunk with n_split = 1
   if (L.item_vox > 0) return L.item_vox;
   if (L.n_split > 0) {
@@ -270,7 +307,7 @@ std::vector<std::pair<int, int>> staggered_cut(const prism_problem* h, const pri
 int plan(prism_problem* h) {
   const prism_launch& L = h->launch;
   std::vector<ItemDev> items;
-  std::vector<int> item_vpl;
+  std::vector<int> item_vpl, item_ls;
   bool keep_order = false;  // a staggered cut is launched in its own order
   std::vector<std::vector<int>> per_group(h->groups.size());
   int64_t total = 0;
@@ -279,7 +316,8 @@ int plan(prism_problem* h) {
     GroupDev& g = h->groups[gi];
     const prism_launch Lg = group_launch(h, g);
     const int item_vox = group_item_vox(h, Lg, g, total);
-    if (Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
+    const int ls = group_split(h, Lg, g);
+    if (ls == 0 && Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
       return fail(PRISM_E_INVALID, "group %d: item_vox %d is not a multiple of the block chunk %d", (int)gi,
                   item_vox, 64 * Lg.vox_per_lane * (4 / Lg.n_split));
     int rec = 0;
@@ -296,6 +334,7 @@ int plan(prism_problem* h) {
       per_group[gi].push_back((int)items.size());
       items.push_back(it);
       item_vpl.push_back(Lg.vox_per_lane);
+      item_ls.push_back(ls);
       v0 += it.nv;
     }
     g.item_count = rec;
@@ -307,7 +346,7 @@ int plan(prism_problem* h) {
   if (L.persistent) {
     // one launch per register class; items largest first (LPT) within each
     for (int cls = 0; cls < 2; ++cls) {
-      Bucket b{0, 0, 0, 0, (int)ordered.size(), 0, 0, 1, 0, cls, 0};
+      Bucket b{0, 0, 0, 0, (int)ordered.size(), 0, 0, 1, 0, cls, 0, 0};
       for (const ItemDev& it : items)
         if (persistent_class(h->groups[it.group].K) == cls) ordered.push_back(it);
       std::stable_sort(ordered.begin() + b.item_begin, ordered.end(),
@@ -326,11 +365,13 @@ int plan(prism_problem* h) {
     for (size_t i0 = 0; i0 < items.size(); ++i0) {
       if (done[i0]) continue;
       const GroupDev& g0 = h->groups[items[i0].group];
-      Bucket b{g0.K, g0.mode, g0.learn_d, 0, (int)ordered.size(), 0, 0, item_vpl[i0]};
+      Bucket b{g0.K, g0.mode, g0.learn_d, 0, (int)ordered.size(), 0, 0, item_vpl[i0], 0, 0, item_ls[i0], 0};
       std::vector<ItemDev> bi;
       for (size_t i = i0; i < items.size(); ++i) {
         const GroupDev& g = h->groups[items[i].group];
-        if (done[i] || g.K != b.K || g.mode != b.mode || g.learn_d != b.learn_d || item_vpl[i] != b.vpl) continue;
+        if (done[i] || g.K != b.K || g.mode != b.mode || g.learn_d != b.learn_d || item_vpl[i] != b.vpl ||
+            item_ls[i] != b.ls)
+          continue;
         done[i] = true;
         b.maxN = std::max(b.maxN, g.N);
         bi.push_back(items[i]);
@@ -997,6 +1038,8 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
     if (timed) (void)hipEventRecord(h->ev[h->ev_used], s);
     if (h->launch.persistent)
       e = launch_pass_persistent(a, b.cls, b.maxN, b.grid, counter + 32 * b.cls, bs);
+    else if (b.ls > 0)
+      e = launch_split_maxn(a, b.K, b.mode, b.learn_d, b.ls, b.maxN, bs);
     else
       e = launch_pass_maxn(a, b.K, b.mode, b.learn_d, b.vpl, b.maxN, bs);
     if (e != hipSuccess) return hip_fail(e, "fused-pass launch");

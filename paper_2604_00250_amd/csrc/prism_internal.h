@@ -196,6 +196,14 @@ int pass_waves_per_simd(int K, int mode, int learn_d, int vpl);
 // every fused-pass variant of one K (one translation unit per K)
 template <int K>
 hipError_t launch_pass_k(const PassArgs& a, int mode, int learn_d, int vpl, int maxN, hipStream_t s);
+// the same for items of one row of 64, 32 or 16 voxels (ls = 1, 2, 4; prism_split.h)
+template <int K>
+hipError_t launch_split_k(const PassArgs& a, int mode, int learn_d, int ls, int maxN, hipStream_t s);
+// blocks of that kernel that a compute unit holds at once
+template <int K>
+int split_occupancy_k(int mode, int learn_d, int ls, int N);
+int split_blocks_per_cu(int K, int mode, int learn_d, int ls, int N);
+hipError_t launch_split_maxn(const PassArgs& a, int K, int mode, int learn_d, int ls, int maxN, hipStream_t s);
 hipError_t launch_pass_maxn(const PassArgs& a, int K, int mode, int learn_d, int vpl, int maxN,
                             hipStream_t s);
 // max_records: most records of a group

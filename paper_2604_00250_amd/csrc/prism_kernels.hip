@@ -581,6 +581,30 @@ hipError_t launch_pass_maxn(const PassArgs& a, int K, int mode, int learn_d, int
   }
 }
 
+hipError_t launch_split_maxn(const PassArgs& a, int K, int mode, int learn_d, int ls, int maxN, hipStream_t s) {
+  switch (K) {
+    case 1: return launch_split_k<1>(a, mode, learn_d, ls, maxN, s);
+    case 2: return launch_split_k<2>(a, mode, learn_d, ls, maxN, s);
+    case 3: return launch_split_k<3>(a, mode, learn_d, ls, maxN, s);
+    case 4: return launch_split_k<4>(a, mode, learn_d, ls, maxN, s);
+    case 5: return launch_split_k<5>(a, mode, learn_d, ls, maxN, s);
+    case 6: return launch_split_k<6>(a, mode, learn_d, ls, maxN, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+int split_blocks_per_cu(int K, int mode, int learn_d, int ls, int N) {
+  switch (K) {
+    case 1: return split_occupancy_k<1>(mode, learn_d, ls, N);
+    case 2: return split_occupancy_k<2>(mode, learn_d, ls, N);
+    case 3: return split_occupancy_k<3>(mode, learn_d, ls, N);
+    case 4: return split_occupancy_k<4>(mode, learn_d, ls, N);
+    case 5: return split_occupancy_k<5>(mode, learn_d, ls, N);
+    case 6: return split_occupancy_k<6>(mode, learn_d, ls, N);
+    default: return 0;
+  }
+}
+
 template <int CT>
 static void launch_spatial_t(const PassArgs& a, dim3 grid, dim3 block, hipStream_t s) {
   hipLaunchKernelGGL(k_fractions<CT>, grid, block, 0, s, a);

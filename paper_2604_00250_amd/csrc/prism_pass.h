@@ -545,6 +545,261 @@ __device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<
   }
 }
 
+// ---------------------------------------------------------------------------
+// per-voxel epilogue: priors and the chain rule to the raw parameters
+// ---------------------------------------------------------------------------
+// The Eq. 7 adjoint of voxel v, w(x)|N(x)| - sum_{u in N(x)} w(u), from the weight
+// rows [V][C]; six neighbours per round trip: their table entries, then their rows
+// (an absent neighbour reads this voxel's row with factor 0).
+template <int C>
+__device__ __forceinline__ void spatial_gather(const float* wrow, const int32_t* nbr, int nbh, int64_t V, int v,
+                                               float (&out)[C]) {
+  const uint32_t vrowb = (uint32_t)V * 4u, voff = (uint32_t)v * 4u;
+  float sum[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) sum[c] = 0.0f;
+  int cnt = 0;
+  constexpr int kNb = 6;
+  RowCursor<const int32_t> nrows(nbr, V);
+  for (int q0 = 0; q0 < nbh; q0 += kNb) {
+    int u[kNb];
+#pragma unroll
+    for (int e = 0; e < kNb; ++e) {
+      const int32_t* nrow = nrows.next();
+      u[e] = q0 + e < nbh ? load_row_i32(nrow, vrowb, voff) : -1;
+    }
+    float t[kNb][C];
+#pragma unroll
+    for (int e = 0; e < kNb; ++e) load_row<C>(wrow, u[e] >= 0 ? u[e] : v, t[e]);
+#pragma unroll
+    for (int e = 0; e < kNb; ++e) {
+      const float on = u[e] >= 0 ? 1.0f : 0.0f;
+      cnt += u[e] >= 0 ? 1 : 0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) sum[c] = fmaf(on, t[e][c], sum[c]);
+    }
+  }
+  const float fc = (float)cnt;
+  float own[C];
+  load_row<C>(wrow, v, own);
+#pragma unroll
+  for (int c = 0; c < C; ++c) out[c] = fmaf(own[c], fc, -sum[c]);
+}
+
+// a voxel's terms of the item record, and its bias-field adjoint dL/dlogB(x)
+struct VoxTerms {
+  float rep, spa, orph, cont, ord, tv, glb;
+};
+
+// The gradient gout of voxel v's raw parameters and its record terms, from the
+// measurement loop's sums, the constrained quantities D, the unit directions dir and
+// the Eq. 7 adjoint sp (not read without the prior).
+template <int K, bool LD>
+__device__ __forceinline__ void chain_rule(const PassArgs& A, const GroupDev& g, int v, const Derived& D,
+                                           const float (&dir)[K][3], const Acc<K, LD>& acc,
+                                           const float (&sp)[K + 3], float (&gout)[4 * K + 5 + (LD ? 2 : 0)],
+                                           VoxTerms& t) {
+  constexpr int C = K + 3;
+  const int64_t V = g.V;
+  const uint32_t vrowb = (uint32_t)V * 4u, voff = (uint32_t)v * 4u;  // rows of V entries
+  const float sdata = g.sdata;
+  t = VoxTerms{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  using AC = Acc<K, LD>;
+  // sum_n dS E_c per compartment (fibres: f_in e1 + (1 - f_in) e12)
+  float aE[C];
+  aE[0] = acc.r[0];
+  aE[1] = acc.r[1];
+  aE[C - 1] = acc.r[2];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    aE[2 + k] = fmaf(D.fin, acc.r[AC::kE1 + k], D.omf * acc.r[AC::kE12 + k]);
+  const float BS0 = D.B * D.S0;
+  float gF[C], gf[C];
+  float gS0 = 0.0f, slb = 0.0f;
+  const float sB = sdata * D.B;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    gF[c] = sB * aE[c];
+    gf[c] = D.S0 * gF[c];
+    gS0 = fmaf(D.f[c], gF[c], gS0);
+    slb = fmaf(BS0 * D.f[c], aE[c], slb);   // sum_n seed (yhat - beta) = sum_c F_c sum dS E_c
+  }
+  float gd[K][3];
+  float sfin = 0.0f;                          // sum_k F_k sum dS dE_k/df_in
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const float Fk = BS0 * D.f[2 + k];
+    const float sF = sdata * Fk;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) gd[k][a] = sF * acc.r[AC::kGd + 3 * k + a];
+    sfin = fmaf(Fk, acc.r[AC::kE1 + k] - acc.r[AC::kE12 + k], sfin);
+  }
+  if ((g.priors & kPriorSpatial) && g.nbh > 0) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) gf[c] = fmaf(g.sc_sp, sp[c], gf[c]);
+  }
+  if (g.priors & kPriorRep) {
+    float lr = 0.0f;
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int k = i + 1; k < K; ++k) {
+        const float dot = dir[i][0] * dir[k][0] + dir[i][1] * dir[k][1] +
+                          dir[i][2] * dir[k][2];
+        const float ad = fabsf(dot);
+        const float sg = dot > 0.0f ? 1.0f : (dot < 0.0f ? -1.0f : 0.0f);
+        const float fi = D.f[2 + i], fk = D.f[2 + k];
+        lr = fmaf(fi * fk, ad, lr);
+        gf[2 + i] = fmaf(g.sc_rep * fk, ad, gf[2 + i]);
+        gf[2 + k] = fmaf(g.sc_rep * fi, ad, gf[2 + k]);
+        const float w2 = g.sc_rep * fi * fk * sg;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          gd[i][a] = fmaf(w2, dir[k][a], gd[i][a]);
+          gd[k][a] = fmaf(w2, dir[i][a], gd[k][a]);
+        }
+      }
+    t.rep = lr;
+  }
+  if (g.priors & kPriorSparse) {
+    float ls = 0.0f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const float fk = D.f[2 + k];
+      if (fk < A.model.tau_sparse) {
+        ls += fk;
+        gf[2 + k] += g.sc_spa;
+      }
+    }
+    t.spa = ls;
+  }
+  if (g.priors & kPriorOrphan) {
+    // WM fractions where S0 is near zero: hinge max(0, 1 - S0/s0) on S0
+    const float s0o = A.model.s0_orphan;
+    const float sc = g.sc_orph;
+    const float h = fmaxf(0.0f, fmaf(-D.S0, g.inv_s0o, 1.0f));
+    float wsum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      wsum += D.f[2 + k];
+      gf[2 + k] = fmaf(sc, h, gf[2 + k]);
+    }
+    if (D.S0 < s0o) gS0 -= g.sc_orph_s0 * wsum;
+    t.orph = h * wsum;
+  }
+  if (g.priors & kPriorOrder) {
+    // fibre slots in descending order of fraction: hinge on each adjacent pair
+    const float sc = g.sc_ord;
+    float lo = 0.0f;
+#pragma unroll
+    for (int k = 0; k + 1 < K; ++k) {
+      const float gap = D.f[3 + k] - D.f[2 + k];
+      if (gap > 0.0f) {
+        lo += gap;
+        gf[3 + k] += sc;
+        gf[2 + k] -= sc;
+      }
+    }
+    t.ord = lo;
+  }
+  if ((g.priors & kPriorCont) && g.nbh > 0) {
+    // slot-wise alignment with the neighbours' directions; the pair (x, u)
+    // enters the sums of x and of u, weighted 1/|N(x)| and 1/|N(u)|
+    const int32_t* nbr = A.nbr + g.nbr_off;
+    const float* ninv = A.ninv + g.ninv_off;
+    const float* th = A.th_micro + g.micro_off;
+    const float sc2 = g.sc_cont2;
+    const float ax = ninv[v];
+    float lc = 0.0f;
+    for (int q = 0; q < g.nbh; ++q) {
+      const int u = nbr[(int64_t)q * V + v];
+      if (u < 0) continue;
+      const float w = sc2 * (ax + ninv[u]);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const float ux = th[(int64_t)row_v(C, k, 0) * V + u];
+        const float uy = th[(int64_t)row_v(C, k, 1) * V + u];
+        const float uz = th[(int64_t)row_v(C, k, 2) * V + u];
+        const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
+        const float in = n2 > 0.0f ? rsq(n2) : 0.0f;
+        const float dx = ux * in, dy = uy * in, dz = uz * in;
+        const float dot = dir[k][0] * dx + dir[k][1] * dy + dir[k][2] * dz;
+        lc = fmaf(ax, fmaf(-dot, dot, 1.0f), lc);
+        const float wd = w * dot;
+        gd[k][0] = fmaf(wd, dx, gd[k][0]);
+        gd[k][1] = fmaf(wd, dy, gd[k][1]);
+        gd[k][2] = fmaf(wd, dz, gd[k][2]);
+      }
+    }
+    t.cont = lc;
+  }
+  // softmax chain rule
+  float gsum = 0.0f;
+#pragma unroll
+  for (int c = 0; c < C; ++c) gsum = fmaf(D.f[c], gf[c], gsum);
+  gout[0] = D.sig_s * gS0;
+#pragma unroll
+  for (int c = 0; c < C; ++c) gout[row_logit(c)] = D.f[c] * (gf[c] - gsum);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const float pr = gd[k][0] * dir[k][0] + gd[k][1] * dir[k][1] + gd[k][2] * dir[k][2];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      gout[row_v(C, k, a)] = (gd[k][a] - pr * dir[k][a]) * D.invn[k];
+  }
+  gout[row_fin(C, K)] = D.fin * D.omf * sdata * sfin;
+  if (LD) {
+    gout[row_dpar(C, K)] = D.sig_dpar * sdata * acc.r[Acc<K, LD>::kDpar];
+    gout[row_dpar(C, K) + 1] = D.sig_dperp * sdata * acc.r[Acc<K, LD>::kDperp];
+  }
+  // bias-field adjoint dL/dlogB(x)
+  t.glb = sdata * slb;
+  if ((g.priors & kPriorTV) && g.bias != 0) {
+    // |B(x+e_a) - B(x)| over the in-mask face pairs: x owns the pair toward +e_a
+    // and takes the derivative of both pairs it belongs to
+    const int32_t* nbr = A.nbr + g.nbr_off;
+    const float* cal = A.th_cal + g.cal_off;
+    const int32_t pc = A.coords[g.vox_off + v];
+    const float lb0 = log_bias(g, cal, pc);
+    const float B0 = D.B;
+    float lt = 0.0f, gt = 0.0f;
+    RowCursor<const int32_t> frows(nbr, V);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int32_t step = 1 << (10 * a);
+      const int32_t *below = frows.next(), *above = frows.next();
+      if (load_row_i32(above, vrowb, voff) >= 0) {
+        const float dl = log_bias(g, cal, pc + step) - lb0;
+        lt = fmaf(B0, fabsf(expm1f(dl)), lt);
+        gt += dl > 0.0f ? -B0 : (dl < 0.0f ? B0 : 0.0f);
+      }
+      if (load_row_i32(below, vrowb, voff) >= 0) {
+        const float dl = lb0 - log_bias(g, cal, pc - step);
+        gt += dl > 0.0f ? B0 : (dl < 0.0f ? -B0 : 0.0f);
+      }
+    }
+    t.glb = fmaf(g.sc_tv, gt, t.glb);
+    t.tv = lt;
+  }
+}
+
+// The squares of a group's calibration parameters, before anything changes them: one
+// wave of the block of the group's first item, a fixed order.
+__device__ __forceinline__ void calibration_squares(const PassArgs& A, const GroupDev& g, int group, int lane) {
+  const float* cal = A.th_cal + g.cal_off;
+  double s[3] = {0.0, 0.0, 0.0};
+  for (int i = lane; i < g.n_bias; i += 64) s[2] += (double)cal[i] * cal[i];
+  for (int i = lane; i < g.N; i += 64) {
+    s[0] += (double)cal[g.n_bias + i] * cal[g.n_bias + i];
+    s[1] += (double)cal[g.n_bias + g.N + i] * cal[g.n_bias + g.N + i];
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double t = wave_sum_f64(s[i]);
+    if (lane == 0) A.calsq[3 * group + i] = t;
+  }
+}
+
 // statically sized LDS of the fused pass (one instance per kernel, shared by the
 // variants a persistent kernel inlines)
 constexpr int kRecVals = 18;  // per-thread record values of the fused pass
@@ -554,9 +809,9 @@ struct PassShared {
 };
 
 // The fused pass over one work item (a run of one group's voxels).
-template <int K, int MODE, bool LD, int VL>
 // bes: the Eq. 9 table in LDS (NLL; stage_bessel was called, this function
 // synchronises before the first read); smem4: the rest of the dynamic LDS.
+template <int K, int MODE, bool LD, int VL>
 __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __restrict__ acq_global,
                                           const ItemDev& it, const float4* bes, float4* smem4, PassShared& sh) {
   auto& wrec = sh.wrec;
@@ -585,24 +840,7 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
     adam_factors(A.step, A.lr, A.b1, A.b2, sh.adam_sc[0], sh.adam_sc[1]);
     if (it.first && A.info) *A.info = StepInfo{sh.adam_sc[0], sh.adam_sc[1], A.step[0]};
   }
-  if (it.rec == 0) {
-    // the group's first item: the squares of its calibration parameters, before
-    // anything changes them (one wave, a fixed order)
-    if (wave == 3) {
-      const float* cal = A.th_cal + g.cal_off;
-      double s[3] = {0.0, 0.0, 0.0};
-      for (int i = lane; i < g.n_bias; i += 64) s[2] += (double)cal[i] * cal[i];
-      for (int i = lane; i < N; i += 64) {
-        s[0] += (double)cal[g.n_bias + i] * cal[g.n_bias + i];
-        s[1] += (double)cal[g.n_bias + N + i] * cal[g.n_bias + N + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const double t = wave_sum_f64(s[i]);
-        if (lane == 0) A.calsq[3 * it.group + i] = t;
-      }
-    }
-  }
+  if (it.rec == 0 && wave == 3) calibration_squares(A, g, it.group, lane);
   __syncthreads();
 
   const int nb = (N * split) / WN, ne = (N * (split + 1)) / WN;
@@ -673,7 +911,6 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
       const GroupDev g = reread(A.groups + it.group);
       const int64_t V = g.V;
       const bool has_sp = (g.priors & kPriorSpatial) && g.nbh > 0;
-      const float sdata = g.sdata;
       // the chunk's epilogue terms per thread, summed over the wave after the chunk
       // (so that nothing of them is live across the measurement loop)
       double e_rep = 0.0, e_spa = 0.0;
@@ -682,9 +919,6 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
 #pragma unroll
       for (int q = 0; q < 10; ++q) e_b[q] = 0.0f;
       float* gm = A.g_micro + g.micro_off;
-      const float sc_rep = g.sc_rep;
-      const float sc_spa = g.sc_spa;
-      const float sc_sp = g.sc_sp;
 #pragma unroll
       for (int j = 0; j < VL; ++j) {
         if (valid[j] == 0.0f) continue;
@@ -696,187 +930,18 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
           bool zd = false;
           load_voxel<K, LD>(A, g, v, x_again, D, zd);
         }
-        using AC = Acc<K, LD>;
-        // sum_n dS E_c per compartment (fibres: f_in e1 + (1 - f_in) e12)
-        float aE[C];
-        aE[0] = acc[j].r[0];
-        aE[1] = acc[j].r[1];
-        aE[C - 1] = acc[j].r[2];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-          aE[2 + k] = fmaf(D.fin, acc[j].r[AC::kE1 + k], D.omf * acc[j].r[AC::kE12 + k]);
-        const float BS0 = D.B * D.S0;
-        float gF[C], gf[C];
-        float gS0 = 0.0f, slb = 0.0f;
-        const float sB = sdata * D.B;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          gF[c] = sB * aE[c];
-          gf[c] = D.S0 * gF[c];
-          gS0 = fmaf(D.f[c], gF[c], gS0);
-          slb = fmaf(BS0 * D.f[c], aE[c], slb);   // sum_n seed (yhat - beta) = sum_c F_c sum dS E_c
-        }
-        float gd[K][3];
-        float sfin = 0.0f;                          // sum_k F_k sum dS dE_k/df_in
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const float Fk = BS0 * D.f[2 + k];
-          const float sF = sdata * Fk;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) gd[k][a] = sF * acc[j].r[AC::kGd + 3 * k + a];
-          sfin = fmaf(Fk, acc[j].r[AC::kE1 + k] - acc[j].r[AC::kE12 + k], sfin);
-        }
-        if (has_sp) {
-          // Eq. 7 adjoint: w(x)|N(x)| - sum_{u in N(x)} w(u), weight rows [V][C]
-          const float* wrow = A.wsp + g.w_off;
-          const int32_t* nbr = A.nbr + g.nbr_off;
-          float sum[C];
-#pragma unroll
-          for (int c = 0; c < C; ++c) sum[c] = 0.0f;
-          int cnt = 0;
-          // six neighbours per round trip: their table entries, then their weight
-          // rows (an absent neighbour reads this voxel's row with factor 0)
-          constexpr int kNb = 6;
-          RowCursor<const int32_t> nrows(nbr, V);
-          for (int q0 = 0; q0 < g.nbh; q0 += kNb) {
-            int u[kNb];
-#pragma unroll
-            for (int e = 0; e < kNb; ++e) {
-              const int32_t* nrow = nrows.next();
-              u[e] = q0 + e < g.nbh ? load_row_i32(nrow, vrowb, voff) : -1;
-            }
-            float t[kNb][C];
-#pragma unroll
-            for (int e = 0; e < kNb; ++e) load_row<C>(wrow, u[e] >= 0 ? u[e] : v, t[e]);
-#pragma unroll
-            for (int e = 0; e < kNb; ++e) {
-              const float on = u[e] >= 0 ? 1.0f : 0.0f;
-              cnt += u[e] >= 0 ? 1 : 0;
-#pragma unroll
-              for (int c = 0; c < C; ++c) sum[c] = fmaf(on, t[e][c], sum[c]);
-            }
-          }
-          const float fc = (float)cnt;
-          float own[C];
-          load_row<C>(wrow, v, own);
-#pragma unroll
-          for (int c = 0; c < C; ++c) gf[c] = fmaf(sc_sp, fmaf(own[c], fc, -sum[c]), gf[c]);
-        }
-        if (g.priors & kPriorRep) {
-          float lr = 0.0f;
-#pragma unroll
-          for (int i = 0; i < K; ++i)
-#pragma unroll
-            for (int k = i + 1; k < K; ++k) {
-              const float dot = x[j].d[i][0] * x[j].d[k][0] + x[j].d[i][1] * x[j].d[k][1] +
-                                x[j].d[i][2] * x[j].d[k][2];
-              const float ad = fabsf(dot);
-              const float sg = dot > 0.0f ? 1.0f : (dot < 0.0f ? -1.0f : 0.0f);
-              const float fi = D.f[2 + i], fk = D.f[2 + k];
-              lr = fmaf(fi * fk, ad, lr);
-              gf[2 + i] = fmaf(sc_rep * fk, ad, gf[2 + i]);
-              gf[2 + k] = fmaf(sc_rep * fi, ad, gf[2 + k]);
-              const float w2 = sc_rep * fi * fk * sg;
-#pragma unroll
-              for (int a = 0; a < 3; ++a) {
-                gd[i][a] = fmaf(w2, x[j].d[k][a], gd[i][a]);
-                gd[k][a] = fmaf(w2, x[j].d[i][a], gd[k][a]);
-              }
-            }
-          e_rep += (double)lr;
-        }
-        if (g.priors & kPriorSparse) {
-          float ls = 0.0f;
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-            const float fk = D.f[2 + k];
-            if (fk < A.model.tau_sparse) {
-              ls += fk;
-              gf[2 + k] += sc_spa;
-            }
-          }
-          e_spa += (double)ls;
-        }
-        if (g.priors & kPriorOrphan) {
-          // WM fractions where S0 is near zero: hinge max(0, 1 - S0/s0) on S0
-          const float s0o = A.model.s0_orphan;
-          const float sc = g.sc_orph;
-          const float h = fmaxf(0.0f, fmaf(-D.S0, g.inv_s0o, 1.0f));
-          float wsum = 0.0f;
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-            wsum += D.f[2 + k];
-            gf[2 + k] = fmaf(sc, h, gf[2 + k]);
-          }
-          if (D.S0 < s0o) gS0 -= g.sc_orph_s0 * wsum;
-          e_orph += h * wsum;
-        }
-        if (g.priors & kPriorOrder) {
-          // fibre slots in descending order of fraction: hinge on each adjacent pair
-          const float sc = g.sc_ord;
-          float lo = 0.0f;
-#pragma unroll
-          for (int k = 0; k + 1 < K; ++k) {
-            const float gap = D.f[3 + k] - D.f[2 + k];
-            if (gap > 0.0f) {
-              lo += gap;
-              gf[3 + k] += sc;
-              gf[2 + k] -= sc;
-            }
-          }
-          e_ord += lo;
-        }
-        if ((g.priors & kPriorCont) && g.nbh > 0) {
-          // slot-wise alignment with the neighbours' directions; the pair (x, u)
-          // enters the sums of x and of u, weighted 1/|N(x)| and 1/|N(u)|
-          const int32_t* nbr = A.nbr + g.nbr_off;
-          const float* ninv = A.ninv + g.ninv_off;
-          const float* th = A.th_micro + g.micro_off;
-          const float sc2 = g.sc_cont2;
-          const float ax = ninv[v];
-          float lc = 0.0f;
-          for (int q = 0; q < g.nbh; ++q) {
-            const int u = nbr[(int64_t)q * V + v];
-            if (u < 0) continue;
-            const float w = sc2 * (ax + ninv[u]);
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const float ux = th[(int64_t)row_v(C, k, 0) * V + u];
-              const float uy = th[(int64_t)row_v(C, k, 1) * V + u];
-              const float uz = th[(int64_t)row_v(C, k, 2) * V + u];
-              const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-              const float in = n2 > 0.0f ? rsq(n2) : 0.0f;
-              const float dx = ux * in, dy = uy * in, dz = uz * in;
-              const float dot = x[j].d[k][0] * dx + x[j].d[k][1] * dy + x[j].d[k][2] * dz;
-              lc = fmaf(ax, fmaf(-dot, dot, 1.0f), lc);
-              const float wd = w * dot;
-              gd[k][0] = fmaf(wd, dx, gd[k][0]);
-              gd[k][1] = fmaf(wd, dy, gd[k][1]);
-              gd[k][2] = fmaf(wd, dz, gd[k][2]);
-            }
-          }
-          e_cont += lc;
-        }
-        // softmax chain rule
-        float gsum = 0.0f;
-#pragma unroll
-        for (int c = 0; c < C; ++c) gsum = fmaf(D.f[c], gf[c], gsum);
-        float gout[4 * kMaxK + 7];
-        gout[0] = D.sig_s * gS0;
-#pragma unroll
-        for (int c = 0; c < C; ++c) gout[row_logit(c)] = D.f[c] * (gf[c] - gsum);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const float pr = gd[k][0] * x[j].d[k][0] + gd[k][1] * x[j].d[k][1] + gd[k][2] * x[j].d[k][2];
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-            gout[row_v(C, k, a)] = (gd[k][a] - pr * x[j].d[k][a]) * D.invn[k];
-        }
-        gout[row_fin(C, K)] = D.fin * D.omf * sdata * sfin;
-        if (LD) {
-          gout[row_dpar(C, K)] = D.sig_dpar * sdata * acc[j].r[Acc<K, LD>::kDpar];
-          gout[row_dpar(C, K) + 1] = D.sig_dperp * sdata * acc[j].r[Acc<K, LD>::kDperp];
-        }
+        float sp[C];
+        if (has_sp) spatial_gather<C>(A.wsp + g.w_off, A.nbr + g.nbr_off, g.nbh, V, v, sp);
+        float gout[4 * K + 5 + (LD ? 2 : 0)];
+        VoxTerms vt;
+        chain_rule<K, LD>(A, g, v, D, x[j].d, acc[j], sp, gout, vt);
+        if (g.priors & kPriorRep) e_rep += (double)vt.rep;
+        if (g.priors & kPriorSparse) e_spa += (double)vt.spa;
+        if (g.priors & kPriorOrphan) e_orph += vt.orph;
+        if ((g.priors & kPriorCont) && g.nbh > 0) e_cont += vt.cont;
+        if (g.priors & kPriorOrder) e_ord += vt.ord;
+        if ((g.priors & kPriorTV) && g.bias != 0) e_tv += vt.tv;
+        const float glb = vt.glb;
         constexpr int P = 4 * K + 5 + (LD ? 2 : 0);
         if (A.adam) {
           // fused Adam on this voxel's parameters (only this thread touches them)
@@ -917,35 +982,6 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
             if (!isfinite(gout[p])) bad_grad = true;
             store_row_f32(gs.next(), vrowb, voff, gout[p]);
           }
-        }
-        // bias-field adjoint dL/dlogB(x)
-        float glb = sdata * slb;
-        if ((g.priors & kPriorTV) && g.bias != 0) {
-          // |B(x+e_a) - B(x)| over the in-mask face pairs: x owns the pair toward +e_a
-          // and takes the derivative of both pairs it belongs to
-          const int32_t* nbr = A.nbr + g.nbr_off;
-          const float* cal = A.th_cal + g.cal_off;
-          const int32_t pc = A.coords[g.vox_off + v];
-          const float lb0 = log_bias(g, cal, pc);
-          const float B0 = D.B;
-          float lt = 0.0f, gt = 0.0f;
-          RowCursor<const int32_t> frows(nbr, V);
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            const int32_t step = 1 << (10 * a);
-            const int32_t *below = frows.next(), *above = frows.next();
-            if (load_row_i32(above, vrowb, voff) >= 0) {
-              const float dl = log_bias(g, cal, pc + step) - lb0;
-              lt = fmaf(B0, fabsf(expm1f(dl)), lt);
-              gt += dl > 0.0f ? -B0 : (dl < 0.0f ? B0 : 0.0f);
-            }
-            if (load_row_i32(below, vrowb, voff) >= 0) {
-              const float dl = lb0 - log_bias(g, cal, pc - step);
-              gt += dl > 0.0f ? B0 : (dl < 0.0f ? -B0 : 0.0f);
-            }
-          }
-          glb = fmaf(g.sc_tv, gt, glb);
-          e_tv += lt;
         }
         if (g.bias == 1) {
           const int32_t pc = A.coords[g.vox_off + v];

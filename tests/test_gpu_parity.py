@@ -247,3 +247,37 @@ def test_record_reduction_at_the_edges_of_its_tiles(n_items):
     g = with_theta(g, I.perturb_theta(I.init_theta(V, 1, acq.n, 10, rng), rng))
     r = _check_groups(f"{n_items} items", [g], launch=dict(vox_per_lane=1, n_split=4, item_vox=64))
     assert r["prob"].plan_info()["items"] == n_items
+
+
+@pytest.mark.parametrize("V,N", [(1, 1), (15, 3), (16, 17), (17, 33), (4095, 7), (4097, 31), (8190, 16), (8193, 40),
+                                 (16386, 5)])
+@pytest.mark.parametrize("K,mode,learn_d", [(1, "mse", False), (3, "nll", False), (2, "mse", True), (6, "nll", True)])
+def test_small_problems_in_rows_of_16_32_and_64_voxels(V, N, K, mode, learn_d):
+    """The split kernels at the ends of their ranges: fewer measurements than slots and
+    ragged shares, short last rows, both sides of each change of row length; gradient
+    against the oracle and the fused Adam step bit for bit the unfused one's."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(V + 100 * N + K)
+    shape = (3, -(-V // 60), 20)
+    mask = np.zeros(60 * shape[1], dtype=bool)
+    mask[:V] = True
+    bval = np.sort(rng.integers(0, 4, size=N)).astype(np.float64)
+    bval[-1] = max(bval[-1], 1.0)   # at b = 0 alone the data term has no gradient in the fractions
+    acq = I.Acquisition(bval=bval, bvec=I.uniform_sphere(N, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=K, mode=mode, bias="poly2", learn_diffusivity=learn_d,
+                neighbourhood=6)
+    g.y = rng.uniform(0.05, 1.0, size=(N, V)).astype(np.float32)
+    g = with_theta(g, I.perturb_theta(I.init_theta(V, K, N, 10, rng, sigma_init=0.1 if mode == "nll" else 0.0,
+                                                   learn_diffusivity=learn_d), rng, scale=0.3))
+    _check_groups(f"V={V} N={N} K={K} {mode}", [g])
+    states = []
+    for fused in (True, False):
+        prob = Problem([g])
+        st = DeviceState(prob, ys=[g.y], thetas=[g.theta])
+        for _ in range(2):
+            st.iteration(lr=1e-2) if fused else st.iteration_unfused(lr=1e-2)
+        torch.cuda.synchronize()
+        states.append(st)
+    for a in ("params", "m", "v", "step", "loss"):
+        assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
