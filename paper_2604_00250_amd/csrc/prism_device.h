@@ -75,6 +75,13 @@ __device__ __forceinline__ int32_t load_row_i32(const int32_t* row, uint32_t nby
   return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
 
+// Four int32 at p + 4 i (16-byte aligned, in memory that no kernel of the call writes) by
+// scalar loads; i is uniform.
+__device__ __forceinline__ int4 uniform_int4(const int32_t* p, int i) {
+  typedef const __attribute__((address_space(4))) int4* Cp;
+  return *(const int4*)((Cp)p + i);
+}
+
 // The rows of a [rows][V] block one after the other.  The row's base stays in
 // scalar registers and moves on by one addition per row; it passes through an
 // empty asm statement at each row, so the compiler can neither form the bases of
@@ -182,6 +189,51 @@ __device__ __forceinline__ void row_scatter_group(RowScatter& s, bool here) {
   float t = s.q + dpp_f32<0x141>(s.q);  // row_half_mirror: lane xor 7
   t += dpp_f32<0x140>(t);               // row_mirror: lane xor 15
   s.acc = here ? t : s.acc;
+}
+
+// Sums over the wave of two values per lane per measurement, for a group of four
+// measurements (0..3): afterwards lane l holds the wave's sum of value l / 32 for
+// measurement group_sums_index(l) (the same in the eight lanes of its half row).  The two
+// values share a register from the first step on: v_permlane32_swap exchanges the upper half
+// of one register with the lower half of the other, so one addition then leaves the first
+// value's sums in the lower half and the second's in the upper half; v_permlane16_swap
+// does the same for two measurements and the rows of each half, and a select with the row
+// mirror for the two pairs and the halves of each row.  Four swaps, four additions; two and
+// two; three; then three additions of mirrored operands: 18 operations per group for both
+// values, where the reduce-scatter within rows below takes 25.  (The swaps are inline asm
+// because this compiler's builtins return the first result for both outputs.  A swap needs
+// two wait states after the operation that wrote its operands, which the compiler does not
+// count into inline asm: the s_nop.)
+struct GroupSums {
+  float c, d01, d23;   // the pending measurement, the pairs (0, 1) and (2, 3)
+};
+__device__ __forceinline__ float swap32_sum(float x, float y) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+  return x + y;
+}
+__device__ __forceinline__ float swap16_sum(float x, float y) {
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+  return x + y;
+}
+__device__ __forceinline__ int group_sums_index(int lane) { return ((lane >> 4) & 1) | ((lane >> 3) & 1) << 1; }
+// the values a, b of measurement u (known at compile time), in order
+__device__ __forceinline__ void group_sums_push(GroupSums& s, float a, float b, int u) {
+  const float c = swap32_sum(a, b);
+  if ((u & 1) == 0)
+    s.c = c;
+  else if (u == 1)
+    s.d01 = swap16_sum(s.c, c);
+  else
+    s.d23 = swap16_sum(s.c, c);
+}
+// hi8: the lane's bit 3
+__device__ __forceinline__ float group_sums_total(const GroupSums& s, bool hi8) {
+  const float kept = hi8 ? s.d23 : s.d01, sent = hi8 ? s.d01 : s.d23;
+  float e = kept + dpp_f32<0x140>(sent);   // row_mirror: the lane with the other bit 3
+  e += dpp_f32<0xB1>(e);                   // quad_perm xor 1
+  e += dpp_f32<0x4E>(e);                   // quad_perm xor 2
+  e += dpp_f32<0x141>(e);                  // row_half_mirror: the other quad
+  return e;
 }
 
 // Lane exchanges across rows without per-use index arithmetic: ds_swizzle in

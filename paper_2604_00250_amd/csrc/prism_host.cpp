@@ -89,6 +89,8 @@ struct prism_problem {
   GroupDev* d_groups = nullptr;
   ItemDev* d_items = nullptr;
   TileDev* d_tiles = nullptr;
+  int32_t* d_perm = nullptr;
+  RunDev* d_runs = nullptr;
   float* d_bval = nullptr;
   float* d_bvec = nullptr;
   int32_t* d_coords = nullptr;
@@ -134,6 +136,8 @@ struct prism_problem {
   ~prism_problem() {
     free_plan();
     (void)hipFree(d_groups);
+    (void)hipFree(d_perm);
+    (void)hipFree(d_runs);
     (void)hipFree(d_bval);
     (void)hipFree(d_bvec);
     (void)hipFree(d_coords);
@@ -152,6 +156,41 @@ struct prism_problem {
 namespace {
 
 int n_bias_of(int bias) { return bias == PRISM_BIAS_POLY2 ? 10 : bias == PRISM_BIAS_TRILINEAR8 ? 512 : 0; }
+
+// The order in which the fused pass takes an acquisition's measurements: for each
+// b-value as many whole groups of four as it has (b = 0 first, then by b; within one in
+// the caller's order), then the measurements left over, in the caller's order, padded with
+// the last one to a whole group.  Measurements of one b-value share the balls' terms
+// whatever the order in which the scanner took them.
+struct AcqOrder {
+  int32_t perm_off, run_off, n_runs, n_ug;
+};
+AcqOrder order_acquisition(const float* b, int N, std::vector<int32_t>& perm, std::vector<RunDev>& runs) {
+  AcqOrder o{(int32_t)perm.size(), (int32_t)runs.size(), 0, 0};
+  std::vector<int32_t> by(N);
+  for (int n = 0; n < N; ++n) by[n] = n;
+  std::stable_sort(by.begin(), by.end(), [&](int i, int j) { return b[i] < b[j]; });
+  std::vector<char> left(N, 1);
+  for (int i = 0; i < N;) {
+    int j = i;
+    while (j < N && b[by[j]] == b[by[i]]) ++j;
+    const int groups = (j - i) / 4;
+    if (groups > 0) {
+      runs.push_back(RunDev{o.n_ug, o.n_ug + groups, b[by[i]] == 0.0f ? 1 : 0});
+      for (int k = i; k < i + 4 * groups; ++k) {
+        perm.push_back(by[k]);
+        left[by[k]] = 0;
+      }
+      o.n_ug += groups;
+      ++o.n_runs;
+    }
+    i = j;
+  }
+  for (int n = 0; n < N; ++n)
+    if (left[n]) perm.push_back(n);
+  while (perm.size() % 4) perm.push_back(perm.back());
+  return o;
+}
 
 // Measurement split of one item: with n_split = 0 the item's size picks it
 // (few voxels -> more waves share each voxel row, each over a part of N).
@@ -599,6 +638,10 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
       bvec.push_back(gz);
     }
   }
+  std::vector<int32_t> perm;
+  std::vector<RunDev> runs;
+  std::vector<AcqOrder> orders;
+  for (int a = 0; a < n_acq; ++a) orders.push_back(order_acquisition(bval.data() + acq_off[a], acqs[a].n_meas, perm, runs));
   prism_problem* h = new (std::nothrow) prism_problem();
   if (!h) return fail(PRISM_E_ALLOC, "host allocation failed");
   (void)hipGetDevice(&h->device);
@@ -677,8 +720,10 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
       }
     }
     g.acq_off = acq_off[d.acq];
-    g.nb0 = 0;
-    while (g.nb0 < g.N && bval[(size_t)g.acq_off + g.nb0] == 0.0f) ++g.nb0;
+    g.perm_off = orders[d.acq].perm_off;
+    g.run_off = orders[d.acq].run_off;
+    g.n_runs = orders[d.acq].n_runs;
+    g.n_ug = orders[d.acq].n_ug;
     g.rec_stride = kRecHead + 2 * g.N;
     g.invM = V > 0 ? 1.0f / (float)V : 0.0f;
     {
@@ -777,6 +822,8 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
   h->launch.concurrent = 1;
   hipError_t e = upload(&h->d_bval, bval);
   if (e == hipSuccess) e = upload(&h->d_bvec, bvec);
+  if (e == hipSuccess) e = upload(&h->d_perm, perm);
+  if (e == hipSuccess) e = upload(&h->d_runs, runs);
   if (e == hipSuccess) e = upload(&h->d_coords, coords);
   if (e == hipSuccess) e = upload(&h->d_nbr, nbr);
   if (e == hipSuccess) e = upload(&h->d_ninv, ninv);
@@ -912,6 +959,8 @@ static PassArgs pass_args(const prism_problem* h, const float* y, const float* t
   a.items = h->d_items;
   a.bval = h->d_bval;
   a.bvec = h->d_bvec;
+  a.perm = h->d_perm;
+  a.runs = h->d_runs;
   a.coords = h->d_coords;
   a.nbr = h->d_nbr;
   a.ninv = h->d_ninv;

@@ -50,7 +50,9 @@ struct GroupDev {
   float bsc[3], boff[3]; // quadratic bias coordinates xi_a = i_a bsc[a] + boff[a] in [-1, 1]
                          // (2/(n_a - 1) and -1; both 0 when n_a = 1)
   int32_t acq_off;    // offset of the group's measurements in the acquisition arrays
-  int32_t nb0;        // measurements with b = 0 at the start of the acquisition
+  int32_t perm_off;   // offset of the acquisition's order in PassArgs.perm (a multiple of 4)
+  int32_t run_off, n_runs;  // its runs in PassArgs.runs
+  int32_t n_ug;       // groups of four measurements in the runs
   int32_t rec_stride; // float64 fields per record
   int32_t item_begin, item_count;
   float invM;         // 1/|M| (0 when the group is empty)
@@ -63,6 +65,14 @@ struct GroupDev {
   float inv_s0o;      // 1 / s0_orphan
   float sc_orph_s0;   // lam_orphan / |M| / s0_orphan
   float tri_sc[3];    // 7 / (n_a - 1): trilinear control-grid coordinate per voxel step (0 if n_a = 1)
+};
+
+constexpr int padded4(int n) { return (n + 3) & ~3; }   // positions of N measurements in whole groups
+
+// groups of four measurements [g0, g1) of one b-value in an acquisition's order
+struct RunDev {
+  int32_t g0, g1;
+  int32_t b0;         // 1: at b = 0
 };
 
 struct ItemDev {
@@ -104,6 +114,9 @@ struct PassArgs {
   const ItemDev* items;
   const float* bval;
   const float* bvec;
+  const int32_t* perm;     // per acquisition the measurement at each position, padded to whole
+                           // groups of four with its last one
+  const RunDev* runs;
   const int32_t* coords;   // packed i | j << 10 | k << 20
   const int32_t* nbr;
   const float* ninv;       // 1/|N(x)| per voxel

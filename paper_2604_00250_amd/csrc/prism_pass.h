@@ -5,6 +5,7 @@
 // variant (prism_persistent.hip).
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "prism_common.h"
 
@@ -22,7 +23,7 @@ namespace prism {
 #ifndef PRISM_FOUR_WAVES
 #define PRISM_FOUR_WAVES 1
 #endif
-// measurements per tile of the per-measurement sums (one per lane of a row of 16)
+// measurements whose loss terms are summed in float32
 constexpr int kTile = 16;
 // depth of the y prefetch ring (measurements ahead); kTile is a multiple of it
 constexpr int kPf = PRISM_PREFETCH;
@@ -61,21 +62,23 @@ constexpr int sched_span(int K, int MODE, bool LD, int VL) {
 // (the fourth component of a and of c is not read with fixed diffusivities: the
 // three read share one LDS load)
 // ---------------------------------------------------------------------------
-inline __device__ void stage_acquisition(const PassArgs& A, const GroupDev& g, float4* acq) {
+// ordered: in the order of measurement_loop, else as the caller gave them
+inline __device__ void stage_acquisition(const PassArgs& A, const GroupDev& g, float4* acq, bool ordered) {
   const float* cal = A.th_cal + g.cal_off;
   const float* alpha = cal + g.n_bias;
   const float* beta = alpha + g.N;
   const float dpar = g.learn_d ? 1.0f : A.model.d_par;     // d_par > 0 (checked at create)
   const float dperp = g.learn_d ? 1.0f : A.model.d_perp;
-  for (int n = threadIdx.x; n < g.N; n += blockDim.x) {
+  for (int p = threadIdx.x; p < g.N; p += blockDim.x) {
+    const int n = ordered ? A.perm[g.perm_off + p] : p;
     const float b = A.bval[g.acq_off + n];
     const float* gv = A.bvec + 3 * (int64_t)(g.acq_off + n);
     const float kpar = -b * dpar * kLog2e, kperp = -b * dperp * kLog2e;
     const float s = g.learn_d ? 1.0f : sqrtf(-kpar);
-    acq[3 * n + 0] = make_float4(s * gv[0], s * gv[1], s * gv[2], kpar);
-    acq[3 * n + 1] = make_float4(kperp, expf(-b * A.model.d_csf), expf(-b * A.model.d_gm),
+    acq[3 * p + 0] = make_float4(s * gv[0], s * gv[1], s * gv[2], kpar);
+    acq[3 * p + 1] = make_float4(kperp, expf(-b * A.model.d_csf), expf(-b * A.model.d_gm),
                                  expf(-b * A.model.d_res));
-    acq[3 * n + 2] = make_float4(expf(alpha[n]), beta[n], g.learn_d ? -2.0f * b : dperp / dpar - 1.0f, 0.0f);
+    acq[3 * p + 2] = make_float4(expf(alpha[n]), beta[n], g.learn_d ? -2.0f * b : dperp / dpar - 1.0f, 0.0f);
   }
 }
 
@@ -309,19 +312,34 @@ __device__ __forceinline__ void pair_b0(float Fsum, float& dS0, float yv, float 
   dS0 = fmaf(seed, c.x, dS0);
 }
 
-template <int K, int MODE, bool LD>
-__device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float yv, float valid,
+// What a run of measurements of one b-value shares per voxel: the balls' signal (Eq. 4)
+// and, with learned diffusivities, the exponents' factors; dS sums the seeds of the run,
+// multiplied by the balls' attenuations once at its end.
+struct RunVox {
+  float iso, dS;
+  float kp, kq, kd;
+};
+
+// UNI: the measurement belongs to the run of `run` (b is not read then: the balls, the
+// exponents' constants and -2b, in mb2, come from the run).
+template <int K, int MODE, bool LD, bool UNI>
+__device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, RunVox& run, float mb2, float yv, float valid,
                                      const float4 a, const float4 b, const float4 c, float inv_s2,
                                      const float4* bes, float& t_loss, float& t_sig, float& sq, float& seed) {
   using AC = Acc<K, LD>;
   // fixed D: (gx, gy, gz) = s g and cc = s cos (see stage_acquisition)
   const float gx = a.x, gy = a.y, gz = a.z;
-  const float kp = LD ? a.w * x.dpar : 0.0f;    // learned D: log2 e1 = kp cos^2
-  const float kq = LD ? b.x * x.dperp : b.x;    // log2 e12 = kq + kd cc^2
-  const float kd = LD ? kp - kq : c.z;
-  float S = x.Fi[0] * b.y;
-  S = fmaf(x.Fi[1], b.z, S);
-  S = fmaf(x.Fi[2], b.w, S);
+  const float kp = !LD ? 0.0f : UNI ? run.kp : a.w * x.dpar;              // learned D: log2 e1 = kp cos^2
+  const float kq = UNI ? run.kq : LD ? b.x * x.dperp : b.x;               // log2 e12 = kq + kd cc^2
+  const float kd = UNI ? run.kd : LD ? kp - kq : c.z;
+  float S;
+  if (UNI) {
+    S = run.iso;
+  } else {
+    S = x.Fi[0] * b.y;
+    S = fmaf(x.Fi[1], b.z, S);
+    S = fmaf(x.Fi[2], b.w, S);
+  }
   float cc[K], e1[K], e12[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -338,14 +356,19 @@ __device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float
   const float dS = seed * c.x;
   // the factor of the direction adjoint shared by the fibres: dS (-2b) (learned D),
   // dS (fixed D: -2 ln2 is in a1, a2 and the scale s in cc and the staged vector)
-  const float dSz = LD ? dS * c.z : dS;
+  const float cz = UNI ? mb2 : c.z;
+  const float dSz = LD ? dS * cz : dS;
   // from three fibres on, fold dSz into the two per-voxel factors once per pair
   // (two products) rather than into each fibre's cosine (one product per fibre)
   constexpr bool kFold = K >= 3;
   const float a1z = kFold ? x.a1 * dSz : x.a1, a2z = kFold ? x.a2 * dSz : x.a2;
-  acc.r[0] = fmaf(dS, b.y, acc.r[0]);
-  acc.r[1] = fmaf(dS, b.z, acc.r[1]);
-  acc.r[2] = fmaf(dS, b.w, acc.r[2]);
+  if (UNI) {
+    run.dS += dS;
+  } else {
+    acc.r[0] = fmaf(dS, b.y, acc.r[0]);
+    acc.r[1] = fmaf(dS, b.z, acc.r[1]);
+    acc.r[2] = fmaf(dS, b.w, acc.r[2]);
+  }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     acc.r[AC::kE1 + k] = fmaf(dS, e1[k], acc.r[AC::kE1 + k]);
@@ -359,7 +382,7 @@ __device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float
     acc.r[AC::kGd + 3 * k + 2] = fmaf(dc, gz, acc.r[AC::kGd + 3 * k + 2]);
     if (LD) {
       // dE/dDpar = -b cos^2 E, dE/dDperp = -b sin^2 (1-fin) e12, with -b = (-2b)/2
-      const float mb = 0.5f * c.z;
+      const float mb = 0.5f * cz;
       const float c2 = cc[k] * cc[k];
       const float FE = fmaf(x.Fa[k], e1[k], x.Fb[k] * e12[k]);
       acc.r[AC::kDpar] = fmaf(dS * FE, mb * c2, acc.r[AC::kDpar]);
@@ -368,181 +391,197 @@ __device__ __forceinline__ void pair(const Vox<K, LD>& x, Acc<K, LD>& acc, float
   }
 }
 
-static_assert(kPf == 4, "the per-measurement sums take four measurements at a time");
+static_assert(kPf == 4, "the measurements come in groups of four");
 
-// Measurements [nb, ne) for the VL voxels of this lane, in tiles of kTile.
-// The per-measurement sums over the wave's 64 x VL voxels (the beta_n adjoint,
-// and the alpha_n adjoint divided by exp(alpha_n), which multiplies the tile's
-// totals) are reduced over each row of 16 lanes as the measurements arrive
-// (RowScatter, four at a time); after the tile lane l holds its row's sum for
-// measurement n0 + row_scatter_index(l), and two lane exchanges (xor 16,
-// xor 32) add the four rows.  Invalid lanes (beyond the item) carry valid = 0,
-// which removes them from every sum.  FULL: every lane's voxels are in the
-// item (the validity factors are 1 and drop out at compile time).
+// The groups of four measurements [ga, gb) of the acquisition's order (see order_acquisition
+// in prism_host.cpp: position p of the staged table is measurement perm[p]; the first n_ug
+// groups are whole groups of one b-value each, in runs, b = 0 first; the rest mix b-values
+// and the last may be partial) for the VL voxels of this lane.  A group of a run saves the
+// balls' terms (5 of 58 counted operations at K = 3), one at b = 0 everything but the data
+// term; each kind of group has a straight-line loop of its own.  The loop is bound by VALU
+// issue: brain volume, K = 3, N = 288, one iteration 494 -> 464 us with the runs and the
+// sums below (the sums alone: no change there, slabs of it at K = 2, N = 96, 224 -> 220 us).
+// The per-measurement sums over the wave's 64 x VL voxels (the beta_n adjoint, and
+// the alpha_n adjoint divided by exp(alpha_n)) are reduced as the measurements arrive
+// (GroupSums) and added to wacc [2][4 groups] by position.  Invalid lanes (beyond the item) carry valid = 0, which removes them from
+// every sum.  FULL: every lane's voxels are in the item (the validity factors are 1 and drop
+// out at compile time).
 template <int K, int MODE, bool LD, int VL, bool FULL>
-__device__ __forceinline__ void measurement_loop(const Vox<K, LD> (&x)[VL], Acc<K, LD> (&acc)[VL],
-                                                 const float* yg, int64_t V, const int (&vox)[VL],
-                                                 const float (&valid)[VL],
-                                                 const float4* __restrict__ acq,
-                                                 const float4* __restrict__ bes, int nb, int ne, int nb0, int N, float inv_s2, int lane,
-                                                 float* wacc, double& dloss, double& dsig) {
+__device__ __forceinline__ void measurement_loop(const PassArgs& A, const GroupDev& g, const Vox<K, LD> (&x)[VL],
+                                                 Acc<K, LD> (&acc)[VL], const int (&vox)[VL],
+                                                 const float (&valid)[VL], const float4* __restrict__ acq,
+                                                 const float4* __restrict__ bes, int ga, int gb, float inv_s2,
+                                                 int lane, float* wacc, double& dloss, double& dsig) {
+  if (ga >= gb) return;
+  const int64_t V = g.V;
+  const int N = g.N;
+  const float* yg = A.y + g.y_off;
+  const int32_t* perm = A.perm + g.perm_off;
   uint32_t voff[VL];  // byte offsets of the lane's voxels in a row of y
 #pragma unroll
   for (int j = 0; j < VL; ++j) voff[j] = (uint32_t)vox[j] * 4u;
   const uint32_t rowb = (uint32_t)V * 4u;  // bytes in a row of y (V <= 1023^3)
-  // y prefetch ring kPf measurements deep (slot u holds measurement nb + u mod kPf)
+  // y prefetch ring one group deep (slot u: the group's u-th measurement)
   float yr[kPf][VL];
+  {
+    const int4 r = uniform_int4(perm, ga);
+    const int rows[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
-  for (int u = 0; u < kPf; ++u)
+    for (int u = 0; u < kPf; ++u)
 #pragma unroll
-    for (int j = 0; j < VL; ++j) yr[u][j] = load_row_f32(yg + (int64_t)min(nb + u, ne - 1) * V, rowb, voff[j]);
-  const RowScatterMasks sm = row_scatter_masks(lane);
-  const int bank = (lane >> 2) & 3;   // the group of four measurements this lane's row sums keep
-  RowScatter sa, sb;                  // the alpha and beta sums of the tile
+      for (int j = 0; j < VL; ++j) yr[u][j] = load_row_f32(yg + (int64_t)rows[u] * V, rowb, voff[j]);
+  }
+  const bool hi8 = (lane & 8) != 0;
+  // where lane l adds its sum of a group (GroupSums): the eight lanes with the same sum
+  // all do, since a branch here would let the compiler move the group's adjoint behind it
+  // (with everything that it needs kept in registers until then)
+  float* const mine = wacc + (lane >> 5) * padded4(N) + group_sums_index(lane);
+  GroupSums gs;
   float lacc, sacc;
-  int n0 = nb;
-  // one measurement, u = n - n0 mod 4: the ring slot u is refilled (measurement
-  // n + kPf) only after its value has been consumed, so the load can target the
-  // slot's register directly and the wait for it lands kPf measurements later
-  auto body = [&](int t, int u, float (&slot)[VL]) {
-    const int n = n0 + t;
-    const float4 a = acq[3 * n + 0];
-    const float4 b = acq[3 * n + 1];
-    const float4 c = acq[3 * n + 2];
-    float pa = 0.0f, pb = 0.0f;
-#pragma unroll
-    for (int j = 0; j < VL; ++j) {
-      float tl, ts, sq, sd;
-      pair<K, MODE, LD>(x[j], acc[j], slot[j], FULL ? 1.0f : valid[j], a, b, c, inv_s2, bes, tl, ts, sq, sd);
-      lacc += tl;
-      if (MODE == kNLL) sacc += ts;
-      pa = j == 0 ? sq : pa + sq;
-      pb = j == 0 ? sd : pb + sd;
-    }
-    // refill from the measurement's row (a uniform base) at the lane's voxel
-    const float* row = yg + (int64_t)min(n + kPf, ne - 1) * V;  // clamped: in bounds
+  RunVox run[VL];
+  float mb2 = 0.0f;
+  int4 next;   // rows of y of the next group
+  // refill slot u from the next group's row (a uniform base), only after its value has been
+  // consumed, so the load can target the slot's register directly and the wait for it lands
+  // a group later
+  auto refill = [&](int u, float (&slot)[VL]) {
+    const float* row = yg + (int64_t)(u == 0 ? next.x : u == 1 ? next.y : u == 2 ? next.z : next.w) * V;
 #pragma unroll
     for (int j = 0; j < VL; ++j) slot[j] = load_row_f32(row, rowb, voff[j]);
-    row_scatter_push(sa, pa, u, sm);
-    row_scatter_push(sb, pb, u, sm);
   };
-  // a measurement past the end of the range: zeros complete the group
-  auto body_none = [&](int u) {
-    row_scatter_push(sa, 0.0f, u, sm);
-    row_scatter_push(sb, 0.0f, u, sm);
+  auto sums = [&](int u, const float (&sq)[VL], const float (&sd)[VL]) {
+    float pa = sq[0], pb = sd[0];
+#pragma unroll
+    for (int j = 1; j < VL; ++j) {
+      pa += sq[j];
+      pb += sd[j];
+    }
+    group_sums_push(gs, pa, pb, u);
   };
-  auto group_end = [&](int t0) {
-    const bool here = bank == (t0 >> 2);
-    row_scatter_group(sa, here);
-    row_scatter_group(sb, here);
-  };
-  auto tile_begin = [&]() {
-    lacc = 0.0f;
-    sacc = 0.0f;
-    sa.acc = 0.0f;
-    sb.acc = 0.0f;
-  };
-  // the same at b = 0 (see pair_b0)
-  float Fsum[VL], dS0[VL];
-  auto body_b0 = [&](int t, int u, float (&slot)[VL]) {
-    const int n = n0 + t;
-    const float4 c = acq[3 * n + 2];
-    float pa = 0.0f, pb = 0.0f;
+  // the measurement at position p, the u-th of its group
+  auto body = [&](auto uni, int p, int u, float (&slot)[VL]) {
+    constexpr bool UNI = decltype(uni)::value;
+    const float4 a = acq[3 * p + 0], c = acq[3 * p + 2];
+    const float4 b = UNI ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : acq[3 * p + 1];
+    float sq[VL], sd[VL];
 #pragma unroll
     for (int j = 0; j < VL; ++j) {
-      float tl, ts, sq, sd;
-      pair_b0<MODE>(Fsum[j], dS0[j], slot[j], FULL ? 1.0f : valid[j], c, inv_s2, bes, tl, ts, sq, sd);
+      float tl, ts;
+      pair<K, MODE, LD, UNI>(x[j], acc[j], run[j], mb2, slot[j], FULL ? 1.0f : valid[j], a, b, c, inv_s2, bes, tl, ts,
+                             sq[j], sd[j]);
       lacc += tl;
       if (MODE == kNLL) sacc += ts;
-      pa = j == 0 ? sq : pa + sq;
-      pb = j == 0 ? sd : pb + sd;
     }
-    const float* row = yg + (int64_t)min(n + kPf, ne - 1) * V;  // clamped: in bounds
-#pragma unroll
-    for (int j = 0; j < VL; ++j) slot[j] = load_row_f32(row, rowb, voff[j]);
-    row_scatter_push(sa, pa, u, sm);
-    row_scatter_push(sb, pb, u, sm);
+    refill(u, slot);
+    sums(u, sq, sd);
   };
-  // four straight-line measurements from t0 (a multiple of kPf)
-  auto group = [&](int t0) {
-#pragma unroll
-    for (int u = 0; u < kPf; ++u) {
-      body(t0 + u, u, yr[u]);
-      if ((u + 1) % sched_span(K, MODE, LD, VL) == 0) __builtin_amdgcn_sched_barrier(0);
-    }
-    group_end(t0);
-  };
-  // wave totals of the tile's per-measurement sums (cnt measurements)
-  auto tile_end = [&](int cnt) {
-    float ra = sa.acc, rb = sb.acc;
-    ra += xor16_f32(ra);
-    rb += xor16_f32(rb);
-    ra += xor32_f32(ra);
-    rb += xor32_f32(rb);
-    const int tn = row_scatter_index(lane);
-    if (lane < kTile && tn < cnt) {
-      const int n = n0 + tn;
-      wacc[n] = fmaf(ra, acq[3 * n + 2].x, wacc[n]);  // times exp(alpha_n)
-      wacc[N + n] += rb;
-    }
-    dloss += (double)lacc;
-    if (MODE == kNLL) dsig += (double)sacc;  // 0 for MSE
-  };
-  // whole tiles of the acquisition's leading b = 0 measurements first
-  const int b0end = min(nb0, ne);
-  if (n0 + kTile <= b0end) {
+  // the same at b = 0 (see pair_b0; run.iso: sum_c F_c)
+  auto body_b0 = [&](int p, int u, float (&slot)[VL]) {
+    const float4 c = acq[3 * p + 2];
+    float sq[VL], sd[VL];
 #pragma unroll
     for (int j = 0; j < VL; ++j) {
-      float sF = 0.0f;
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) sF += x[j].Fi[cc];
-#pragma unroll
-      for (int k = 0; k < K; ++k) sF += x[j].Fa[k] + x[j].Fb[k];
-      Fsum[j] = sF;
-      dS0[j] = 0.0f;
+      float tl, ts;
+      pair_b0<MODE>(run[j].iso, run[j].dS, slot[j], FULL ? 1.0f : valid[j], c, inv_s2, bes, tl, ts, sq[j], sd[j]);
+      lacc += tl;
+      if (MODE == kNLL) sacc += ts;
     }
-    for (; n0 + kTile <= b0end; n0 += kTile) {
-      tile_begin();
+    refill(u, slot);
+    sums(u, sq, sd);
+  };
+  auto keep = [&](int gi) { mine[4 * gi] += group_sums_total(gs, hi8); };
+  // groups [lo, hi) by f, the loss in float32 over four groups and in float64 above that
+  auto groups = [&](int lo, int hi, auto&& f) {
+    for (int gi = lo; gi < hi;) {
+      const int e = min(gi + kTile / kPf, hi);
+      lacc = 0.0f;
+      sacc = 0.0f;
 #pragma unroll 1
-      for (int t0 = 0; t0 < kTile; t0 += kPf) {
-#pragma unroll
-        for (int u = 0; u < kPf; ++u) body_b0(t0 + u, u, yr[u]);
-        group_end(t0);
-        __builtin_amdgcn_sched_barrier(0);
+      for (; gi < e; ++gi) {
+        next = uniform_int4(perm, min(gi + 1, gb - 1));  // in range, like every padded position
+        f(gi);
       }
-      tile_end(kTile);
+      dloss += (double)lacc;
+      if (MODE == kNLL) dsig += (double)sacc;  // 0 for MSE
     }
+  };
+  for (int r = 0; r < g.n_runs; ++r) {
+    const RunDev& rd = reread(A.runs + g.run_off + r);
+    const int lo = max(rd.g0, ga), hi = min(rd.g1, gb);
+    if (lo >= hi) continue;
+    if (rd.b0) {
 #pragma unroll
-    for (int j = 0; j < VL; ++j)
+      for (int j = 0; j < VL; ++j) {
+        float sF = 0.0f;
 #pragma unroll
-      for (int cc = 0; cc < 3 + 2 * K; ++cc) acc[j].r[cc] += dS0[j];  // e1 = e12 = 1
-  }
-  // whole tiles: every path into the loop has the ring's loads in flight in slot
-  // order, so each wait is for exactly one slot
-  for (; n0 + kTile <= ne; n0 += kTile) {
-    tile_begin();
-#pragma unroll 1
-    for (int t0 = 0; t0 < kTile; t0 += kPf) group(t0);
-    tile_end(kTile);
-  }
-  if (n0 < ne) {  // the range's last, partial tile
-    const int cnt = ne - n0;
-    const int full = cnt & ~(kPf - 1);  // cnt > 0
-    tile_begin();
-#pragma unroll 1
-    for (int t0 = 0; t0 < full; t0 += kPf) group(t0);
-    if (full < cnt) {
+        for (int c = 0; c < 3; ++c) sF += x[j].Fi[c];
+#pragma unroll
+        for (int k = 0; k < K; ++k) sF += x[j].Fa[k] + x[j].Fb[k];
+        run[j].iso = sF;
+        run[j].dS = 0.0f;
+      }
+      groups(lo, hi, [&](int gi) {
+#pragma unroll
+        for (int u = 0; u < kPf; ++u) body_b0(4 * gi + u, u, yr[u]);
+        keep(gi);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int j = 0; j < VL; ++j)
+#pragma unroll
+        for (int c = 0; c < 3 + 2 * K; ++c) acc[j].r[c] += run[j].dS;  // e1 = e12 = 1
+      continue;
+    }
+    {
+      const float4 a = acq[12 * lo], b = acq[12 * lo + 1], c = acq[12 * lo + 2];
+      mb2 = c.z;
+#pragma unroll
+      for (int j = 0; j < VL; ++j) {
+        run[j].iso = fmaf(x[j].Fi[2], b.w, fmaf(x[j].Fi[1], b.z, x[j].Fi[0] * b.y));
+        run[j].dS = 0.0f;
+        run[j].kp = LD ? a.w * x[j].dpar : 0.0f;
+        run[j].kq = LD ? b.x * x[j].dperp : b.x;
+        run[j].kd = LD ? run[j].kp - run[j].kq : c.z;
+      }
+    }
+    groups(lo, hi, [&](int gi) {
 #pragma unroll
       for (int u = 0; u < kPf; ++u) {
-        if (full + u < cnt)
-          body(full + u, u, yr[u]);
-        else
-          body_none(u);
+        body(std::true_type{}, 4 * gi + u, u, yr[u]);
+        if ((u + 1) % sched_span(K, MODE, LD, VL) == 0) __builtin_amdgcn_sched_barrier(0);
       }
-      group_end(full);
+      keep(gi);
+    });
+    const float4 b = acq[12 * lo + 1];
+#pragma unroll
+    for (int j = 0; j < VL; ++j) {
+      acc[j].r[0] = fmaf(run[j].dS, b.y, acc[j].r[0]);
+      acc[j].r[1] = fmaf(run[j].dS, b.z, acc[j].r[1]);
+      acc[j].r[2] = fmaf(run[j].dS, b.w, acc[j].r[2]);
     }
-    tile_end(cnt);
   }
+  // the groups of mixed b-values: whole ones, then the partial last one
+  const int lo = max(g.n_ug, ga), whole = min(N / kPf, gb);
+  groups(lo, whole, [&](int gi) {
+#pragma unroll
+    for (int u = 0; u < kPf; ++u) {
+      body(std::false_type{}, 4 * gi + u, u, yr[u]);
+      if ((u + 1) % sched_span(K, MODE, LD, VL) == 0) __builtin_amdgcn_sched_barrier(0);
+    }
+    keep(gi);
+  });
+  groups(max(whole, lo), gb, [&](int gi) {
+    const float zero[VL] = {};
+#pragma unroll
+    for (int u = 0; u < kPf; ++u) {
+      if (4 * gi + u < N)
+        body(std::false_type{}, 4 * gi + u, u, yr[u]);
+      else
+        sums(u, zero, zero);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    keep(gi);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -825,16 +864,17 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
   const int row = wave / WN, split = wave - row * WN;
   const int N = g.N;
   float4* acq = smem4;                                       // [3N] unless read from SMEM
-  float* accab = reinterpret_cast<float*>(smem4 + (PRISM_ACQ_SMEM ? 0 : 3 * N));  // [4][2][N]
-  float* xbuf = accab + 8 * N;                               // [rows][WN-1][NACC][64*VL]
+  const int Np = padded4(N);
+  float* accab = reinterpret_cast<float*>(smem4 + (PRISM_ACQ_SMEM ? 0 : 3 * N));  // [4][2][Np]
+  float* xbuf = accab + 8 * Np;                              // [rows][WN-1][NACC][64*VL]
 
 #if PRISM_ACQ_SMEM
   const float4* __restrict__ acq_tab = acq_global + g.acqtab_off / 4;
 #else
-  stage_acquisition(A, g, acq);
+  stage_acquisition(A, g, acq, true);
   const float4* acq_tab = acq;
 #endif
-  for (int i = tid; i < 8 * N; i += kBlock) accab[i] = 0.0f;
+  for (int i = tid; i < 8 * Np; i += kBlock) accab[i] = 0.0f;
   if (lane < kRecVals) wrec[wave][lane] = 0.0;
   if (A.adam && tid == 0) {
     adam_factors(A.step, A.lr, A.b1, A.b2, sh.adam_sc[0], sh.adam_sc[1]);
@@ -843,12 +883,11 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
   if (it.rec == 0 && wave == 3) calibration_squares(A, g, it.group, lane);
   __syncthreads();
 
-  const int nb = (N * split) / WN, ne = (N * (split + 1)) / WN;
-  const int64_t V = g.V;
-  const float* yg = A.y + g.y_off;
+  const int n_groups = (N + kPf - 1) / kPf;
+  const int ga = n_groups * split / WN, gb = n_groups * (split + 1) / WN;
   const float* cal = A.th_cal + g.cal_off;
   const float inv_s2 = MODE == kNLL ? expf(-2.0f * cal[g.n_bias + 2 * N]) : 0.0f;
-  float* wacc = accab + wave * 2 * N;
+  float* wacc = accab + wave * 2 * Np;
 
   double dloss = 0.0, dsig = 0.0;
   bool bad_grad = false, zero_dir = false;
@@ -876,11 +915,11 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
 
     // a chunk that lies wholly inside the item runs the loop without validity factors
     if (cb + chunk <= it.nv)
-      measurement_loop<K, MODE, LD, VL, true>(x, acc, yg, V, vox, valid, acq_tab, bes, nb, ne, g.nb0, N, inv_s2, lane,
-                                              wacc, dloss, dsig);
+      measurement_loop<K, MODE, LD, VL, true>(A, g, x, acc, vox, valid, acq_tab, bes, ga, gb, inv_s2, lane, wacc, dloss,
+                                              dsig);
     else
-      measurement_loop<K, MODE, LD, VL, false>(x, acc, yg, V, vox, valid, acq_tab, bes, nb, ne, g.nb0, N, inv_s2, lane,
-                                               wacc, dloss, dsig);
+      measurement_loop<K, MODE, LD, VL, false>(A, g, x, acc, vox, valid, acq_tab, bes, ga, gb, inv_s2, lane, wacc, dloss,
+                                               dsig);
 
     // combine the per-voxel accumulators of the waves that split this row over n
     if (WN > 1) {
@@ -1039,11 +1078,13 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
     rec[field] = s;
   }
   if (tid == kBlock - 1 && !((gr.priors & kPriorSpatial) && gr.nbh > 0)) rec[kRecSpatial] = 0.0;
-  for (int n = tid; n < N; n += kBlock) {
-    rec[kRecAlpha + n] = (double)accab[n] + (double)accab[2 * N + n] + (double)accab[4 * N + n] +
-                         (double)accab[6 * N + n];
-    rec[kRecAlpha + N + n] = (double)accab[N + n] + (double)accab[3 * N + n] +
-                             (double)accab[5 * N + n] + (double)accab[7 * N + n];
+  for (int p = tid; p < N; p += kBlock) {
+    const int n = Ar.perm[gr.perm_off + p];
+    auto waves = [&](const float* s) {
+      return (double)s[0] + (double)s[2 * Np] + (double)s[4 * Np] + (double)s[6 * Np];
+    };
+    rec[kRecAlpha + n] = waves(accab + p) * (double)acq_tab[3 * p + 2].x;  // times exp(alpha_n)
+    rec[kRecAlpha + N + n] = waves(accab + Np + p);
   }
 }
 
@@ -1138,7 +1179,7 @@ __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
   const ItemDev it = A.items[A.item_base + xcd_item(blockIdx.x, gridDim.x)];
   const GroupDev g = A.groups[it.group];
   float4* acq = smem4;
-  stage_acquisition(A, g, acq);
+  stage_acquisition(A, g, acq, false);
   __syncthreads();
   bool zero_dir = false;
   // items of up to two rows (the cut of small and middling problems): one voxel per lane
@@ -1157,7 +1198,7 @@ __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
 // per-wave measurement sums and the cross-wave buffer of the worst measurement split
 // in the launch (xsplit = max rows*(WN-1): 0, 2 or 3)
 inline size_t pass_lds_bytes(int maxN, int xsplit, int nacc_, int vpl, bool nll) {
-  size_t b = (PRISM_ACQ_SMEM ? 0 : (size_t)maxN * 3 * sizeof(float4)) + (size_t)8 * maxN * sizeof(float);
+  size_t b = (PRISM_ACQ_SMEM ? 0 : (size_t)maxN * 3 * sizeof(float4)) + (size_t)8 * padded4(maxN) * sizeof(float);
   if (nll) b += (size_t)kBesselRows * sizeof(float4);
   b += (size_t)xsplit * nacc_ * 64 * vpl * sizeof(float);
   return b;

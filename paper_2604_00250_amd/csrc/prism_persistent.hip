@@ -8,7 +8,7 @@ namespace prism {
 // pass through the scalar cache (uniform loads into SGPRs).
 __global__ __launch_bounds__(256) void k_stage(PassArgs A) {
   const GroupDev g = A.groups[blockIdx.x];
-  stage_acquisition(A, g, reinterpret_cast<float4*>(A.wsp + g.acqtab_off));
+  stage_acquisition(A, g, reinterpret_cast<float4*>(A.wsp + g.acqtab_off), true);
 }
 
 // Persistent launch over items of every variant: each block pops the next item

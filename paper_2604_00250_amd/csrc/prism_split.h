@@ -39,6 +39,7 @@ __device__ __forceinline__ void slot_loop(const Vox<K, LD>& x, Acc<K, LD>& acc, 
   for (int u = 0; u < kPf; ++u) yr[u] = at(nb + u);
   const RowScatterMasks sm = row_scatter_masks(lane);
   const int bank = (lane >> 2) & 3;
+  RunVox run;   // not used
   for (int t0 = 0; t0 < steps; t0 += kTile) {
     RowScatter sa, sb;
     float lacc = 0.0f, sacc = 0.0f;
@@ -51,7 +52,7 @@ __device__ __forceinline__ void slot_loop(const Vox<K, LD>& x, Acc<K, LD>& acc, 
         const int n = nb + t0 + t + u, m = min(n, last);
         const float4 a = acq[3 * m], b = acq[3 * m + 1], c = acq[3 * m + 2];
         float tl, ts, sq, sd;
-        pair<K, MODE, LD>(x, acc, yr[u], n < ne ? valid : 0.0f, a, b, c, inv_s2, bes, tl, ts, sq, sd);
+        pair<K, MODE, LD, false>(x, acc, run, 0.0f, yr[u], n < ne ? valid : 0.0f, a, b, c, inv_s2, bes, tl, ts, sq, sd);
         lacc += tl;
         if (MODE == kNLL) sacc += ts;
         yr[u] = at(n + kPf);
@@ -107,12 +108,12 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slot = wave * LS + (LS == 1 ? 0 : lane / NV);
-  const int N = g.N;
+  const int N = g.N, Np = padded4(N);
   const int64_t V = g.V;
   float4* bes = smem4;
   float4* acq = smem4 + (MODE == kNLL ? kBesselRows : 0);   // [3N]
-  float* asum = reinterpret_cast<float*>(acq + 3 * N);      // [2][N] (LS = 1: [4][2][N], per wave)
-  float4* comb = reinterpret_cast<float4*>(asum + (LS == 1 ? 8 : 2) * N + (LS == 1 ? 0 : (N & 1) * 2));  // [NACC][NV]
+  float* asum = reinterpret_cast<float*>(acq + 3 * N);      // [2][Np] (LS = 1: [4][2][Np], per wave)
+  float4* comb = reinterpret_cast<float4*>(asum + (LS == 1 ? 8 : 2) * Np);  // [NACC][NV]
   const int lv = lane & (NV - 1);
   const bool ok = lv < it.nv;
   const float valid = ok ? 1.0f : 0.0f;
@@ -133,9 +134,9 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
     }
   }
   if (MODE == kNLL) stage_bessel(bes);
-  stage_acquisition(A, g, acq);
+  stage_acquisition(A, g, acq, LS == 1);   // slot_loop takes them as they come
   if (LS == 1)
-    for (int i = tid; i < 8 * N; i += kBlock) asum[i] = 0.0f;
+    for (int i = tid; i < 8 * Np; i += kBlock) asum[i] = 0.0f;
   if (A.adam && tid == 0) {
     adam_factors(A.step, A.lr, A.b1, A.b2, adam_sc[0], adam_sc[1]);
     if (it.first && A.info) *A.info = StepInfo{adam_sc[0], adam_sc[1], A.step[0]};
@@ -157,13 +158,15 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
   __syncthreads();
 
   double dloss = 0.0, dsig = 0.0;
-  const int nb = (N * slot) / S, ne = (N * (slot + 1)) / S;
   if constexpr (LS == 1) {
+    const int n_groups = (N + kPf - 1) / kPf;
+    const int ga = n_groups * wave / 4, gb = n_groups * (wave + 1) / 4;
     const int vs[1] = {v};
     const float va[1] = {valid};
-    measurement_loop<K, MODE, LD, 1, false>(xs, as, A.y + g.y_off, V, vs, va, acq, bes, nb, ne, g.nb0, N, inv_s2, lane,
-                                            asum + wave * 2 * N, dloss, dsig);
+    measurement_loop<K, MODE, LD, 1, false>(A, g, xs, as, vs, va, acq, bes, ga, gb, inv_s2, lane, asum + wave * 2 * Np,
+                                            dloss, dsig);
   } else {
+    const int nb = (N * slot) / S, ne = (N * (slot + 1)) / S;
     slot_loop<K, MODE, LD, LS>(x, acc, A.y + g.y_off, V, v, valid, acq, bes, nb, ne, N, inv_s2, lane, asum, dloss,
                                dsig);
   }
@@ -242,17 +245,25 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
     rec[kRecSigma] = (wsum[0][1] + wsum[1][1]) + (wsum[2][1] + wsum[3][1]);
     if (!has_sp) rec[kRecSpatial] = 0.0;
   }
-  for (int n = tid; n < 2 * N; n += kBlock)
-    rec[kRecAlpha + n] = LS == 1 ? ((double)asum[n] + (double)asum[2 * N + n]) +
-                                       ((double)asum[4 * N + n] + (double)asum[6 * N + n])
-                                 : (double)asum[n];
+  if constexpr (LS == 1) {
+    for (int p = tid; p < N; p += kBlock) {
+      const int n = A.perm[g.perm_off + p];
+      auto waves = [&](const float* s) {
+        return ((double)s[0] + (double)s[2 * Np]) + ((double)s[4 * Np] + (double)s[6 * Np]);
+      };
+      rec[kRecAlpha + n] = waves(asum + p) * (double)acq[3 * p + 2].x;   // times exp(alpha_n)
+      rec[kRecAlpha + N + n] = waves(asum + Np + p);
+    }
+  } else {
+    for (int n = tid; n < 2 * N; n += kBlock) rec[kRecAlpha + n] = (double)asum[n];
+  }
   if (bad_grad) atomicOr(A.status, (uint32_t)kStNonfiniteGrad);
   if (zero_dir) atomicOr(A.status, (uint32_t)kStZeroDir);
 }
 
 inline size_t split_lds_bytes(int N, int nacc, int ls, bool nll) {
-  return (size_t)N * 3 * sizeof(float4) + (size_t)(ls == 1 ? 8 : 4) * N * sizeof(float) +
-         (size_t)nacc * (64 / ls) * sizeof(float4) + (nll ? (size_t)kBesselRows * sizeof(float4) : 0) + 16;
+  return (size_t)N * 3 * sizeof(float4) + (size_t)(ls == 1 ? 8 : 2) * padded4(N) * sizeof(float) +
+         (size_t)nacc * (64 / ls) * sizeof(float4) + (nll ? (size_t)kBesselRows * sizeof(float4) : 0);
 }
 
 // f(kernel, LDS bytes) for the variant of one K

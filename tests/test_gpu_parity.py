@@ -281,3 +281,34 @@ def test_small_problems_in_rows_of_16_32_and_64_voxels(V, N, K, mode, learn_d):
         states.append(st)
     for a in ("params", "m", "v", "step", "loss"):
         assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
+
+
+@pytest.mark.parametrize("order", ["sorted", "interleaved", "all_different", "one_b", "b0_only_groups"])
+@pytest.mark.parametrize("N,mode,learn_d,launch", [(3, "mse", False, None), (41, "nll", True, dict(vox_per_lane=2, n_split=1)),
+                                                   (50, "mse", False, dict(vox_per_lane=1, n_split=2)),
+                                                   (64, "mse", True, dict(vox_per_lane=1, n_split=1, item_vox=512)),
+                                                   (30, "nll", False, dict(vox_per_lane=1, n_split=4, item_vox=64))])
+def test_runs_of_equal_b_in_any_order_of_the_acquisition(order, N, mode, learn_d, launch):
+    """Runs, left-over measurements and partial groups, taken in the library's own order
+    and returned in the caller's: every launch shape that has the measurement loop."""
+    rng = np.random.default_rng(N)
+    b = np.array([0.0, 1.0, 2.0, 3.0])[rng.integers(0, 4, size=N)]
+    b[0] = 1.0
+    if order == "sorted":
+        b = np.sort(b)
+    elif order == "all_different":
+        b = 0.5 + np.arange(N) / N
+    elif order == "one_b":
+        b[:] = 2.0
+    elif order == "b0_only_groups":
+        b = np.where(np.arange(N) % 9 < 8, 0.0, 0.5 + np.arange(N) / N)
+        b[0] = 1.0
+    acq = I.Acquisition(bval=b, bvec=I.uniform_sphere(N, rng))
+    shape = (5, 7, 19)
+    mask = rng.random(shape) < 0.9
+    V = int(mask.sum())
+    g = I.Group(shape=shape, mask=mask, acq=acq, K=3, mode=mode, bias="poly2", learn_diffusivity=learn_d)
+    g.y = rng.uniform(0.05, 1.0, size=(N, V)).astype(np.float32)
+    g = with_theta(g, I.perturb_theta(I.init_theta(V, 3, N, 10, rng, sigma_init=0.1 if mode == "nll" else 0.0,
+                                                   learn_diffusivity=learn_d), rng, scale=0.3))
+    _check_groups(f"{order} N={N} {mode} {launch}", [g], launch=launch)
