@@ -78,12 +78,18 @@ __device__ __forceinline__ void slot_loop(const Vox<K, LD>& x, Acc<K, LD>& acc, 
   }
 }
 
-// The element i of a register array at a slot that differs between lanes
+// The element i of a register array, i differing between lanes, by selects (through empty
+// asm statements: without them the compiler turns the selects into a store of the array to
+// scratch memory and a load at i, two round trips to the cache)
 template <int M>
 __device__ __forceinline__ float pick(const float (&x)[M], int i) {
   float r = x[0];
 #pragma unroll
-  for (int k = 1; k < M; ++k) r = i == k ? x[k] : r;
+  for (int k = 1; k < M; ++k) {
+    float t = x[k];
+    asm("" : "+v"(t));
+    r = i == k ? t : r;
+  }
   return r;
 }
 
