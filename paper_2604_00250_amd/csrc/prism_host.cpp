@@ -1062,7 +1062,11 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   if (!h->items.empty() && h->spatial_c >= 0) {  // some group has the Eq. 7 prior
     a.item_base = 0;
     a.n_items = (int)h->items.size();
-    e = launch_spatial(a, (int)h->items.size(), h->spatial_c, h->max_item_nv, s);
+    // six or fewer softmaxes more per voxel cost less than storing the fractions in a
+    // launch of their own; 26 cost more (see spatial_item)
+    bool from_logits = true;
+    for (const GroupDev& g : h->groups) from_logits = from_logits && g.nbh <= 6;
+    e = launch_spatial(a, (int)h->items.size(), h->spatial_c, h->max_item_nv, from_logits, s);
     if (e != hipSuccess) return hip_fail(e, "spatial-prior launch");
   } else if (h->launch.persistent) {
     e = launch_counter_reset(counter, s);

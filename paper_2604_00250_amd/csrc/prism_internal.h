@@ -192,8 +192,9 @@ struct StitchArgs {
 
 // launchers (prism_kernels.hip)
 // spatial_c: the C shared by every group with the Eq. 7 prior (0: none, or they differ)
-// max_nv: voxels of the largest work item
-hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, hipStream_t s);
+// max_nv: voxels of the largest work item; from_logits: one launch, no stored fractions
+hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, bool from_logits,
+                          hipStream_t s);
 // the persistent launches' counters, for calls without the kernels above
 hipError_t launch_counter_reset(int32_t* counters, hipStream_t s);
 hipError_t launch_stage(const PassArgs& a, int n_groups, hipStream_t s);

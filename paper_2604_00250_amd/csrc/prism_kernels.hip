@@ -2,8 +2,8 @@
 // other than the fused pass itself (prism_pass.h, instantiated per K in
 // prism_pass_k.hip, and its persistent form in prism_persistent.hip):
 //
-// k_fractions, k_spatial  Eq. 7: softmax fractions, then the residual weights
-//             rho'(r)/|N| per voxel and compartment.
+// k_spatial   Eq. 7: the residual weights rho'(r)/|N| per voxel and compartment, from
+//             the logits or (26-neighbourhood) the fractions that k_fractions stored.
 // k_reduce    deterministic reduction of per-item records into the calibration
 //             gradient and the loss terms.
 // k_bias_tri  gradient of the 8^3 trilinear log-bias grid.
@@ -17,7 +17,7 @@
 
 namespace prism {
 
-// The two Eq. 7 kernels run one block per work item with up to kAuxBlock
+// The Eq. 7 kernels run one block per work item with up to kAuxBlock
 // threads, one voxel per thread (the launch sizes the block to the largest
 // item): with fewer threads each one walked several voxels and the dependent
 // table-then-gather loads of each voxel in turn.
@@ -43,6 +43,14 @@ __device__ __forceinline__ void with_C(int C, F&& f) {
   }
 }
 
+template <int C>
+__device__ __forceinline__ void softmax_row(const float* th, int64_t V, int v, float (&r)[C]) {
+  float f[kMaxC];
+  softmax_at(th, V, C, v, f);
+#pragma unroll
+  for (int c = 0; c < C; ++c) r[c] = f[c];
+}
+
 // fractions f = softmax(logits) once per voxel, rows [V][C] (see load_row)
 template <int C>
 __device__ __forceinline__ void fractions_item(const PassArgs& A, const GroupDev& g, const ItemDev& it) {
@@ -51,11 +59,8 @@ __device__ __forceinline__ void fractions_item(const PassArgs& A, const GroupDev
   float* f_out = A.wsp + g.w_off + (int64_t)C * V;
   for (int lv = threadIdx.x; lv < it.nv; lv += blockDim.x) {
     const int v = it.v0 + lv;
-    float f[kMaxC];
-    softmax_at(th, V, C, v, f);
     float r[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) r[c] = f[c];
+    softmax_row<C>(th, V, v, r);
     store_row<C>(f_out, v, r);
   }
 }
@@ -73,14 +78,20 @@ __global__ __launch_bounds__(kAuxBlock) void k_fractions(PassArgs A) {
 // Eq. 7 residual weights w_c(x) = rho'(r_c(x)) / |N(x)| from the stored fractions.
 // Neighbours are taken six at a time: all six table entries are loaded, then
 // all their fraction rows (an absent neighbour reads the voxel's own row with
-// weight 0), so one round trip serves six neighbours.
-template <int C>
+// weight 0), so one round trip serves six neighbours.  FROM_LOGITS: the fractions are not
+// stored, each is taken from its voxel's logits again (the same bits).  The rows of the
+// logits are read at consecutive voxels for every neighbour, from the cache, so with the
+// 6-neighbourhood this takes less than storing the fractions first (an iteration of 16250
+// voxels, K = 3: 23.8 -> 22.6 us, 262k: 58.2 -> 55.3; the volume's Eq. 7 27 -> 23 us); with
+// 26 neighbours more (16250 voxels: 27.4 -> 28.3).
+template <int C, bool FROM_LOGITS>
 __device__ __forceinline__ double spatial_item(const PassArgs& A, const GroupDev& g, const ItemDev& it) {
   constexpr int kNb = 6;
   double lsum = 0.0;
   const int32_t* nbr = A.nbr + g.nbr_off;
   const int64_t V = g.V;
   const float* fr = A.wsp + g.w_off + (int64_t)C * V;
+  const float* th = A.th_micro + g.micro_off;
   float* w_out = A.wsp + g.w_off;
   const float delta = A.model.huber_delta;
   for (int lv = threadIdx.x; lv < it.nv; lv += blockDim.x) {
@@ -95,7 +106,12 @@ __device__ __forceinline__ double spatial_item(const PassArgs& A, const GroupDev
       for (int j = 0; j < kNb; ++j) u[j] = q0 + j < g.nbh ? nbr[(int64_t)(q0 + j) * V + v] : -1;
       float t[kNb][C];
 #pragma unroll
-      for (int j = 0; j < kNb; ++j) load_row<C>(fr, u[j] >= 0 ? u[j] : v, t[j]);
+      for (int j = 0; j < kNb; ++j) {
+        if (FROM_LOGITS)
+          softmax_row<C>(th, V, u[j] >= 0 ? u[j] : v, t[j]);
+        else
+          load_row<C>(fr, u[j] >= 0 ? u[j] : v, t[j]);
+      }
 #pragma unroll
       for (int j = 0; j < kNb; ++j) {
         const float on = u[j] >= 0 ? 1.0f : 0.0f;
@@ -105,7 +121,10 @@ __device__ __forceinline__ double spatial_item(const PassArgs& A, const GroupDev
       }
     }
     float own[C];
-    load_row<C>(fr, v, own);
+    if (FROM_LOGITS)
+      softmax_row<C>(th, V, v, own);
+    else
+      load_row<C>(fr, v, own);
     float ls = 0.0f;
     const float icnt = cnt > 0 ? 1.0f / (float)cnt : 0.0f;
     float w[C];
@@ -125,15 +144,16 @@ __device__ __forceinline__ double spatial_item(const PassArgs& A, const GroupDev
   return lsum;
 }
 
-template <int CT>
+template <int CT, bool FROM_LOGITS>
 __global__ __launch_bounds__(kAuxBlock) void k_spatial(PassArgs A) {
   __shared__ double red[kAuxBlock / 64];
+  if (FROM_LOGITS && blockIdx.x == 0 && threadIdx.x < 2) A.counters[32 * threadIdx.x] = 0;  // as k_fractions
   const ItemDev it = A.items[xcd_item(blockIdx.x, gridDim.x)];
   const GroupDev g = A.groups[it.group];
   const int tid = threadIdx.x;
   if (!((g.priors & kPriorSpatial) && g.nbh > 0)) return;  // the fused pass writes the record's 0
   double lsum = 0.0;
-  with_C<CT>(g.C, [&](auto c) { lsum = spatial_item<decltype(c)::value>(A, g, it); });
+  with_C<CT>(g.C, [&](auto c) { lsum = spatial_item<decltype(c)::value, FROM_LOGITS>(A, g, it); });
   lsum = wave_sum_f64(lsum);
   if ((tid & 63) == 0) red[tid >> 6] = lsum;
   __syncthreads();
@@ -606,23 +626,28 @@ int split_blocks_per_cu(int K, int mode, int learn_d, int ls, int N) {
 }
 
 template <int CT>
-static void launch_spatial_t(const PassArgs& a, dim3 grid, dim3 block, hipStream_t s) {
-  hipLaunchKernelGGL(k_fractions<CT>, grid, block, 0, s, a);
-  hipLaunchKernelGGL(k_spatial<CT>, grid, block, 0, s, a);
+static void launch_spatial_t(const PassArgs& a, dim3 grid, dim3 block, bool from_logits, hipStream_t s) {
+  if (from_logits) {
+    hipLaunchKernelGGL((k_spatial<CT, true>), grid, block, 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_fractions<CT>, grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_spatial<CT, false>), grid, block, 0, s, a);
+  }
 }
 
-hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, hipStream_t s) {
+hipError_t launch_spatial(const PassArgs& a, int n_items, int spatial_c, int max_nv, bool from_logits,
+                          hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   // whole waves, one thread per voxel of the largest item, at most kAuxBlock
   const dim3 grid(n_items), block(std::min(kAuxBlock, std::max(64, (max_nv + 63) / 64 * 64)));
   switch (spatial_c) {
-    case 4: launch_spatial_t<4>(a, grid, block, s); break;
-    case 5: launch_spatial_t<5>(a, grid, block, s); break;
-    case 6: launch_spatial_t<6>(a, grid, block, s); break;
-    case 7: launch_spatial_t<7>(a, grid, block, s); break;
-    case 8: launch_spatial_t<8>(a, grid, block, s); break;
-    case 9: launch_spatial_t<9>(a, grid, block, s); break;
-    default: launch_spatial_t<0>(a, grid, block, s); break;
+    case 4: launch_spatial_t<4>(a, grid, block, from_logits, s); break;
+    case 5: launch_spatial_t<5>(a, grid, block, from_logits, s); break;
+    case 6: launch_spatial_t<6>(a, grid, block, from_logits, s); break;
+    case 7: launch_spatial_t<7>(a, grid, block, from_logits, s); break;
+    case 8: launch_spatial_t<8>(a, grid, block, from_logits, s); break;
+    case 9: launch_spatial_t<9>(a, grid, block, from_logits, s); break;
+    default: launch_spatial_t<0>(a, grid, block, from_logits, s); break;
   }
   return hipGetLastError();
 }
