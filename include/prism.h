@@ -314,13 +314,12 @@ int32_t prism_adam_step(float* p, const float* g, float* m, float* v, int64_t n,
  * theta_cal, after which step[0] has advanced by one.  The results are
  * bitwise those of prism_loss_grad followed by prism_adam_step over the same
  * parameters.  The per-voxel parameters are updated inside the fused pass, so
- * their gradient never goes through memory; when a group uses the continuity
- * prior (which reads neighbouring voxels' parameters during the pass) the call
- * runs the two steps one after the other and grad_micro receives the
- * per-voxel gradient.  Arguments as for prism_loss_grad and prism_adam_step;
- * m_micro, v_micro [n_micro] and m_cal, v_cal [n_cal] are the Adam moments
- * (device), grad_micro [n_micro] (device) is scratch for the unfused case,
- * grad_cal [n_cal] receives the calibration gradient.
+ * their gradient never goes through memory; only when a group uses the
+ * continuity prior grad_micro receives the per-voxel gradient as well.
+ * Arguments as for prism_loss_grad and prism_adam_step; m_micro, v_micro
+ * [n_micro] and m_cal, v_cal [n_cal] are the Adam moments (device), grad_micro
+ * [n_micro] (device) is scratch otherwise, grad_cal [n_cal] receives the
+ * calibration gradient.
  *   loss_history  NULL, or a device float64 ring [history_len][n_groups]
  *                 [PRISM_LOSS_TERMS]: the call also writes its loss rows to
  *                 slot t mod history_len, t = the iteration's index (step[0]

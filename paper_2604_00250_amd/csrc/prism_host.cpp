@@ -84,7 +84,7 @@ struct prism_problem {
   int max_item_nv = 0;  // voxels of the plan's largest work item
   int persistent_grid = 0;
   int64_t n_vox = 0, n_micro = 0, n_cal = 0, n_y = 0;
-  size_t ws_rec = 0, ws_float = 0;  // element counts
+  size_t ws_rec = 0, ws_float = 0, ws_dirs = 0;  // element counts
   // device tables
   GroupDev* d_groups = nullptr;
   ItemDev* d_items = nullptr;
@@ -655,7 +655,7 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
                       model->lam_tv};
   std::vector<int32_t> coords, nbr, grid;
   std::vector<float> ninv;
-  int64_t micro = 0, cal = 0, y = 0, vox = 0, wfl = 0;
+  int64_t micro = 0, cal = 0, y = 0, vox = 0, wfl = 0, dfl = 0;
   for (int gi = 0; gi < n_groups; ++gi) {
     const prism_group_desc& d = groups[gi];
     auto bad = [&](const char* what) {
@@ -780,7 +780,7 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
     g.grid_off = (int64_t)grid.size();
     if (d.bias == PRISM_BIAS_TRILINEAR8) {
       grid.insert(grid.end(), idx.begin(), idx.end());
-      h->tri_groups.push_back(gi);
+      if (V > 0) h->tri_groups.push_back(gi);
     }
     wfl = (wfl + 3) & ~(int64_t)3;  // 16-byte aligned buffers
     g.w_off = wfl;  // [V][C] residual weights, then [V][C] fractions
@@ -789,6 +789,8 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
       wfl = (wfl + 3) & ~(int64_t)3;
       h->spatial_c = h->spatial_c < 0 ? g.C : (h->spatial_c == g.C ? g.C : 0);
     }
+    g.dir_off = dfl;
+    if ((d.priors & PRISM_PRIOR_CONTINUITY) && d.neighbourhood) dfl += (int64_t)3 * g.K * V;
     g.glb_off = wfl;
     if (d.bias == PRISM_BIAS_TRILINEAR8) wfl += V;
     wfl = (wfl + 3) & ~(int64_t)3;  // 16-byte aligned acquisition table
@@ -808,6 +810,7 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
   h->n_cal = cal;
   h->n_y = y;
   h->ws_float = (size_t)wfl;
+  h->ws_dirs = (size_t)dfl;
   h->acq_off = acq_off;
   h->coords_host = coords;
   // default launch shape: one voxel per lane (three waves per SIMD for the
@@ -944,11 +947,18 @@ int32_t prism_problem_plan_info(const prism_problem* h, int32_t* n_items, int32_
 
 const char* prism_build_id(void) { return PRISM_SOURCE_HASH; }
 
+// The workspace of a pass that writes the gradient; prism_iteration_adam's copy of the
+// directions for the continuity prior follows it (the allocation-free entry point, which
+// only writes the gradient, needs no room for it).
+static size_t workspace_without_dirs(const prism_problem* h) {
+  return align256(h->ws_rec * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
+         align256(h->groups.size() * 3 * sizeof(double)) +
+         512;  // + the persistent launches' item counters, the step's StepInfo
+}
+
 int32_t prism_workspace_bytes(const prism_problem* h, size_t* bytes) {
   if (!h || !bytes) return fail(PRISM_E_INVALID, "NULL argument");
-  *bytes = align256(h->ws_rec * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
-           align256(h->groups.size() * 3 * sizeof(double)) +
-           512;  // + the persistent launches' item counters, the step's StepInfo
+  *bytes = workspace_without_dirs(h) + align256(h->ws_dirs * sizeof(float));
   return PRISM_OK;
 }
 
@@ -1045,6 +1055,9 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   PassArgs a = pass_args(h, y, theta_micro, theta_cal, grad_micro, rec, wsp, status);
   a.calsq = calsq;
   a.counters = counter;
+  const size_t base = workspace_without_dirs(h);
+  // (a pass that only writes the gradient leaves theta_micro as it is)
+  if (adam && h->ws_dirs > 0) a.dirs = (float*)(ws + base);
   if (adam) {
     a.adam = 1;
     a.th_upd = adam->th_upd;
@@ -1056,17 +1069,20 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
     a.b2 = adam->b2;
     a.eps = adam->eps;
     if (cal_adam) a.info = info;
+    // a problem with the continuity prior returns the per-voxel gradient too
+    for (const GroupDev& g : h->groups)
+      if ((g.priors & PRISM_PRIOR_CONTINUITY) && g.nbh > 0) a.store_grad = 1;
   }
   hipError_t e = launch_stage(a, (int)h->groups.size(), s);
   if (e != hipSuccess) return hip_fail(e, "acquisition staging launch");
-  if (!h->items.empty() && h->spatial_c >= 0) {  // some group has the Eq. 7 prior
+  if (!h->items.empty() && (h->spatial_c >= 0 || a.dirs)) {  // some group has the Eq. 7 prior, or the continuity prior
     a.item_base = 0;
     a.n_items = (int)h->items.size();
     // six or fewer softmaxes more per voxel cost less than storing the fractions in a
     // launch of their own; 26 cost more (see spatial_item)
     bool from_logits = true;
     for (const GroupDev& g : h->groups) from_logits = from_logits && g.nbh <= 6;
-    e = launch_spatial(a, (int)h->items.size(), h->spatial_c, h->max_item_nv, from_logits, s);
+    e = launch_spatial(a, (int)h->items.size(), std::max(h->spatial_c, 0), h->max_item_nv, from_logits, s);
     if (e != hipSuccess) return hip_fail(e, "spatial-prior launch");
   } else if (h->launch.persistent) {
     e = launch_counter_reset(counter, s);
@@ -1122,6 +1138,8 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   r.status = status;
   r.model = h->model;
   r.n_tiles = h->n_tiles;
+  r.tri_groups = h->d_tri;
+  r.n_tri = (int)h->tri_groups.size();
   r.row_tiles = h->d_tiles + h->n_tiles;
   r.n_row_tiles = (int)h->tiles.size() - h->n_tiles;
   r.n_groups = (int)h->groups.size();
@@ -1147,8 +1165,6 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   }
   e = launch_reduce(r, h->max_records, s);
   if (e != hipSuccess) return hip_fail(e, "reduction launch");
-  e = launch_bias_trilinear(r, h->d_tri, (int)h->tri_groups.size(), s);
-  if (e != hipSuccess) return hip_fail(e, "trilinear-bias launch");
   return PRISM_OK;
 }
 
@@ -1185,8 +1201,7 @@ int32_t prism_loss_grad_noalloc(const prism_problem* h, const float* y, const fl
                                 const float* theta_cal, double* loss, float* grad_micro,
                                 float* grad_cal, uint32_t* status, void* stream) {
   if (!h) return fail(PRISM_E_INVALID, "handle is NULL");
-  size_t need = 0;
-  prism_workspace_bytes(h, &need);
+  const size_t need = workspace_without_dirs(h);
   if (need > kStaticScratchBytes)
     return fail(PRISM_E_WORKSPACE,
                 "the problem needs %zu bytes of workspace; the static workspace of "
@@ -1196,7 +1211,7 @@ int32_t prism_loss_grad_noalloc(const prism_problem* h, const float* y, const fl
   void* ws = static_scratch(h->device, &e);
   if (!ws) return hip_fail(e, "static workspace of the problem's device");
   int rc = check_pass_args(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, ws,
-                           kStaticScratchBytes, status);
+                           SIZE_MAX, status);
   if (rc != PRISM_OK) return rc;
   return run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, ws, status,
                   (hipStream_t)stream, nullptr);
@@ -1217,10 +1232,7 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
   if (!(lr >= 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) || !(eps >= 0.0f))
     return fail(PRISM_E_INVALID, "Adam hyper-parameters out of range");
   hipStream_t s = (hipStream_t)stream;
-  bool fuse = true;  // the continuity prior reads neighbours' parameters during the pass
-  for (const GroupDev& g : h->groups)
-    if ((g.priors & PRISM_PRIOR_CONTINUITY) && g.nbh > 0) fuse = false;
-  if (fuse && !h->items.empty()) {
+  if (!h->items.empty()) {
     // one call: the per-voxel parameters are updated in the fused pass, the
     // calibration vector where its gradient is written, the step counter after both
     PassArgs ad{};
@@ -1237,29 +1249,11 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
     return run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, &ad, &ca,
                     &hi);
   }
-  if (fuse) {
-    PassArgs ad{};
-    ad.th_upd = theta_micro;
-    ad.m_micro = m_micro;
-    ad.v_micro = v_micro;
-    ad.step = step;
-    ad.lr = lr;
-    ad.b1 = beta1;
-    ad.b2 = beta2;
-    ad.eps = eps;
-    const History hi{loss_history, step, history_len};
-    rc = run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, &ad, nullptr,
-                  &hi);
-    if (rc != PRISM_OK) return rc;
-  } else {
-    const History hi{loss_history, step, history_len};
-    rc = run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, nullptr,
-                  nullptr, &hi);
-    if (rc != PRISM_OK) return rc;
-    hipError_t e = launch_adam(theta_micro, grad_micro, m_micro, v_micro, h->n_micro, lr, beta1, beta2, eps,
-                               step, s, false);
-    if (e != hipSuccess) return hip_fail(e, "Adam launch");
-  }
+  // empty groups alone: their losses, then Adam on the calibration
+  const History hi{loss_history, step, history_len};
+  rc = run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status, s, nullptr, nullptr,
+                &hi);
+  if (rc != PRISM_OK) return rc;
   hipError_t e = launch_adam(theta_cal, grad_cal, m_cal, v_cal, update_cal ? h->n_cal : 0, lr, beta1, beta2,
                              eps, step, s, true);
   if (e != hipSuccess) return hip_fail(e, "Adam launch");

@@ -39,6 +39,7 @@ struct GroupDev {
                       // the face neighbours -x, +x, -y, +y, -z, +z, then the rest of 26
   int64_t ninv_off;   // float offset of 1/|N(x)| [V] (0 without neighbours)
   int64_t w_off;      // float offset of the spatial weights [V][C], then fractions [V][C], in the workspace
+  int64_t dir_off;    // float offset of the raw directions [3K][V] in PassArgs.dirs (continuity)
   int64_t glb_off;    // float offset of per-voxel dL/dlogB [V] in the workspace (trilinear)
   int64_t rec_off;    // float64 offset of the group's first item record
   int64_t grid_off;   // int32 offset of the dense raster->voxel index grid (trilinear)
@@ -126,6 +127,9 @@ struct PassArgs {
   float* g_micro;
   double* rec;
   float* wsp;              // workspace floats (spatial weights, per-voxel dlogB, acquisition tables)
+  float* dirs;             // workspace: a copy of the raw directions of the groups with the continuity prior,
+                           // left by k_spatial (nullptr: the pass takes the neighbours' from theta_micro)
+  int32_t store_grad;      // with adam: the per-voxel gradient is stored too
   uint32_t* status;
   ModelDev model;
   int32_t item_base;       // first item of this launch
@@ -150,6 +154,8 @@ struct PassArgs {
 struct ReduceArgs {
   const GroupDev* groups;
   const TileDev* tiles;
+  const int32_t* tri_groups; // groups with voxels and a trilinear bias grid, 512 blocks each after the tiles
+  int32_t n_tri;
   const TileDev* row_tiles;  // of k_reduce_rows
   int32_t n_row_tiles;
   double* rec;
@@ -222,8 +228,6 @@ hipError_t launch_pass_maxn(const PassArgs& a, int K, int mode, int learn_d, int
                             hipStream_t s);
 // max_records: most records of a group
 hipError_t launch_reduce(const ReduceArgs& a, int max_records, hipStream_t s);
-hipError_t launch_bias_trilinear(const ReduceArgs& a, const int32_t* tri_groups, int n_tri,
-                                 hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr,
                        float b1, float b2, float eps, int32_t* step, hipStream_t s,
                        bool advance = true);

@@ -5,8 +5,7 @@
 // k_spatial   Eq. 7: the residual weights rho'(r)/|N| per voxel and compartment, from
 //             the logits or (26-neighbourhood) the fractions that k_fractions stored.
 // k_reduce    deterministic reduction of per-item records into the calibration
-//             gradient and the loss terms.
-// k_bias_tri  gradient of the 8^3 trilinear log-bias grid.
+//             gradient (the 8^3 trilinear log-bias grid's too) and the loss terms.
 // k_stitch    blend of per-slab maps into whole-volume maps (slab fitting).
 // k_adam, k_rprop  optimiser steps.
 #include <algorithm>
@@ -144,6 +143,15 @@ __device__ __forceinline__ double spatial_item(const PassArgs& A, const GroupDev
   return lsum;
 }
 
+// A copy of the raw directions [3K][V] for the continuity prior, before the fused pass
+// updates any voxel's: the pass reads its neighbours' from here.
+__device__ __forceinline__ void directions_item(const PassArgs& A, const GroupDev& g, const ItemDev& it) {
+  const float* th = A.th_micro + g.micro_off + (int64_t)row_v(g.C, 0, 0) * g.V;
+  float* out = A.dirs + g.dir_off;
+  for (int lv = threadIdx.x; lv < it.nv; lv += blockDim.x)
+    for (int r = 0; r < 3 * g.K; ++r) out[(int64_t)r * g.V + it.v0 + lv] = th[(int64_t)r * g.V + it.v0 + lv];
+}
+
 template <int CT, bool FROM_LOGITS>
 __global__ __launch_bounds__(kAuxBlock) void k_spatial(PassArgs A) {
   __shared__ double red[kAuxBlock / 64];
@@ -151,6 +159,8 @@ __global__ __launch_bounds__(kAuxBlock) void k_spatial(PassArgs A) {
   const ItemDev it = A.items[xcd_item(blockIdx.x, gridDim.x)];
   const GroupDev g = A.groups[it.group];
   const int tid = threadIdx.x;
+  if (A.dirs && (g.priors & kPriorCont) && g.nbh > 0)
+    directions_item(A, g, it);
   if (!((g.priors & kPriorSpatial) && g.nbh > 0)) return;  // the fused pass writes the record's 0
   double lsum = 0.0;
   with_C<CT>(g.C, [&](auto c) { lsum = spatial_item<decltype(c)::value, FROM_LOGITS>(A, g, it); });
@@ -258,6 +268,86 @@ __global__ __launch_bounds__(256) void k_stitch(StitchArgs S) {
   for (int p = 0; p < P; ++p) S.maps[(int64_t)p * S.n_out + o] = out[p];
 }
 
+// a finished entry of a group's calibration gradient, and its Adam step
+__device__ __forceinline__ void cal_entry(const ReduceArgs& R, const GroupDev& g, int dst, float out) {
+  const int64_t i = g.cal_off + dst;
+  R.g_cal[i] = out;
+  if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
+  if (R.cal_adam) {
+    float p = R.th_cal_upd[i], m = R.m_cal[i], v = R.v_cal[i];
+    adam_one(p, out, m, v, R.b1, R.b2, R.eps, R.info->step_size, R.info->ibc2);
+    R.th_cal_upd[i] = p;
+    R.m_cal[i] = m;
+    R.v_cal[i] = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// trilinear 8^3 log-bias gradient: dL/db(c) = sum_x w_c(x) dL/dlogB(x)
+// ---------------------------------------------------------------------------
+// Control point cp of one group by one block of k_reduce's launch (it reads none of what
+// the tiles write: as a launch after them it took 12 us more for 30k voxels).  red: one
+// value per wave.
+__device__ void bias_tri_point(const ReduceArgs& R, const GroupDev& g, int cp, double* red) {
+  const int nt = blockDim.x;
+  const int cidx[3] = {cp >> 6, (cp >> 3) & 7, cp & 7};
+  const int nn[3] = {g.nx, g.ny, g.nz};
+  int lo[3], hi[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (nn[a] == 1) {
+      lo[a] = 0;
+      hi[a] = cidx[a] == 0 ? 0 : -1;
+    } else {
+      const float sc = (float)(nn[a] - 1) / 7.0f;
+      lo[a] = max(0, (int)ceilf((cidx[a] - 1) * sc));
+      hi[a] = min(nn[a] - 1, (int)floorf((cidx[a] + 1) * sc));
+    }
+  }
+  double acc = 0.0;
+  const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
+  if (ex > 0 && ey > 0 && ez > 0) {
+    const int tot = ex * ey * ez;   // a part of a box of at most 2^31 voxels
+    const int32_t* grid = R.grid + g.grid_off;
+    const float* glb = R.wsp + g.glb_off;
+    // four positions per round: their voxels, then those voxels' adjoints
+    for (int64_t q0 = threadIdx.x; q0 < tot; q0 += 4 * nt) {
+      float w[4];
+      int v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t qe = q0 + (int64_t)e * nt;
+        const uint32_t q = (uint32_t)(qe < tot ? qe : tot - 1);
+        const uint32_t ij = q / (uint32_t)ez, ia = ij / (uint32_t)ey;
+        const int ii[3] = {lo[0] + (int)ia, lo[1] + (int)(ij - ia * (uint32_t)ey), lo[2] + (int)(q - ij * (uint32_t)ez)};
+        v[e] = grid[((int64_t)ii[0] * g.ny + ii[1]) * g.nz + ii[2]];
+        w[e] = qe < tot ? 1.0f : 0.0f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const float p = ii[a] * g.tri_sc[a];  // the coordinate of log_bias, bit for bit
+          w[e] *= fmaxf(0.0f, 1.0f - fabsf(p - (float)cidx[a]));
+        }
+      }
+      float b[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[e] = glb[max(v[e], 0)];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (v[e] >= 0) acc += (double)w[e] * (double)b[e];
+    }
+  }
+  acc = wave_sum_f64(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int i = 0; i < nt / 64; ++i) s += red[i];
+    const float* cal = R.th_cal + g.cal_off;
+    const bool cal_on = (g.priors & kPriorCal) != 0;
+    cal_entry(R, g, cp, (float)(s + (cal_on ? 2.0 * (double)R.model.lam_bias * cal[cp] : 0.0)));
+  }
+}
+
 // ---------------------------------------------------------------------------
 // deterministic reduction of the item records
 // ---------------------------------------------------------------------------
@@ -299,6 +389,11 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce_rows(ReduceArgs R) {
 __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
   __shared__ double part[kReduceWide];
   __shared__ double sq[3][kReduceWide / 64];
+  if ((int)blockIdx.x >= R.n_tiles) {
+    const int q = blockIdx.x - R.n_tiles;
+    bias_tri_point(R, R.groups[R.tri_groups[q / 512]], q % 512, sq[0]);
+    return;
+  }
   const TileDev t = R.tiles[blockIdx.x];
   const GroupDev g = R.groups[t.group];
   const int tid = threadIdx.x, nt = blockDim.x;
@@ -377,18 +472,12 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
       dst = nb + N + n;
       out = (float)(sdata * tot + (cal_on ? 2.0 * (double)R.model.lam_beta * cal[nb + N + n] : 0.0));
     }
-    if (dst >= 0) {
-      R.g_cal[g.cal_off + dst] = out;
-      if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
-      if (R.cal_adam) {
-        float p = R.th_cal_upd[g.cal_off + dst], m = R.m_cal[g.cal_off + dst], v = R.v_cal[g.cal_off + dst];
-        adam_one(p, out, m, v, R.b1, R.b2, R.eps, R.info->step_size, R.info->ibc2);
-        R.th_cal_upd[g.cal_off + dst] = p;
-        R.m_cal[g.cal_off + dst] = m;
-        R.v_cal[g.cal_off + dst] = v;
-      }
-    }
+    if (dst >= 0) cal_entry(R, g, dst, out);
   }
+  // an empty group's control grid has its prior alone
+  if (empty && g.bias == 2)
+    for (int i = tid; i < nb; i += nt)
+      cal_entry(R, g, i, cal_on ? (float)(2.0 * (double)R.model.lam_bias * cal[i]) : 0.0f);
   // the step counter: no other block of this launch reads it (they read R.info)
   if (R.step && blockIdx.x == 0 && tid == 0) {
     R.step[0] = R.step[0] + 1;
@@ -437,71 +526,6 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
       double* H = R.hist + ((int64_t)slot * R.n_groups + t.group) * kLossTerms;
 #pragma unroll
       for (int i = 0; i < kLossTerms; ++i) H[i] = L[i];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// trilinear 8^3 log-bias gradient: dL/db(c) = sum_x w_c(x) dL/dlogB(x)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bias_tri(ReduceArgs R, const int32_t* tri_groups) {
-  __shared__ double red[4];
-  const GroupDev g = R.groups[tri_groups[blockIdx.y]];
-  const int cp = blockIdx.x;
-  const int cidx[3] = {cp >> 6, (cp >> 3) & 7, cp & 7};
-  const int nn[3] = {g.nx, g.ny, g.nz};
-  int lo[3], hi[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (nn[a] == 1) {
-      lo[a] = 0;
-      hi[a] = cidx[a] == 0 ? 0 : -1;
-    } else {
-      const float sc = (float)(nn[a] - 1) / 7.0f;
-      lo[a] = max(0, (int)ceilf((cidx[a] - 1) * sc));
-      hi[a] = min(nn[a] - 1, (int)floorf((cidx[a] + 1) * sc));
-    }
-  }
-  double acc = 0.0;
-  const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
-  if (ex > 0 && ey > 0 && ez > 0) {
-    const int64_t tot = (int64_t)ex * ey * ez;
-    const int32_t* grid = R.grid + g.grid_off;
-    const float* glb = R.wsp + g.glb_off;
-    for (int64_t q = threadIdx.x; q < tot; q += 256) {
-      const int i = lo[0] + (int)(q / ((int64_t)ey * ez));
-      const int j = lo[1] + (int)((q / ez) % ey);
-      const int k = lo[2] + (int)(q % ez);
-      const int v = grid[((int64_t)i * g.ny + j) * g.nz + k];
-      if (v < 0) continue;
-      const int ii[3] = {i, j, k};
-      float w = 1.0f;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const float p = ii[a] * g.tri_sc[a];  // the coordinate of log_bias, bit for bit
-        w *= fmaxf(0.0f, 1.0f - fabsf(p - (float)cidx[a]));
-      }
-      acc += (double)w * (double)glb[v];
-    }
-  }
-  acc = wave_sum_f64(acc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double s = red[0] + red[1] + red[2] + red[3];
-    const float* cal = R.th_cal + g.cal_off;
-    const bool cal_on = (g.priors & kPriorCal) != 0;
-    const float out = (float)(s + (cal_on ? 2.0 * (double)R.model.lam_bias * cal[cp] : 0.0));
-    R.g_cal[g.cal_off + cp] = out;
-    if (!isfinite(out)) atomicOr(R.status, (uint32_t)kStNonfiniteGrad);
-    if (R.cal_adam) {
-      const float ss = R.info->step_size, ib = R.info->ibc2;
-      const int64_t i = g.cal_off + cp;
-      float p = R.th_cal_upd[i], m = R.m_cal[i], v = R.v_cal[i];
-      adam_one(p, out, m, v, R.b1, R.b2, R.eps, ss, ib);
-      R.th_cal_upd[i] = p;
-      R.m_cal[i] = m;
-      R.v_cal[i] = v;
     }
   }
 }
@@ -658,14 +682,7 @@ hipError_t launch_reduce(const ReduceArgs& a, int max_records, hipStream_t s) {
   // narrow tiles of up to 256 records: one round of loads with 32 threads a column; of
   // more: 128 threads a column
   const int block = max_records > 256 ? kReduceWide : kReduceBlock;
-  hipLaunchKernelGGL(k_reduce, dim3(a.n_tiles), dim3(block), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_bias_trilinear(const ReduceArgs& a, const int32_t* tri_groups, int n_tri,
-                                 hipStream_t s) {
-  if (n_tri <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bias_tri, dim3(512, n_tri), dim3(256), 0, s, a, tri_groups);
+  hipLaunchKernelGGL(k_reduce, dim3(a.n_tiles + 512 * a.n_tri), dim3(block), 0, s, a);
   return hipGetLastError();
 }
 

@@ -746,7 +746,8 @@ __device__ __forceinline__ void chain_rule(const PassArgs& A, const GroupDev& g,
     // enters the sums of x and of u, weighted 1/|N(x)| and 1/|N(u)|
     const int32_t* nbr = A.nbr + g.nbr_off;
     const float* ninv = A.ninv + g.ninv_off;
-    const float* th = A.th_micro + g.micro_off;
+    // the raw directions [3K][V]: the copy that no block updates, or theta_micro's rows
+    const float* vd = A.dirs ? A.dirs + g.dir_off : A.th_micro + g.micro_off + (int64_t)row_v(C, 0, 0) * V;
     const float sc2 = g.sc_cont2;
     const float ax = ninv[v];
     float lc = 0.0f;
@@ -756,9 +757,9 @@ __device__ __forceinline__ void chain_rule(const PassArgs& A, const GroupDev& g,
       const float w = sc2 * (ax + ninv[u]);
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const float ux = th[(int64_t)row_v(C, k, 0) * V + u];
-        const float uy = th[(int64_t)row_v(C, k, 1) * V + u];
-        const float uz = th[(int64_t)row_v(C, k, 2) * V + u];
+        const float ux = vd[(int64_t)(3 * k) * V + u];
+        const float uy = vd[(int64_t)(3 * k + 1) * V + u];
+        const float uz = vd[(int64_t)(3 * k + 2) * V + u];
         const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
         const float in = n2 > 0.0f ? rsq(n2) : 0.0f;
         const float dx = ux * in, dy = uy * in, dz = uz * in;
@@ -982,6 +983,14 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
         if ((g.priors & kPriorTV) && g.bias != 0) e_tv += vt.tv;
         const float glb = vt.glb;
         constexpr int P = 4 * K + 5 + (LD ? 2 : 0);
+        if (!A.adam || A.store_grad) {
+          RowCursor<float> gs(gm, V);
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            if (!A.adam && !isfinite(gout[p])) bad_grad = true;
+            store_row_f32(gs.next(), vrowb, voff, gout[p]);
+          }
+        }
         if (A.adam) {
           // fused Adam on this voxel's parameters (only this thread touches them)
           const float ss = sh.adam_sc[0], ib = sh.adam_sc[1];
@@ -1013,13 +1022,6 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
                 store_row_f32(vs.next(), vrowb, voff, v1[q]);
               }
             __builtin_amdgcn_sched_barrier(0);
-          }
-        } else {
-          RowCursor<float> gs(gm, V);
-#pragma unroll
-          for (int p = 0; p < P; ++p) {
-            if (!isfinite(gout[p])) bad_grad = true;
-            store_row_f32(gs.next(), vrowb, voff, gout[p]);
           }
         }
         if (g.bias == 1) {

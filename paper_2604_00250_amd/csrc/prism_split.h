@@ -215,9 +215,8 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
         store_row_f32(A.th_upd + g.micro_off, blkb, off, pp[i]);
         store_row_f32(A.m_micro + g.micro_off, blkb, off, m1[i]);
         store_row_f32(A.v_micro + g.micro_off, blkb, off, v1[i]);
-      } else {
-        store_row_f32(A.g_micro + g.micro_off, blkb, off, gp);
       }
+      if (!A.adam || A.store_grad) store_row_f32(A.g_micro + g.micro_off, blkb, off, gp);
     }
   }
   if (g.bias == 2 && ok && slot == 0) A.wsp[g.glb_off + v] = vt.glb;

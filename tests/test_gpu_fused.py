@@ -60,3 +60,27 @@ def test_fused_iteration_can_hold_the_calibration():
     torch.cuda.synchronize()
     assert torch.equal(a.params[a.n_micro:], cal0)
     assert _same(a, b)
+
+
+@pytest.mark.parametrize("launch", [None, dict(vox_per_lane=1, n_split=0, item_vox=0, persistent=1),
+                                    dict(vox_per_lane=1, n_split=1, item_vox=256)])
+def test_continuity_iteration_still_returns_the_per_voxel_gradient(launch):
+    """The fused pass updates the directions that neighbours read (from a copy) and, with
+    the continuity prior, stores the gradient beside the update: both bit for bit those
+    of the separate steps, with a group of another K and no Eq. 7 prior beside it."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    a = masked_group((6, 7, 9), K=3, mode="mse", seed=5, priors=("spatial", "rep", "cal", "continuity"))
+    b = masked_group((5, 6, 4), K=2, mode="nll", seed=6, priors=("continuity",), nbh=26)
+    groups = [a, b]
+    states = []
+    for fused in (True, False):
+        st = DeviceState(Problem(groups, launch=launch), ys=[g.y for g in groups], thetas=[g.theta for g in groups])
+        for _ in range(2):
+            st.iteration(lr=1e-2) if fused else st.iteration_unfused(lr=1e-2)
+        torch.cuda.synchronize()
+        states.append(st)
+    n = states[0].n_micro
+    for name in ("params", "m", "v", "step", "loss"):
+        assert torch.equal(getattr(states[0], name), getattr(states[1], name)), name
+    assert torch.equal(states[0].grad[:n], states[1].grad[:n])
