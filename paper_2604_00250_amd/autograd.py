@@ -35,7 +35,8 @@ class PrismLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_out):
         (grad,) = ctx.saved_tensors
-        return grad * g_out.to(grad.dtype), None
+        # g_out is a 0-dim float64 tensor: the product is float32, g_out rounded to it once
+        return grad * g_out, None
 
 
 def prism_loss(params, state):
