@@ -244,7 +244,9 @@ int64_t voxel_cost(const GroupDev& g) { return loop_cost(g) + fixed_cost(g); }
 //    8000   34.5 /  53.9  32.8 /  52.7  29.0 / 39.7   30.8 / 41.1
 //   16250   35.7 /  55.3  34.4 /  55.6  33.4 / 50.6   37.8 / 62.6
 //   32768   41.2 /  69.4  40.6 /  94.8  41.6 / 81.1   52.7 / 103
-// (K = 5 NLL blocks are resident one per compute unit: 64 voxels end at 16384.)
+// Rows of 64 also serve up to two rounds of blocks where the fused pass would take two as
+// well: K = 4, NLL, learned D, N = 96, 42768 voxels 60.9 -> 55.1 us, 64000 71.4 -> 64.7; K = 2, NLL,
+// N = 33, 64000 voxels 44.4 -> 38.7, but 42768, one round of the fused pass, 31.1 -> 34.7.
 int group_split(const prism_problem* h, const prism_launch& L, const GroupDev& g) {
   if (L.persistent || L.vox_per_lane != 1 || L.n_split != 4 || (L.item_vox != 0 && L.item_vox != 64)) return 0;
   if ((int64_t)g.V * std::max(g.N, g.P) * 4 >= ((int64_t)1 << 31)) return 0;
@@ -257,6 +259,9 @@ int group_split(const prism_problem* h, const prism_launch& L, const GroupDev& g
     const int most = ls == 2 && loop_cost(g) < 4 * fixed_cost(g) ? 1 : 4 / ls;
     const int64_t per_cu = std::min(most, split_blocks_per_cu(g.K, g.mode, g.learn_d, ls, g.N));
     if (blocks <= cus * per_cu) return ls;
+    if (ls == 1 && blocks <= 2 * cus * per_cu &&
+        blocks > (int64_t)cus * split_blocks_per_cu(g.K, g.mode, g.learn_d, 0, g.N))
+      return ls;
   }
   return 0;
 }
@@ -1021,8 +1026,8 @@ namespace {
 // Workspace carve-up and the pass: Eq. 7 weights, fused pass, reductions, the
 // trilinear bias adjoint.  `adam` (optional) turns on the fused update of the
 // per-voxel parameters in the pass epilogue; with `cal_adam` also set, the
-// calibration vector is updated where its gradient is written (k_reduce,
-// k_bias_tri) and k_reduce advances the step counter.
+// calibration vector is updated where its gradient is written, in k_reduce,
+// which also advances the step counter.
 struct CalAdam {
   float* th;
   float* m;

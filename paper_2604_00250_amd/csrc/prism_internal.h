@@ -148,7 +148,7 @@ struct PassArgs {
   StepInfo* info;          // left by the first item's block (nullptr: not needed)
   double* calsq;           // [n_groups][3] sums of squares of alpha, beta, bias, left by the block
                            // of each group's first item
-  int32_t* counters;       // the persistent launches' item counters, cleared by k_fractions
+  int32_t* counters;       // the persistent launches' item counters, cleared by k_fractions or k_spatial
 };
 
 struct ReduceArgs {
@@ -219,7 +219,8 @@ hipError_t launch_pass_k(const PassArgs& a, int mode, int learn_d, int vpl, int 
 // the same for items of one row of 64, 32 or 16 voxels (ls = 1, 2, 4; prism_split.h)
 template <int K>
 hipError_t launch_split_k(const PassArgs& a, int mode, int learn_d, int ls, int maxN, hipStream_t s);
-// blocks of that kernel that a compute unit holds at once
+// blocks of that kernel that a compute unit holds at once (ls = 0: of the fused pass with
+// four waves on each row)
 template <int K>
 int split_occupancy_k(int mode, int learn_d, int ls, int N);
 int split_blocks_per_cu(int K, int mode, int learn_d, int ls, int N);

@@ -95,9 +95,14 @@ __device__ __forceinline__ float pick(const float (&x)[M], int i) {
 
 // One row of 64 voxels: as many waves as the fused pass where they fit (a problem's blocks
 // should all be resident at once); shorter rows run where few waves share a SIMD, and
-// take the registers to keep several measurements in flight.
+// take the registers to keep several measurements in flight.  The Rician variants whose
+// 253-259 registers come down to the 256 of two waves for at most three spilled ones are
+// held to them (one iteration, 32768 voxels: K = 4, learned D, N = 96, 42.8 -> 38.8 us, K = 5, N =
+// 288, 67.4 -> 65.1, 16250 voxels 50.6 -> 46.3); the larger ones (K = 5, learned D; K = 6)
+// would spill 18 to 66 and run 5 to 14% slower.
 constexpr int split_min_waves(int K, int MODE, bool LD, int LS) {
-  return LS == 1 && MODE == kMSE ? pass_min_waves(K, MODE, LD, 1) : 1;
+  if (MODE == kNLL) return K == (LD ? 4 : 5) ? 2 : 1;
+  return LS == 1 ? pass_min_waves(K, MODE, LD, 1) : 1;
 }
 
 template <int K, int MODE, bool LD, int LS>
@@ -299,6 +304,13 @@ hipError_t launch_split_k(const PassArgs& a, int mode, int ld, int ls, int maxN,
 }
 template <int K>
 int split_occupancy_k(int mode, int ld, int ls, int N) {
+  if (ls == 0) {   // the fused pass with four waves on each row
+    const void* fn = mode == kMSE ? (ld ? (const void*)k_pass<K, kMSE, true, 1> : (const void*)k_pass<K, kMSE, false, 1>)
+                                  : (ld ? (const void*)k_pass<K, kNLL, true, 1> : (const void*)k_pass<K, kNLL, false, 1>);
+    int nb = 0;
+    const size_t lds = pass_lds_bytes(N, 3, acc_count(K, ld != 0), 1, mode == kNLL);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, lds) == hipSuccess ? nb : 0;
+  }
   return with_split_variant<K>(mode, ld, ls, N, [&](auto kernel, size_t lds) {
     int nb = 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, kBlock, lds) == hipSuccess ? nb : 0;

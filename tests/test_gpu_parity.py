@@ -283,6 +283,14 @@ def test_small_problems_in_rows_of_16_32_and_64_voxels(V, N, K, mode, learn_d):
         assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
 
 
+@pytest.mark.parametrize("V,N,K,mode,learn_d", [(32769, 7, 4, "nll", True), (61000, 5, 4, "nll", True),
+                                                (61000, 9, 2, "nll", False), (49153, 6, 5, "nll", False)])
+def test_rows_of_64_voxels_in_two_rounds(V, N, K, mode, learn_d):
+    """Problems whose rows of 64 are more blocks than the device holds at once, where the
+    fused pass would need two rounds as well (the shortest is one past a full round)."""
+    test_small_problems_in_rows_of_16_32_and_64_voxels(V, N, K, mode, learn_d)
+
+
 @pytest.mark.parametrize("order", ["sorted", "interleaved", "all_different", "one_b", "b0_only_groups"])
 @pytest.mark.parametrize("N,mode,learn_d,launch", [(3, "mse", False, None), (41, "nll", True, dict(vox_per_lane=2, n_split=1)),
                                                    (50, "mse", False, dict(vox_per_lane=1, n_split=2)),
