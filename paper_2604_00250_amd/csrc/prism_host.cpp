@@ -347,6 +347,33 @@ std::vector<std::pair<int, int>> staggered_cut(const prism_problem* h, const pri
   return cut;
 }
 
+// The kernels give XCD x the x-th contiguous run of a launch's items (xcd_item), which keeps
+// the neighbours of a large group in one L2.  Items sorted by falling cost would give the
+// first XCD all the work and the last one the crumbs; where the largest run is more than a
+// tenth above the mean they are dealt to the XCDs in turn instead, as the dispatcher deals
+// blocks (one launch per variant, 512 mixed patches of up to 24^3: 934 -> 890 us, 500 of up
+// to 10^3: 209 -> 199).
+template <typename F>
+void deal_items(std::vector<ItemDev>& items, F&& cost) {
+  constexpr size_t kXcd = 8;
+  const size_t n = items.size(), q = n / kXcd, r = n % kXcd;
+  if (q == 0) return;
+  int64_t most = 0, total = 0;
+  for (size_t x = 0, i = 0; x < kXcd; ++x) {
+    int64_t run = 0;
+    for (size_t e = i + q + (x < r ? 1 : 0); i < e; ++i) run += cost(items[i]);
+    most = std::max(most, run);
+    total += run;
+  }
+  if (most * (int64_t)kXcd * 10 <= total * 11) return;
+  std::vector<ItemDev> dealt(n);
+  for (size_t b = 0; b < n; ++b) {
+    const size_t x = b % kXcd;
+    dealt[x * q + std::min(x, r) + b / kXcd] = items[b];
+  }
+  items.swap(dealt);
+}
+
 // Work items, launch buckets and reduction tiles for the current launch shape.
 int plan(prism_problem* h) {
   const prism_launch& L = h->launch;
@@ -422,6 +449,7 @@ int plan(prism_problem* h) {
       }
       if (!keep_order)
         std::stable_sort(bi.begin(), bi.end(), [&](const ItemDev& a, const ItemDev& c) { return cost(a) > cost(c); });
+      if (!keep_order) deal_items(bi, cost);
       for (const ItemDev& it : bi) b.xsplit = std::max(b.xsplit, xsplit_of(it.n_split));
       ordered.insert(ordered.end(), bi.begin(), bi.end());
       b.item_count = (int)bi.size();

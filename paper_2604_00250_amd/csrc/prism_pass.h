@@ -32,8 +32,7 @@ static_assert(kTile % kPf == 0, "tile must be a multiple of the prefetch depth")
 
 // Waves per SIMD that the register allocation of the fused pass must allow.
 // MSE with fixed diffusivities and at most three fibres, one voxel per lane:
-// four (128 registers; the measurement loop stays free of spills, the few
-// spills are in the per-voxel prologue and epilogue), scheduling one
+// four (128 registers; the K = 3 kernel takes 115), scheduling one
 // measurement at a time.  Otherwise three for the variants that fit 168
 // registers without spilling (one voxel per lane, at most two fibres, or three
 // with fixed diffusivities), letting the scheduler interleave two measurements
