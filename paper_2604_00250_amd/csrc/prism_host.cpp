@@ -1235,11 +1235,14 @@ int32_t prism_loss_grad_noalloc(const prism_problem* h, const float* y, const fl
                                 float* grad_cal, uint32_t* status, void* stream) {
   if (!h) return fail(PRISM_E_INVALID, "handle is NULL");
   const size_t need = workspace_without_dirs(h);
-  if (need > kStaticScratchBytes)
+  size_t most = kStaticScratchBytes;
+  for (const GroupDev& g : h->groups)
+    if (group_launch(h, g).n_split == 0) most = kStaticScratchBytes + kStaticCutBytes;
+  if (need > most)
     return fail(PRISM_E_WORKSPACE,
                 "the problem needs %zu bytes of workspace; the static workspace of "
                 "prism_loss_grad_noalloc holds %zu (use prism_loss_grad with a caller workspace)",
-                need, kStaticScratchBytes);
+                need, most);
   hipError_t e = hipSuccess;
   void* ws = static_scratch(h->device, &e);
   if (!ws) return hip_fail(e, "static workspace of the problem's device");
