@@ -985,7 +985,7 @@ const char* prism_build_id(void) { return PRISM_SOURCE_HASH; }
 // only writes the gradient, needs no room for it).
 static size_t workspace_without_dirs(const prism_problem* h) {
   return align256(h->ws_rec * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
-         align256(h->groups.size() * 3 * sizeof(double)) +
+         align256(h->groups.size() * kCalSums * sizeof(double)) +
          512;  // + the persistent launches' item counters, the step's StepInfo
 }
 
@@ -1079,7 +1079,7 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   char* ws = (char*)workspace;
   const size_t o_float = align256(h->ws_rec * sizeof(double));
   const size_t o_calsq = o_float + align256(h->ws_float * sizeof(float));
-  const size_t o_counter = o_calsq + align256(h->groups.size() * 3 * sizeof(double));
+  const size_t o_counter = o_calsq + align256(h->groups.size() * kCalSums * sizeof(double));
   double* rec = (double*)ws;
   float* wsp = (float*)(ws + o_float);
   double* calsq = (double*)(ws + o_calsq);

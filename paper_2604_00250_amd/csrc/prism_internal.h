@@ -96,6 +96,10 @@ struct TileDev {
 constexpr int kReduceRowsFrom = 1500;  // more records than this: summed in runs first
 constexpr int kReduceRun = 64;
 
+// per group, left in the workspace by the fused pass for the reduction: the sums of squares
+// of alpha, beta and bias, and log sigma, all as they are before the reduction updates them
+constexpr int kCalSums = 4;
+
 // What the fused iteration's reductions need of the step counter, left in the workspace
 // by the fused pass, so that the reduction may advance the counter
 struct StepInfo {
@@ -146,8 +150,7 @@ struct PassArgs {
   const int32_t* step;
   float lr, b1, b2, eps;
   StepInfo* info;          // left by the first item's block (nullptr: not needed)
-  double* calsq;           // [n_groups][3] sums of squares of alpha, beta, bias, left by the block
-                           // of each group's first item
+  double* calsq;           // [n_groups][kCalSums], left by the block of each group's first item
   int32_t* counters;       // the persistent launches' item counters, cleared by k_fractions or k_spatial
 };
 
@@ -178,7 +181,7 @@ struct ReduceArgs {
   int32_t* step;           // fused iteration: advanced by k_reduce (nullptr: not here)
   const StepInfo* info;    // fused iteration: Adam's factors and the iteration's index
   float lr, b1, b2, eps;
-  const double* calsq;     // [n_groups][3] of the groups that have items (the cal prior's loss)
+  const double* calsq;     // [n_groups][kCalSums] of the groups that have items (the loss's cal terms)
   // loss-history ring [hist_len][n_groups][terms] (or nullptr): the loss rows also go
   // to slot (iteration's index) mod hist_len; the index is info's, else hist_step[0]
   double* hist;

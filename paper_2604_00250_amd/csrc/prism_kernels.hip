@@ -443,8 +443,10 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
       sq[2][tid >> 6] = sw;
     }
   }
-  // read before any thread of this block updates the calibration vector in place
-  const float sigma_log = cal[nb + 2 * N];
+  // log sigma before the iteration: from the pass, since the block of another tile may
+  // update theta_cal's while this one runs; an empty group's one block reads it before the
+  // barrier that its own update follows
+  const double sigma_log = empty ? (double)cal[nb + 2 * N] : R.calsq[kCalSums * t.group + 3];
   __syncthreads();
   auto total = [&](int f) { return empty ? 0.0 : part[f * T]; };   // field t.f0 + f
   const double M = g.V;
@@ -486,7 +488,7 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
   if (t.f0 == 0 && tid == 0) {
     // loss terms from fields 0-7 (every tile holds at least eight fields)
     const double data = g.mode == kMSE ? total(kRecData) * (double)g.invM
-                                       : total(kRecData) + 2.0 * (double)sigma_log * (double)N * M;
+                                       : total(kRecData) + 2.0 * sigma_log * (double)N * M;
     const double sp = total(kRecSpatial) * (double)R.model.lam_sp * g.invM;
     const double rp = total(kRecRep) * (double)R.model.lam_rep * g.invM;
     const double sa = total(kRecSparse) * (double)R.model.lam_sparse * g.invM;
@@ -500,7 +502,7 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
         if (!empty) {
-          q[i] = R.calsq[3 * t.group + i];
+          q[i] = R.calsq[kCalSums * t.group + i];
         } else {
           q[i] = 0.0;
           for (int w = 0; w < nt / 64; ++w) q[i] += sq[i][w];

@@ -822,9 +822,10 @@ __device__ __forceinline__ void chain_rule(const PassArgs& A, const GroupDev& g,
   }
 }
 
-// The squares of a group's calibration parameters, before anything changes them: one
-// wave of the block of the group's first item, a fixed order.
-__device__ __forceinline__ void calibration_squares(const PassArgs& A, const GroupDev& g, int group, int lane) {
+// The squares of a group's calibration parameters and its log sigma, before anything
+// changes them (k_reduce's blocks update the parameters in place, each the entries of its
+// own tile): one wave of the block of the group's first item, a fixed order.
+__device__ __forceinline__ void calibration_sums(const PassArgs& A, const GroupDev& g, int group, int lane) {
   const float* cal = A.th_cal + g.cal_off;
   double s[3] = {0.0, 0.0, 0.0};
   for (int i = lane; i < g.n_bias; i += 64) s[2] += (double)cal[i] * cal[i];
@@ -835,8 +836,9 @@ __device__ __forceinline__ void calibration_squares(const PassArgs& A, const Gro
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const double t = wave_sum_f64(s[i]);
-    if (lane == 0) A.calsq[3 * group + i] = t;
+    if (lane == 0) A.calsq[kCalSums * group + i] = t;
   }
+  if (lane == 0) A.calsq[kCalSums * group + 3] = (double)cal[g.n_bias + 2 * g.N];
 }
 
 // statically sized LDS of the fused pass (one instance per kernel, shared by the
@@ -880,7 +882,7 @@ __device__ __forceinline__ void pass_item(const PassArgs* Ap, const float4* __re
     adam_factors(A.step, A.lr, A.b1, A.b2, sh.adam_sc[0], sh.adam_sc[1]);
     if (it.first && A.info) *A.info = StepInfo{sh.adam_sc[0], sh.adam_sc[1], A.step[0]};
   }
-  if (it.rec == 0 && wave == 3) calibration_squares(A, g, it.group, lane);
+  if (it.rec == 0 && wave == 3) calibration_sums(A, g, it.group, lane);
   __syncthreads();
 
   const int n_groups = (N + kPf - 1) / kPf;

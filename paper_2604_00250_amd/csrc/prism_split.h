@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kBlock, split_min_waves(K, MODE, LD, LS)) void k_sp
     adam_factors(A.step, A.lr, A.b1, A.b2, adam_sc[0], adam_sc[1]);
     if (it.first && A.info) *A.info = StepInfo{adam_sc[0], adam_sc[1], A.step[0]};
   }
-  if (it.rec == 0 && wave == 3) calibration_squares(A, g, it.group, lane);
+  if (it.rec == 0 && wave == 3) calibration_sums(A, g, it.group, lane);
   Vox<K, LD> xs[1];
   Vox<K, LD>& x = xs[0];
   Derived D;

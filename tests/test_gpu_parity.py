@@ -12,7 +12,7 @@ import pytest
 import oracle as O
 from paper_2604_00250_amd import inputs as I
 
-from gpu_helpers import (assert_parity, masked_group, merged_grad, run_gpu, run_oracle, say,
+from gpu_helpers import (LOSS_RTOL, assert_parity, masked_group, merged_grad, run_gpu, run_oracle, say,
                          theta32, with_theta)
 
 pytestmark = pytest.mark.gpu
@@ -247,6 +247,50 @@ def test_record_reduction_at_the_edges_of_its_tiles(n_items):
     g = with_theta(g, I.perturb_theta(I.init_theta(V, 1, acq.n, 10, rng), rng))
     r = _check_groups(f"{n_items} items", [g], launch=dict(vox_per_lane=1, n_split=4, item_vox=64))
     assert r["prob"].plan_info()["items"] == n_items
+
+
+@pytest.mark.parametrize("n_items", [32, 33, 257, 1501])
+def test_rician_loss_of_the_fused_iteration_is_at_the_sigma_before_it(n_items):
+    """Up to 32 items one block of the reduction has both the loss and sigma's update;
+    above they are in two.  Loss rows, history and every updated value are those of the
+    gradient call and the separate Adam step, bit for bit, and the first loss the oracle's
+    at the parameters before the step (the step moves the loss by more than 100 times the
+    bound)."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    V = 64 * n_items - 5
+    shape = (5, -(-V // 500), 100)
+    mask = np.zeros(5 * shape[1] * 100, dtype=bool)
+    mask[:V] = True
+    rng = np.random.default_rng(n_items)
+    bval = np.array([0.0, 0.0, 1.0, 1.0, 2.0, 2.0, 3.0])
+    acq = I.Acquisition(bval=bval, bvec=I.uniform_sphere(bval.size, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=1, mode="nll", bias="poly2", neighbourhood=0,
+                priors=("rep", "sparse", "cal"))
+    g.y = rng.uniform(0.1, 1.0, size=(acq.n, V)).astype(np.float32)
+    g = with_theta(g, I.perturb_theta(I.init_theta(V, 1, acq.n, 10, rng, sigma_init=0.1), rng))
+    states = []
+    for fused in (True, False):
+        prob = Problem([g], launch=dict(vox_per_lane=1, n_split=4, item_vox=64))
+        st = DeviceState(prob, ys=[g.y], thetas=[g.theta])
+        hist = torch.zeros((2, 1, len(O.TERMS)), dtype=torch.float64, device=st.device)
+        rows = []
+        for _ in range(2):
+            st.iteration(lr=1e-2, history=hist) if fused else st.iteration_unfused(lr=1e-2)
+            torch.cuda.synchronize()
+            rows.append(st.loss.clone())
+        states.append((st, rows, hist))
+    (a, rows_a, hist), (b, rows_b, _) = states
+    assert a.prob.plan_info()["items"] == n_items
+    for t in range(2):
+        assert torch.equal(rows_a[t], rows_b[t]) and torch.equal(hist[t], rows_a[t]), t
+    for name in ("params", "m", "v", "step"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    out, _, _ = run_oracle(g, g.theta)
+    it = O.TERMS.index("total")
+    got = float(rows_a[0][0, it])
+    assert abs(got - out["total"]) <= LOSS_RTOL * abs(out["total"])
+    assert 2e-2 * acq.n * V > 100 * LOSS_RTOL * abs(out["total"])
 
 
 @pytest.mark.parametrize("V,N", [(1, 1), (15, 3), (16, 17), (17, 33), (4095, 7), (4097, 31), (8190, 16), (8193, 40),
