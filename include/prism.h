@@ -285,8 +285,11 @@ int32_t prism_loss_grad(const prism_problem* h, const float* y, const float* the
  * that own no device buffers).  The workspace is a static device array of
  * PRISM_NOALLOC_WORKSPACE_BYTES per GPU inside the library, held from the
  * library's load until the process ends; its address is looked up once per
- * device by prism_problem_create.  Problems whose prism_workspace_bytes
- * exceeds that size are rejected with PRISM_E_WORKSPACE (nothing is queued).
+ * device by prism_problem_create.  Problems that need more are rejected with
+ * PRISM_E_WORKSPACE (nothing is queued); what a problem needs here is its
+ * prism_workspace_bytes, less the copy of the directions that it counts for
+ * prism_iteration_adam alone (12 K bytes per voxel of a group with the
+ * continuity prior and a neighbourhood).
  * Calls on one GPU share that GPU's array (it keeps the last call's contents;
  * nothing in it needs clearing between calls): two calls that may overlap on
  * one GPU, on different streams or from different threads, race and give

@@ -266,9 +266,13 @@ int group_split(const prism_problem* h, const prism_launch& L, const GroupDev& g
   return 0;
 }
 
+// Whether a group's items are cut by the planner, their split chosen per item.
+bool automatic_cut(const prism_launch& L) { return L.n_split == 0 && L.item_vox == 0; }
+
 // Voxels per work item of a group under its launch shape.  total: voxel_cost summed
-// over the problem.
-int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total) {
+// over the problem.  by_count: the automatic cut gives every group items of one size
+// instead of one cost (about six blocks per compute unit, whole chunks).
+int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total, bool by_count) {
   const int vpl = L.vox_per_lane;
   const int ls = group_split(h, L, g);
   if (ls > 0) return 64 / ls;
@@ -279,6 +283,11 @@ int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev
     // best (brain-shaped volume, K = 3: 256-voxel items run the fused pass
     // 2.4% faster than 512-voxel ones)
     return 64 * vpl * (4 / L.n_split);
+  }
+  if (by_count) {
+    const int64_t per = (h->n_vox + 256 * 6 - 1) / (256 * 6);
+    return (int)std::max<int64_t>(base_chunk, std::min<int64_t>((per + base_chunk - 1) / base_chunk * base_chunk,
+                                                                8 * base_chunk));
   }
   // split chosen per item: each block that the device holds at once (about two per
   // compute unit for the mixed launches) gets about three items' worth of work, by
@@ -291,6 +300,41 @@ int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev
   if (per < 2 * base_chunk / 4) return base_chunk / 4;   // one row, four waves on it
   if (per < base_chunk) return base_chunk / 2;
   return (int)std::min<int64_t>(per / base_chunk * base_chunk, 8 * base_chunk);
+}
+
+// The workspace of a pass that writes the gradient, its item records holding `fields`
+// float64 values; prism_iteration_adam's copy of the directions for the continuity prior
+// follows it (the allocation-free entry point, which only writes the gradient, needs no
+// room for it).
+size_t workspace_for(const prism_problem* h, size_t fields) {
+  return align256(fields * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
+         align256(h->groups.size() * kCalSums * sizeof(double)) +
+         512;  // + the persistent launches' item counters, the step's StepInfo
+}
+size_t workspace_without_dirs(const prism_problem* h) { return workspace_for(h, h->ws_rec); }
+
+// The automatic cut is by cost, except where its up to four times as many records would
+// cost a problem the allocation-free entry point, whose static workspace serves the
+// problems that fit it cut by count and reduced in two stages (64 records to a partial
+// sum): those are cut by count where they do not fit by cost (700 groups of 256 voxels,
+// N = 1024: 49.3 MiB by count, 60.6 with the partial sums, 82.5 by cost).  Problems beyond
+// that keep the faster cut (512 patches of up to 24^3: 74.2 MiB by cost).
+bool cut_by_count(const prism_problem* h, int64_t total) {
+  bool automatic = false;
+  for (const GroupDev& g : h->groups) automatic = automatic || automatic_cut(group_launch(h, g));
+  if (!automatic) return false;
+  size_t by_cost = 0, by_count = 0;
+  for (const GroupDev& g : h->groups) {
+    const prism_launch L = group_launch(h, g);
+    auto items = [&](bool count) {
+      const int64_t nv = group_item_vox(h, L, g, total, count);
+      return (size_t)((g.V + nv - 1) / nv);
+    };
+    by_cost += items(false) * g.rec_stride;
+    const size_t n = items(true), columns = (size_t)(g.rec_stride + 63) / 64 * 64;
+    by_count += n * g.rec_stride + (n + 63) / 64 * columns;
+  }
+  return workspace_for(h, by_cost) > kStaticScratchBytes && workspace_for(h, by_count) <= kStaticScratchBytes;
 }
 
 // Staggered first round (prism_launch.stagger).  All blocks of a launch of equal
@@ -383,10 +427,11 @@ int plan(prism_problem* h) {
   std::vector<std::vector<int>> per_group(h->groups.size());
   int64_t total = 0;
   for (const GroupDev& g : h->groups) total += g.V * voxel_cost(g);
+  const bool by_count = cut_by_count(h, total);
   for (size_t gi = 0; gi < h->groups.size(); ++gi) {
     GroupDev& g = h->groups[gi];
     const prism_launch Lg = group_launch(h, g);
-    const int item_vox = group_item_vox(h, Lg, g, total);
+    const int item_vox = group_item_vox(h, Lg, g, total, by_count);
     const int ls = group_split(h, Lg, g);
     if (ls == 0 && Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
       return fail(PRISM_E_INVALID, "group %d: item_vox %d is not a multiple of the block chunk %d", (int)gi,
@@ -980,15 +1025,6 @@ int32_t prism_problem_plan_info(const prism_problem* h, int32_t* n_items, int32_
 
 const char* prism_build_id(void) { return PRISM_SOURCE_HASH; }
 
-// The workspace of a pass that writes the gradient; prism_iteration_adam's copy of the
-// directions for the continuity prior follows it (the allocation-free entry point, which
-// only writes the gradient, needs no room for it).
-static size_t workspace_without_dirs(const prism_problem* h) {
-  return align256(h->ws_rec * sizeof(double)) + align256(h->ws_float * sizeof(float)) +
-         align256(h->groups.size() * kCalSums * sizeof(double)) +
-         512;  // + the persistent launches' item counters, the step's StepInfo
-}
-
 int32_t prism_workspace_bytes(const prism_problem* h, size_t* bytes) {
   if (!h || !bytes) return fail(PRISM_E_INVALID, "NULL argument");
   *bytes = workspace_without_dirs(h) + align256(h->ws_dirs * sizeof(float));
@@ -1235,14 +1271,11 @@ int32_t prism_loss_grad_noalloc(const prism_problem* h, const float* y, const fl
                                 float* grad_cal, uint32_t* status, void* stream) {
   if (!h) return fail(PRISM_E_INVALID, "handle is NULL");
   const size_t need = workspace_without_dirs(h);
-  size_t most = kStaticScratchBytes;
-  for (const GroupDev& g : h->groups)
-    if (group_launch(h, g).n_split == 0) most = kStaticScratchBytes + kStaticCutBytes;
-  if (need > most)
+  if (need > kStaticScratchBytes)
     return fail(PRISM_E_WORKSPACE,
                 "the problem needs %zu bytes of workspace; the static workspace of "
                 "prism_loss_grad_noalloc holds %zu (use prism_loss_grad with a caller workspace)",
-                need, most);
+                need, kStaticScratchBytes);
   hipError_t e = hipSuccess;
   void* ws = static_scratch(h->device, &e);
   if (!ws) return hip_fail(e, "static workspace of the problem's device");

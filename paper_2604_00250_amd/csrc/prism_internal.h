@@ -246,10 +246,6 @@ hipError_t launch_rician_terms(const float* z, float* li, float* omr, float* q, 
 // per device) and the address found by that set-up (nullptr and the error if
 // it failed or has not run).
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
-// ... and room beside it for the records of problems whose items are cut by cost: up to
-// twice the items of a cut into equal voxel counts (4.2 MB more for 512 patches), which
-// must not count against the limit
-constexpr size_t kStaticCutBytes = (size_t)16 << 20;
 hipError_t static_scratch_setup(int device);
 void* static_scratch(int device, hipError_t* err);
 

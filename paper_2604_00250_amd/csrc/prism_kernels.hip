@@ -773,7 +773,7 @@ hipError_t launch_rician_terms(const float* z, float* li, float* omr, float* q, 
 // In host code `scratch` names a host-side stand-in, not the device array:
 // only the address hipGetSymbolAddress returns for the current device may be
 // passed to kernels or copies.
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticCutBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;

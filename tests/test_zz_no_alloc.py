@@ -65,3 +65,39 @@ def test_noalloc_refuses_a_problem_beyond_the_static_workspace():
     assert rc == L.PRISM_E_WORKSPACE and "static workspace" in msg
     torch.cuda.synchronize()
     assert not torch.any(buf)  # nothing was queued
+
+
+@pytest.mark.parametrize("n_groups,fits", [(700, True), (800, False)])
+def test_finer_items_neither_cost_nor_gain_the_static_workspace(n_groups, fits):
+    """Groups of 256 voxels, N = 1024, in the automatic cut: 700 of them fit the static
+    workspace as one item each (49.3 MiB) but not as four (82.5), so they run, bit for bit
+    as with a caller's workspace; 800 never fitted (69 MiB with the partial sums that the
+    coarser cut was reduced through) and are refused."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(n_groups)
+    b = np.full(1024, 2.0)
+    b[::9] = 0.0
+    acq = I.Acquisition(bval=b, bvec=I.uniform_sphere(1024, rng))
+    shape = (16, 16, 1)
+    groups = [I.Group(shape=shape, mask=np.ones(shape, dtype=bool), acq=acq, K=1, mode="mse", priors=("spatial",))
+              for _ in range(n_groups)]
+    prob = Problem(groups)
+    say(f"[noalloc] {n_groups} groups: workspace {prob.workspace_bytes()} B, plan {prob.plan_info()}")
+    assert (prob.workspace_bytes() <= L.NOALLOC_WORKSPACE_BYTES) == fits
+    st = DeviceState(prob)
+    st.params[:st.n_micro].normal_()
+    st.y.uniform_(0.1, 1.0)
+    pm, pc, gm, gc = st.ptrs()
+    loss, grad, status = torch.zeros_like(st.loss), torch.zeros_like(st.grad), torch.zeros_like(st.status)
+    rc = L.lib().prism_loss_grad_noalloc(prob.handle, st.y.data_ptr(), pm, pc, loss.data_ptr(), grad.data_ptr(),
+                                         grad.data_ptr() + 4 * st.n_micro, status.data_ptr(), st._s())
+    assert rc == (0 if fits else L.PRISM_E_WORKSPACE), L.lib().prism_last_error().decode()
+    torch.cuda.synchronize()
+    if fits:
+        st.loss_grad()
+        torch.cuda.synchronize()
+        assert torch.equal(loss, st.loss) and torch.equal(grad, st.grad)
+        assert int(status.item()) == 0 and float(loss[:, -1].min()) > 0.0
+    else:
+        assert not torch.any(loss) and not torch.any(grad)
