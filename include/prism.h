@@ -256,8 +256,11 @@ int32_t prism_problem_plan_info(const prism_problem* h, int32_t* n_items, int32_
  * tied to one build. */
 const char* prism_build_id(void);
 
-/* Bytes of device workspace prism_loss_grad needs (per-item partial sums and
- * the Eq. 7 residual weights).  The caller allocates it; contents need not be
+/* Bytes of device workspace that prism_loss_grad and prism_iteration_adam need
+ * (per-item partial sums and the Eq. 7 residual weights; for the iteration's
+ * part alone a copy of the raw directions, 12 K bytes per voxel, of groups with
+ * the continuity prior and a neighbourhood: prism_loss_grad also takes a
+ * workspace without it).  The caller allocates it; contents need not be
  * initialised and are overwritten by every call. */
 int32_t prism_workspace_bytes(const prism_problem* h, size_t* bytes);
 
@@ -271,7 +274,8 @@ int32_t prism_synthesize(const prism_problem* h, const float* theta_micro,
  *   theta_micro [n_micro], theta_cal [n_cal]  parameters (device)
  *   loss        [n_groups][PRISM_LOSS_TERMS] float64 (device, overwritten)
  *   grad_micro  [n_micro], grad_cal [n_cal] (device, overwritten)
- *   workspace   >= prism_workspace_bytes (device), workspace_bytes its size
+ *   workspace   >= prism_workspace_bytes (device; the iteration's copy of the
+ *               directions not needed), workspace_bytes its size
  *   status      device uint32; PRISM_ST_* bits are OR-ed in, never cleared
  * Asynchronous on `stream`; allocates nothing; graph-capturable. */
 int32_t prism_loss_grad(const prism_problem* h, const float* y, const float* theta_micro,
@@ -288,8 +292,7 @@ int32_t prism_loss_grad(const prism_problem* h, const float* y, const float* the
  * device by prism_problem_create.  Problems that need more are rejected with
  * PRISM_E_WORKSPACE (nothing is queued); what a problem needs here is its
  * prism_workspace_bytes, less the copy of the directions that it counts for
- * prism_iteration_adam alone (12 K bytes per voxel of a group with the
- * continuity prior and a neighbourhood).
+ * prism_iteration_adam alone.
  * Calls on one GPU share that GPU's array (it keeps the last call's contents;
  * nothing in it needs clearing between calls): two calls that may overlap on
  * one GPU, on different streams or from different threads, race and give

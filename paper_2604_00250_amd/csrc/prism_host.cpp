@@ -1237,15 +1237,16 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   return PRISM_OK;
 }
 
+// dirs: the call also needs the copy of the directions (prism_iteration_adam)
 int check_pass_args(const prism_problem* h, const float* y, const float* theta_micro, const float* theta_cal,
                     const double* loss, const float* grad_micro, const float* grad_cal, const void* workspace,
-                    size_t workspace_bytes, const uint32_t* status) {
+                    size_t workspace_bytes, const uint32_t* status, bool dirs) {
   if (!h) return fail(PRISM_E_INVALID, "handle is NULL");
   if ((h->n_y && !y) || (h->n_micro && (!theta_micro || !grad_micro)) || !theta_cal || !grad_cal ||
       !loss || !status)
     return fail(PRISM_E_INVALID, "NULL device pointer");
-  size_t need = 0;
-  prism_workspace_bytes(h, &need);
+  size_t need = workspace_without_dirs(h);
+  if (dirs) prism_workspace_bytes(h, &need);
   if (need > 0 && !workspace) return fail(PRISM_E_INVALID, "workspace is NULL");
   if (workspace_bytes < need)
     return fail(PRISM_E_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
@@ -1258,7 +1259,7 @@ int32_t prism_loss_grad(const prism_problem* h, const float* y, const float* the
                         const float* theta_cal, double* loss, float* grad_micro, float* grad_cal,
                         void* workspace, size_t workspace_bytes, uint32_t* status, void* stream) {
   int rc = check_pass_args(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace,
-                           workspace_bytes, status);
+                           workspace_bytes, status, false);
   if (rc != PRISM_OK) return rc;
   return run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace, status,
                   (hipStream_t)stream, nullptr);
@@ -1280,7 +1281,7 @@ int32_t prism_loss_grad_noalloc(const prism_problem* h, const float* y, const fl
   void* ws = static_scratch(h->device, &e);
   if (!ws) return hip_fail(e, "static workspace of the problem's device");
   int rc = check_pass_args(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, ws,
-                           SIZE_MAX, status);
+                           kStaticScratchBytes, status, false);
   if (rc != PRISM_OK) return rc;
   return run_pass(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, ws, status,
                   (hipStream_t)stream, nullptr);
@@ -1293,7 +1294,7 @@ int32_t prism_iteration_adam(const prism_problem* h, const float* y, float* thet
                              int32_t history_len, float* grad_micro, float* grad_cal, void* workspace,
                              size_t workspace_bytes, uint32_t* status, void* stream) {
   int rc = check_pass_args(h, y, theta_micro, theta_cal, loss, grad_micro, grad_cal, workspace,
-                           workspace_bytes, status);
+                           workspace_bytes, status, true);
   if (rc != PRISM_OK) return rc;
   if (loss_history && history_len < 1) return fail(PRISM_E_INVALID, "history_len must be >= 1");
   if (!step || (h->n_micro && (!m_micro || !v_micro)) || (update_cal && (!m_cal || !v_cal)))

@@ -230,6 +230,36 @@ def test_workspace_smaller_than_required_is_rejected():
     torch.cuda.synchronize()
 
 
+def test_only_the_iteration_needs_the_copy_of_the_directions():
+    """A continuity problem's gradient call takes a workspace without it, with the same
+    bits and nothing written past its end; one byte less is refused, and so is the
+    iteration."""
+    import torch
+    from paper_2604_00250_amd import _lib as L
+    g = masked_group(shape=(7, 6, 5), K=3, mode="mse", seed=13, acq_kind="single33", priors=("spatial", "continuity"))
+    r = run_gpu([g], [g.theta])
+    st = r["state"]
+    full = st.prob.workspace_bytes()
+    need = full - -(-12 * 3 * g.n_vox // 256) * 256
+    loss, grad = st.loss.clone(), st.grad.clone()
+    st.ws.fill_(0xA5)
+    st.loss.zero_()
+    st.grad.zero_()
+    pm, pc, gm, gc = st.ptrs()
+
+    def call(n):
+        return L.lib().prism_loss_grad(st.prob.handle, st.y.data_ptr(), pm, pc, st.loss.data_ptr(), gm, gc,
+                                       st.ws.data_ptr(), n, st.status.data_ptr(), st._s())
+    assert call(need - 1) == L.PRISM_E_WORKSPACE
+    assert call(need) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(st.loss, loss) and torch.equal(st.grad, grad)
+    assert bool((st.ws[need:full] == 0xA5).all())
+    st.ws_bytes = full - 1
+    with pytest.raises(L.PrismError):
+        st.iteration(lr=1e-2)
+
+
 @pytest.mark.parametrize("n_items", [1, 32, 33, 256, 257, 1500, 1501])
 def test_record_reduction_at_the_edges_of_its_tiles(n_items):
     """Items of 64 voxels, the last one short: the reduction's wide and narrow tiles,
