@@ -62,6 +62,12 @@ struct Bucket {
   int grid;    // persistent launch: blocks
 };
 
+// one launch of the forward model
+struct SynthLaunch {
+  int K, mode, learn_d, maxN;
+  int item_begin, item_count;  // in d_items
+};
+
 constexpr int kSideStreams = 3;  // with the caller's: the four hardware queues a process gets
 
 }  // namespace
@@ -75,6 +81,7 @@ struct prism_problem {
   std::vector<GroupDev> groups;
   std::vector<ItemDev> items;
   std::vector<Bucket> buckets;
+  std::vector<SynthLaunch> synth;
   std::vector<TileDev> tiles;
   std::vector<int32_t> tri_groups;
   std::vector<int32_t> acq_off;
@@ -87,7 +94,7 @@ struct prism_problem {
   size_t ws_rec = 0, ws_float = 0, ws_dirs = 0;  // element counts
   // device tables
   GroupDev* d_groups = nullptr;
-  ItemDev* d_items = nullptr;
+  ItemDev* d_items = nullptr;               // `items`, then the forward model's where its order differs
   TileDev* d_tiles = nullptr;
   int32_t* d_perm = nullptr;
   RunDev* d_runs = nullptr;
@@ -418,6 +425,46 @@ void deal_items(std::vector<ItemDev>& items, F&& cost) {
   items.swap(dealt);
 }
 
+// The forward model's launches: one per fibre count and learned diffusivities, which is
+// all that its kernel is compiled for.  items are in the passes' order, sorted by cost over
+// every variant in a persistent plan (a launch at each change of variant in that order
+// would be 203 for 512 mixed patches, 6.4 ms where five take 0.51); where that order has a variant in
+// several pieces, its items follow all of `items` again, largest first and dealt to the
+// XCDs, and the launch reads them there.  A variant that is one piece keeps its order.
+std::vector<SynthLaunch> synth_launches(const prism_problem* h, std::vector<ItemDev>& items) {
+  const int n = (int)items.size();
+  std::vector<SynthLaunch> out;
+  std::vector<int> pieces;
+  const GroupDev* last = nullptr;
+  for (int i = 0; i < n; ++i) {
+    const GroupDev& g = h->groups[items[i].group];
+    size_t s = 0;
+    while (s < out.size() && (out[s].K != g.K || out[s].learn_d != g.learn_d)) ++s;
+    if (s == out.size()) {
+      out.push_back(SynthLaunch{g.K, g.mode, g.learn_d, 0, i, 0});
+      pieces.push_back(0);
+    }
+    if (!last || last->K != g.K || last->learn_d != g.learn_d) ++pieces[s];
+    last = &g;
+    out[s].maxN = std::max(out[s].maxN, g.N);
+    ++out[s].item_count;
+  }
+  auto cost = [&](const ItemDev& a) { return (int64_t)a.nv * h->groups[a.group].N; };
+  for (size_t s = 0; s < out.size(); ++s) {
+    if (pieces[s] == 1) continue;
+    std::vector<ItemDev> own;
+    for (int i = 0; i < n; ++i) {
+      const GroupDev& g = h->groups[items[i].group];
+      if (g.K == out[s].K && g.learn_d == out[s].learn_d) own.push_back(items[i]);
+    }
+    std::stable_sort(own.begin(), own.end(), [&](const ItemDev& a, const ItemDev& c) { return cost(a) > cost(c); });
+    deal_items(own, cost);
+    out[s].item_begin = (int)items.size();
+    items.insert(items.end(), own.begin(), own.end());
+  }
+  return out;
+}
+
 // Work items, launch buckets and reduction tiles for the current launch shape.
 int plan(prism_problem* h) {
   const prism_launch& L = h->launch;
@@ -593,7 +640,8 @@ int plan(prism_problem* h) {
       h->persistent_grid += b.grid;
     }
   }
-  hipError_t e = upload(&h->d_items, h->items);
+  h->synth = synth_launches(h, ordered);
+  hipError_t e = upload(&h->d_items, ordered);
   if (e == hipSuccess) e = upload(&h->d_tiles, h->tiles);
   if (e == hipSuccess) {
     (void)hipFree(h->d_groups);
@@ -1064,23 +1112,11 @@ int32_t prism_synthesize(const prism_problem* h, const float* theta_micro, const
   PassArgs a = pass_args(h, nullptr, theta_micro, theta_cal, nullptr, nullptr, nullptr, nullptr);
   a.synth_only = 1;
   a.yhat = yhat;
-  // one synthesis launch per item of the plan's variant groups (the synthesis
-  // kernel has no persistent form: it runs item by item per variant)
-  for (size_t i = 0; i < h->items.size();) {
-    const GroupDev& g0 = h->groups[h->items[i].group];
-    size_t j = i;
-    int maxN = 0;
-    while (j < h->items.size()) {
-      const GroupDev& g = h->groups[h->items[j].group];
-      if (g.K != g0.K || g.learn_d != g0.learn_d) break;
-      maxN = std::max(maxN, g.N);
-      ++j;
-    }
-    a.item_base = (int)i;
-    a.n_items = (int)(j - i);
-    hipError_t e = launch_pass_maxn(a, g0.K, g0.mode, g0.learn_d, 1, maxN, s);
+  for (const SynthLaunch& l : h->synth) {
+    a.item_base = l.item_begin;
+    a.n_items = l.item_count;
+    hipError_t e = launch_pass_maxn(a, l.K, l.mode, l.learn_d, 1, l.maxN, s);
     if (e != hipSuccess) return hip_fail(e, "synthesis launch");
-    i = j;
   }
   return PRISM_OK;
 }

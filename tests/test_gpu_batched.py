@@ -225,3 +225,33 @@ def test_full_batched_problem_in_its_tuned_persistent_plan():
         g = w.groups[i]
         assert_parity(f"full-batched/{i} V={g.n_vox} K={g.K} N={g.acq.n} {g.mode}", loss[i],
                       merged_grad(gm[i], gc[i]), out, grad)
+
+
+@pytest.mark.parametrize("persistent", [1, 0])
+def test_forward_model_of_a_mixed_batch_is_one_launch_per_variant(persistent):
+    """The forward model's kernel is compiled per fibre count (and learned
+    diffusivities) alone: a batch takes one launch for each, whatever the order of the
+    plan's items (counted in a captured graph), and every group's signal is the oracle's."""
+    import ctypes
+    import oracle as O
+    import torch
+    from gpu_helpers import oracle_problem, theta32
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    w = _workload()
+    prob = Problem(w.groups, launch=dict(vox_per_lane=1, n_split=0, item_vox=0, persistent=persistent))
+    st = DeviceState(prob, ys=[g.y for g in w.groups], thetas=[g.theta for g in w.groups])
+    out = torch.full((st.n_y,), float("nan"), device=st.device)
+    st.synthesize(out)
+    torch.cuda.synchronize()
+    for g, got in zip(w.groups, prob.unpack_y(out.cpu().numpy())):
+        ref = O.synthesize(oracle_problem(g), theta32(g.theta))
+        assert float(np.abs(got - ref).max() / np.abs(ref).max()) < 1e-5
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        st.synthesize(out)
+    hip = ctypes.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    say(f"[batched forward] persistent={persistent} launches {n.value}")
+    assert n.value == len({(g.K, bool(g.learn_diffusivity)) for g in w.groups})
