@@ -236,7 +236,6 @@ int64_t loop_cost(const GroupDev& g) {
 int64_t fixed_cost(const GroupDev& g) { return 450 * g.K + 300; }
 int64_t voxel_cost(const GroupDev& g) { return loop_cost(g) + fixed_cost(g); }
 
-
 // Lane groups per wave (1, 2 or 4) with which a group's items run in the split kernel
 // (prism_split.h: one row of 64, 32 or 16 voxels per block, the measurements shared by 4,
 // 8 or 16 slots), or 0: the fused pass's kernels.  It serves the four-way split of items
@@ -254,23 +253,50 @@ int64_t voxel_cost(const GroupDev& g) { return loop_cost(g) + fixed_cost(g); }
 // Rows of 64 also serve up to two rounds of blocks where the fused pass would take two as
 // well: K = 4, NLL, learned D, N = 96, 42768 voxels 60.9 -> 55.1 us, 64000 71.4 -> 64.7; K = 2, NLL,
 // N = 33, 64000 voxels 44.4 -> 38.7, but 42768, one round of the fused pass, 31.1 -> 34.7.
-int group_split(const prism_problem* h, const prism_launch& L, const GroupDev& g) {
+//
+// Asked once per group of a plan: the problem's blocks are counted once and the occupancies
+// kept per variant and N, so that a plan of many groups stays linear in them (4096 groups:
+// 40 ms without).
+struct SplitRows {
+  const prism_problem* h;
+  int cus = 0;
+  int64_t blocks[3] = {0, 0, 0};  // of the whole problem in rows of 16, 32 and 64 voxels
+  struct Known {
+    int K, mode, learn_d, N, rows;
+  };
+  std::vector<Known> known;
+  explicit SplitRows(const prism_problem* p) : h(p) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) cus = 0;
+    for (const GroupDev& q : h->groups)
+      for (int i = 0; i < 3; ++i) blocks[i] += (q.V + (16 << i) - 1) / (16 << i);
+  }
+  int resident(const GroupDev& g);
+  int of(const prism_launch& L, const GroupDev& g);
+};
+
+// The rows that the automatic cut takes for a variant and N.
+int SplitRows::resident(const GroupDev& g) {
+  for (const Known& k : known)
+    if (k.K == g.K && k.mode == g.mode && k.learn_d == g.learn_d && k.N == g.N) return k.rows;
+  int rows = 0;
+  for (int i = 0; i < 3 && rows == 0; ++i) {
+    const int ls = 4 >> i;
+    const int most = ls == 2 && loop_cost(g) < 4 * fixed_cost(g) ? 1 : 4 / ls;
+    const int64_t per_cu = std::min(most, split_blocks_per_cu(g.K, g.mode, g.learn_d, ls, g.N));
+    if (blocks[i] <= cus * per_cu ||
+        (ls == 1 && blocks[i] <= 2 * cus * per_cu &&
+         blocks[i] > (int64_t)cus * split_blocks_per_cu(g.K, g.mode, g.learn_d, 0, g.N)))
+      rows = ls;
+  }
+  known.push_back(Known{g.K, g.mode, g.learn_d, g.N, rows});
+  return rows;
+}
+
+int SplitRows::of(const prism_launch& L, const GroupDev& g) {
   if (L.persistent || L.vox_per_lane != 1 || L.n_split != 4 || (L.item_vox != 0 && L.item_vox != 64)) return 0;
   if ((int64_t)g.V * std::max(g.N, g.P) * 4 >= ((int64_t)1 << 31)) return 0;
   if (L.item_vox == 64) return 1;
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) return 0;
-  for (int ls = 4; ls >= 1; ls /= 2) {
-    int64_t blocks = 0;
-    for (const GroupDev& q : h->groups) blocks += (q.V + 64 / ls - 1) / (64 / ls);
-    const int most = ls == 2 && loop_cost(g) < 4 * fixed_cost(g) ? 1 : 4 / ls;
-    const int64_t per_cu = std::min(most, split_blocks_per_cu(g.K, g.mode, g.learn_d, ls, g.N));
-    if (blocks <= cus * per_cu) return ls;
-    if (ls == 1 && blocks <= 2 * cus * per_cu &&
-        blocks > (int64_t)cus * split_blocks_per_cu(g.K, g.mode, g.learn_d, 0, g.N))
-      return ls;
-  }
-  return 0;
+  return cus > 0 ? resident(g) : 0;
 }
 
 // Whether a group's items are cut by the planner, their split chosen per item.
@@ -278,10 +304,10 @@ bool automatic_cut(const prism_launch& L) { return L.n_split == 0 && L.item_vox 
 
 // Voxels per work item of a group under its launch shape.  total: voxel_cost summed
 // over the problem.  by_count: the automatic cut gives every group items of one size
-// instead of one cost (about six blocks per compute unit, whole chunks).
-int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total, bool by_count) {
+// instead of one cost (about six blocks per compute unit, whole chunks).  ls: SplitRows.
+int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total, bool by_count,
+                   int ls) {
   const int vpl = L.vox_per_lane;
-  const int ls = group_split(h, L, g);
   if (ls > 0) return 64 / ls;
   const int base_chunk = 64 * vpl * 4;  // voxels per block chunk with n_split = 1
   if (L.item_vox > 0) return L.item_vox;
@@ -326,15 +352,16 @@ size_t workspace_without_dirs(const prism_problem* h) { return workspace_for(h, 
 // sum): those are cut by count where they do not fit by cost (700 groups of 256 voxels,
 // N = 1024: 49.3 MiB by count, 60.6 with the partial sums, 82.5 by cost).  Problems beyond
 // that keep the faster cut (512 patches of up to 24^3: 74.2 MiB by cost).
-bool cut_by_count(const prism_problem* h, int64_t total) {
+bool cut_by_count(const prism_problem* h, int64_t total, SplitRows& split) {
   bool automatic = false;
   for (const GroupDev& g : h->groups) automatic = automatic || automatic_cut(group_launch(h, g));
   if (!automatic) return false;
   size_t by_cost = 0, by_count = 0;
   for (const GroupDev& g : h->groups) {
     const prism_launch L = group_launch(h, g);
+    const int ls = split.of(L, g);
     auto items = [&](bool count) {
-      const int64_t nv = group_item_vox(h, L, g, total, count);
+      const int64_t nv = group_item_vox(h, L, g, total, count, ls);
       return (size_t)((g.V + nv - 1) / nv);
     };
     by_cost += items(false) * g.rec_stride;
@@ -428,9 +455,9 @@ void deal_items(std::vector<ItemDev>& items, F&& cost) {
 // The forward model's launches: one per fibre count and learned diffusivities, which is
 // all that its kernel is compiled for.  items are in the passes' order, sorted by cost over
 // every variant in a persistent plan (a launch at each change of variant in that order
-// would be 203 for 512 mixed patches, 6.4 ms where five take 0.51); where that order has a variant in
-// several pieces, its items follow all of `items` again, largest first and dealt to the
-// XCDs, and the launch reads them there.  A variant that is one piece keeps its order.
+// would be 203 for 512 mixed patches, 6.4 ms where five take 0.51); where that order has a
+// variant in several pieces, its items follow all of `items` again, largest first and dealt
+// to the XCDs, and the launch reads them there.  A variant that is one piece keeps its order.
 std::vector<SynthLaunch> synth_launches(const prism_problem* h, std::vector<ItemDev>& items) {
   const int n = (int)items.size();
   std::vector<SynthLaunch> out;
@@ -474,12 +501,13 @@ int plan(prism_problem* h) {
   std::vector<std::vector<int>> per_group(h->groups.size());
   int64_t total = 0;
   for (const GroupDev& g : h->groups) total += g.V * voxel_cost(g);
-  const bool by_count = cut_by_count(h, total);
+  SplitRows split(h);
+  const bool by_count = cut_by_count(h, total, split);
   for (size_t gi = 0; gi < h->groups.size(); ++gi) {
     GroupDev& g = h->groups[gi];
     const prism_launch Lg = group_launch(h, g);
-    const int item_vox = group_item_vox(h, Lg, g, total, by_count);
-    const int ls = group_split(h, Lg, g);
+    const int ls = split.of(Lg, g);
+    const int item_vox = group_item_vox(h, Lg, g, total, by_count, ls);
     if (ls == 0 && Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
       return fail(PRISM_E_INVALID, "group %d: item_vox %d is not a multiple of the block chunk %d", (int)gi,
                   item_vox, 64 * Lg.vox_per_lane * (4 / Lg.n_split));

@@ -255,3 +255,26 @@ def test_forward_model_of_a_mixed_batch_is_one_launch_per_variant(persistent):
     assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
     say(f"[batched forward] persistent={persistent} launches {n.value}")
     assert n.value == len({(g.K, bool(g.learn_diffusivity)) for g in w.groups})
+
+
+def test_planning_stays_linear_in_the_groups():
+    """The rule for the split kernel's rows looks at the whole problem's blocks and the
+    device's occupancy; asked for each of 4096 groups it must not look again each time.
+    (It did: 50 times the plan without it; counted once, about twice.)"""
+    import time
+    from paper_2604_00250_amd.problem import Problem
+    acq = I.Acquisition(bval=np.ones(8), bvec=I.uniform_sphere(8, np.random.default_rng(0)))
+    mask = np.ones((4, 4, 4), dtype=bool)
+    prob = Problem([I.Group(shape=mask.shape, mask=mask, acq=acq, K=1 + i % 5, mode="nll" if i % 2 else "mse",
+                            priors=("rep",)) for i in range(4096)])
+
+    def best(n_split):
+        times = []
+        for _ in range(5):
+            t = time.perf_counter()
+            prob.tune(vox_per_lane=1, n_split=n_split)
+            times.append(time.perf_counter() - t)
+        return min(times)
+    plain, ruled = best(2), best(4)
+    say(f"[plan] 4096 groups: n_split 2 {plain * 1e3:.2f} ms, n_split 4 {ruled * 1e3:.2f} ms")
+    assert ruled < 8 * plain
