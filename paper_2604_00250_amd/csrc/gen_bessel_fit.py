@@ -13,7 +13,9 @@ both: with delta = z - z0,
 of every octave from 1/8 up to Z_SPLIT, so the interval of an argument is a
 shift of its float32 bits and |delta| <= z/16: the correction to c1 is small and
 1 - R keeps the accuracy of c1, of delta (z - z0 is exact: the two lie within a
-factor of two) and of one rounding.  c1 .. c6 come from a weighted least squares
+factor of two) and of one rounding.  On [0, 1/8) (z0 = 0, c0 = 0, c1 = 1)
+-log I0e is summed as z + z (z s): in c1 + z s and its product with z both
+roundings would count.  c1 .. c6 come from a weighted least squares
 fit of 1 - R; z0 is chosen among the float32 numbers near the interval's middle
 so that both c0 and c1 are float32 numbers to about a thousandth of an ulp
 (accurate tables), which leaves the final rounding as the main error.
@@ -128,7 +130,10 @@ def evaluate_f32(z, table=None):
     t = _fma32(d, ds, f32(s + s))
     omr = _fma32(d, t, c[1])
     nli = _fma32(d, _fma32(d, s, c[1]), c[0])
-    q = f32(f32(z + z) * omr)
+    nli = np.where(bits < _bits(Z_FIRST) - 1, _fma32(f32(z * s), z, z), nli)
+    # q = 2 z (1 - R) from 1 - R and what its rounding left
+    z2 = f32(z + z)
+    q = _fma32(z2, omr, f32(z2 * _fma32(d, t, f32(c[1] - omr))))
     # from the split up
     big = z >= f32(Z_SPLIT)
     zl = np.where(big, z, f32(1.0))
@@ -139,7 +144,7 @@ def evaluate_f32(z, table=None):
     lg = f32(np.log2(zl.astype(np.float64)))                      # v_log_f32
     li = np.where(big, _fma32(f32(-HALF_LN2), lg, _fma32(f32(0.125), iz, f32(-HALF_LOG_2PI))), -nli)
     omr = np.where(big, _fma32(e, r, r), omr)
-    q = np.where(big, f32(f32(1.0) + e), q)
+    q = np.where(big, _fma32(f32(0.25), iz, f32(1.0)), q)
     return li, omr, q
 
 
@@ -196,6 +201,7 @@ def main(out=None):
         f.write(f"static constexpr int kBesselShift = {SHIFT};          // entry = (clamped float32 bits - kBesselBitsLo) >> this\n")
         f.write(f"static constexpr int kBesselBitsLo = 0x{BITS_LO:08x};\n")
         f.write(f"static constexpr int kBesselBitsHi = 0x{BITS_HI:08x};\n")
+        f.write(f"static constexpr float kBesselFirst = {Z_FIRST!r}f;\n")
         f.write(f"static constexpr float kBesselSplit = {Z_SPLIT!r}f;\n")
         f.write(f"static constexpr float kHalfLog2Pi = {float(f32(HALF_LOG_2PI))!r}f;\n")
         f.write(f"static constexpr float kHalfLn2 = {float(f32(HALF_LN2))!r}f;\n")

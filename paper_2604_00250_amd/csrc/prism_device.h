@@ -304,16 +304,25 @@ __device__ __forceinline__ void stage_bessel(float4* tab) {
   }
 }
 
-// nli = -log I0e(z) = z - log I0(z) and omr = 1 - I1(z)/I0(z), each within 1e-7
-// relative over [0, 1e5] (host emulation of this algorithm; the tests measure the
-// device).  omr is the derivative of nli, so one polynomial in d = z - z0 of the
-// argument's interval gives both:
+// nli = -log I0e(z) = z - log I0(z) and omr = 1 - I1(z)/I0(z), each within 6.4e-8
+// relative over [0, 65536) and 9.1e-8 above (host emulation of this algorithm; the tests
+// measure the device).  omr is the derivative of nli, so one polynomial in d = z - z0 of
+// the argument's interval gives both:
 //   nli = c0 + d (c1 + d s),  omr = c1 + d (2 s + d s'),  s = c2 + ... + c6 d^4.
-// z >= kBesselSplit (any size; z NaN gives NaN): the large-argument expansions.
-__device__ __forceinline__ void rician_terms(float z, const float4* tab, float& nli, float& omr) {
+// Two kinds of argument are outside kBesselFirst <= z < kBesselSplit, in one branch that
+// few waves take.  Below it (entry 0: z0 = 0, c0 = 0, c1 = 1) nli is summed as
+// z + z (z s), since both roundings of z (1 + z s) would count (8.9e-8 relative against
+// 6.0e-8; 512 mixed patches 789 -> 800 us with it); from kBesselSplit up (any size; z NaN
+// gives NaN): the large-argument expansions.
+// Q: q = 2 z omr too, from omr and what its own rounding left, so that one rounding counts.
+// (The pass takes this product unrounded into a multiply-add.)
+template <bool Q = false>
+__device__ __forceinline__ void rician_terms(float z, const float4* tab, float& nli, float& omr, float* q = nullptr) {
   // the interval from the float's bits, clamped into the table (negative bits, a
-  // negative NaN, too)
-  const int bits = min(max(__builtin_bit_cast(int, z), kBesselBitsLo), kBesselBitsHi);
+  // negative NaN, too; below kBesselFirst to the last number of entry 0), so that one
+  // comparison tells both kinds
+  constexpr int kLo = __builtin_bit_cast(int, kBesselFirst) - 1;
+  const int zb = __builtin_bit_cast(int, z), bits = min(max(zb, kLo), kBesselBitsHi);
   const int i = (bits - kBesselBitsLo) >> kBesselShift;
   const float4 a = tab[i], b = tab[kBesselEntries + i];
   const float d = z - a.x;
@@ -323,14 +332,20 @@ __device__ __forceinline__ void rician_terms(float z, const float4* tab, float& 
   s = fmaf(s, d, b.x);
   ds = fmaf(ds, d, s);
   s = fmaf(s, d, a.w);
-  omr = fmaf(d, fmaf(d, ds, s + s), a.z);
+  const float t = fmaf(d, ds, s + s);
+  omr = fmaf(d, t, a.z);
   nli = fmaf(d, fmaf(d, s, a.z), a.y);
-  if (z >= kBesselSplit) {
-    const float iz0 = rcp(z);
-    const float iz = fmaf(fmaf(-z, iz0, 1.0f), iz0, iz0);
-    const float r = 0.5f * iz;
-    omr = fmaf(0.25f * iz, r, r);
-    nli = fmaf(kHalfLn2, lg2(z), fmaf(-0.125f, iz, kHalfLog2Pi));
+  if (Q) *q = fmaf(z + z, omr, (z + z) * fmaf(d, t, a.z - omr));
+  if (bits != zb) {
+    nli = fmaf(z * s, z, z);
+    if (z >= kBesselSplit) {
+      const float iz0 = rcp(z);
+      const float iz = fmaf(fmaf(-z, iz0, 1.0f), iz0, iz0);
+      const float r = 0.5f * iz;
+      omr = fmaf(0.25f * iz, r, r);
+      nli = fmaf(kHalfLn2, lg2(z), fmaf(-0.125f, iz, kHalfLog2Pi));
+      if (Q) *q = fmaf(0.25f, iz, 1.0f);
+    }
   }
 }
 

@@ -750,11 +750,11 @@ __global__ __launch_bounds__(256) void k_rician_terms(const float* z, float* li,
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const float zi = z[i];
-    float nli, o;
-    rician_terms(zi, bes, nli, o);
+    float nli, o, qi;
+    rician_terms<true>(zi, bes, nli, o, &qi);
     li[i] = -nli;
     omr[i] = o;
-    q[i] = (zi + zi) * o;
+    q[i] = qi;
   }
 }
 

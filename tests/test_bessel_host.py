@@ -46,6 +46,22 @@ def test_float32_algorithm_meets_the_bound_on_0_to_1e5(gen, emulated):
     assert e_q.max() <= BOUND
 
 
+def one_rounding(gen, z, vals):
+    """The two results whose only error of note is one rounding (2^-24): log I0e below the
+    table's second interval (its z s term, at most z/4 of it, adds three roundings more) and
+    q (what 1 - R's rounding left is |d| t, at most a tenth of it, with two roundings)."""
+    e_li, _, e_q = gen.relative_errors(z, vals)
+    small, table = (z >= np.float32(1e-4)) & (z < np.float32(gen.Z_FIRST)), (z > 0) & (z < np.float32(gen.Z_SPLIT))
+    return e_li[small].max() * 2.0 ** 24 / 1.1, e_q[table].max() * 2.0 ** 24 / 1.25
+
+
+def test_small_arguments_and_q_take_one_rounding(gen, emulated):
+    z, vals = emulated
+    li, q = one_rounding(gen, z, vals)
+    print(f"share of the bound: log I0e on [1e-4, 1/8) {li:.3f}, q on (0, 65536) {q:.3f}")
+    assert li <= 1.0 and q <= 1.0
+
+
 def test_both_branches_are_exercised_and_continuous_at_the_split(gen, emulated):
     z, (li, omr, q) = emulated
     split = np.float32(gen.Z_SPLIT)

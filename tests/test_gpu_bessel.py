@@ -47,6 +47,27 @@ def test_device_special_functions_meet_the_bound():
         assert e.max() <= 2e-7
 
 
+def test_device_small_arguments_and_q_take_one_rounding():
+    """The two results whose only error of note is one rounding, 2^-24: log I0e on
+    [1e-4, 1/8) within 1.1 of it and q on (0, 65536) within 1.25 (what adds to it is a
+    rounding or two of a term at most z/4, respectively a tenth, of the result)."""
+    import torch
+    from paper_2604_00250_amd import _lib as L
+    gen = _gen()
+    z = gen.test_grid()
+    z = z[(z > 0) & (z < np.float32(65536.0))]
+    dev = torch.from_numpy(z).cuda()
+    out = [torch.empty_like(dev) for _ in range(3)]
+    L.check(L.lib().prism_rician_terms(dev.data_ptr(), out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(),
+                                       z.size, None))
+    torch.cuda.synchronize()
+    e_li, _, e_q = gen.relative_errors(z, [o.cpu().numpy() for o in out])
+    small = (z >= np.float32(1e-4)) & (z < np.float32(0.125))
+    say(f"[bessel] log I0e on [1e-4, 1/8) {e_li[small].max():.3e}, q on (0, 65536) {e_q.max():.3e}")
+    assert e_li[small].max() <= 1.1 * 2.0 ** -24
+    assert e_q.max() <= 1.25 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("z", [[0.125, 0.12499999], [65535.996, 65536.0, 65536.01], [1e6, 1e12, 1e30, 1e37], [0.0]])
 def test_device_special_functions_at_the_ends_of_the_table_and_beyond(z):
     """Both sides of the table's first interval and of its end, and arguments far
