@@ -302,11 +302,27 @@ int SplitRows::of(const prism_launch& L, const GroupDev& g) {
 // Whether a group's items are cut by the planner, their split chosen per item.
 bool automatic_cut(const prism_launch& L) { return L.n_split == 0 && L.item_vox == 0; }
 
-// Voxels per work item of a group under its launch shape.  total: voxel_cost summed
-// over the problem.  by_count: the automatic cut gives every group items of one size
-// instead of one cost (about six blocks per compute unit, whole chunks).  ls: SplitRows.
-int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, int64_t total, bool by_count,
-                   int ls) {
+// What the automatic cut looks at of the whole problem, once per plan.
+struct WholeProblem {
+  int64_t cost = 0;  // voxel_cost of every voxel
+  explicit WholeProblem(const prism_problem* h) {
+    for (const GroupDev& g : h->groups) {
+      cost += g.V * voxel_cost(g);
+      for (int i = 0; i < 3; ++i) rows[i] += ((int64_t)g.V + (64 << i) - 1) / (64 << i);
+    }
+  }
+  // items of one row of 64 vpl voxels per ns waves (ns = 4, 2) in all
+  int64_t blocks(int vpl, int ns) const { return rows[(vpl == 2) + (ns == 2)]; }
+
+ private:
+  int64_t rows[3] = {0, 0, 0};  // of 64, 128 and 256 voxels
+};
+
+// Voxels per work item of a group under its launch shape.  by_count: the automatic cut
+// gives every group items of one size instead of one cost (about six blocks per compute
+// unit, whole chunks).  ls: SplitRows.
+int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev& g, const WholeProblem& cut,
+                   bool by_count, int ls) {
   const int vpl = L.vox_per_lane;
   if (ls > 0) return 64 / ls;
   const int base_chunk = 64 * vpl * 4;  // voxels per block chunk with n_split = 1
@@ -328,10 +344,20 @@ int group_item_vox(const prism_problem* h, const prism_launch& L, const GroupDev
   // N = 33, K = 1 MSE group, and a launch is at least as long as its longest item.
   // (Items of equal voxel count, six blocks per compute unit: 512 mixed patches 959 us,
   // cut by cost 884 us.)
-  const int64_t target = total / (256 * 2 * 3);
+  const int64_t target = cut.cost / (256 * 2 * 3);
   const int64_t per = target / std::max<int64_t>(1, voxel_cost(g));
-  if (per < 2 * base_chunk / 4) return base_chunk / 4;   // one row, four waves on it
-  if (per < base_chunk) return base_chunk / 2;
+  // Items below a block chunk have two or four waves on each row, and every wave repeats
+  // the row's prologue: only where that costs the group at most a quarter more (many
+  // measurements), or where all blocks of the problem at that size are resident at once
+  // and the shorter chain counts.  (By cost alone 300 patches of up to 13^3, persistent, take
+  // 103.7 us at N = 32, K = 1, MSE, with this 56.3, and 90.1 and 52.5 at N = 18, K = 4; 512
+  // mixed patches 804 and 803.  A bound of 1.6 instead of 1.25: 74.3, 65.1 and 803.)
+  auto worth = [&](int ns) {
+    return 4 * (ns * fixed_cost(g) + loop_cost(g)) <= 5 * voxel_cost(g) || cut.blocks(vpl, ns) <= 256 * 2;
+  };
+  if (per < base_chunk / 2 && worth(4)) return base_chunk / 4;   // one row, four waves on it
+  if (per < base_chunk && worth(2)) return base_chunk / 2;
+  if (per < base_chunk) return base_chunk;
   return (int)std::min<int64_t>(per / base_chunk * base_chunk, 8 * base_chunk);
 }
 
@@ -352,7 +378,7 @@ size_t workspace_without_dirs(const prism_problem* h) { return workspace_for(h, 
 // sum): those are cut by count where they do not fit by cost (700 groups of 256 voxels,
 // N = 1024: 49.3 MiB by count, 60.6 with the partial sums, 82.5 by cost).  Problems beyond
 // that keep the faster cut (512 patches of up to 24^3: 74.2 MiB by cost).
-bool cut_by_count(const prism_problem* h, int64_t total, SplitRows& split) {
+bool cut_by_count(const prism_problem* h, const WholeProblem& cut, SplitRows& split) {
   bool automatic = false;
   for (const GroupDev& g : h->groups) automatic = automatic || automatic_cut(group_launch(h, g));
   if (!automatic) return false;
@@ -361,7 +387,7 @@ bool cut_by_count(const prism_problem* h, int64_t total, SplitRows& split) {
     const prism_launch L = group_launch(h, g);
     const int ls = split.of(L, g);
     auto items = [&](bool count) {
-      const int64_t nv = group_item_vox(h, L, g, total, count, ls);
+      const int64_t nv = group_item_vox(h, L, g, cut, count, ls);
       return (size_t)((g.V + nv - 1) / nv);
     };
     by_cost += items(false) * g.rec_stride;
@@ -499,15 +525,14 @@ int plan(prism_problem* h) {
   std::vector<int> item_vpl, item_ls;
   bool keep_order = false;  // a staggered cut is launched in its own order
   std::vector<std::vector<int>> per_group(h->groups.size());
-  int64_t total = 0;
-  for (const GroupDev& g : h->groups) total += g.V * voxel_cost(g);
+  const WholeProblem whole(h);
   SplitRows split(h);
-  const bool by_count = cut_by_count(h, total, split);
+  const bool by_count = cut_by_count(h, whole, split);
   for (size_t gi = 0; gi < h->groups.size(); ++gi) {
     GroupDev& g = h->groups[gi];
     const prism_launch Lg = group_launch(h, g);
     const int ls = split.of(Lg, g);
-    const int item_vox = group_item_vox(h, Lg, g, total, by_count, ls);
+    const int item_vox = group_item_vox(h, Lg, g, whole, by_count, ls);
     if (ls == 0 && Lg.n_split > 0 && item_vox % (64 * Lg.vox_per_lane * (4 / Lg.n_split)) != 0)
       return fail(PRISM_E_INVALID, "group %d: item_vox %d is not a multiple of the block chunk %d", (int)gi,
                   item_vox, 64 * Lg.vox_per_lane * (4 / Lg.n_split));

@@ -278,3 +278,29 @@ def test_planning_stays_linear_in_the_groups():
     plain, ruled = best(2), best(4)
     say(f"[plan] 4096 groups: n_split 2 {plain * 1e3:.2f} ms, n_split 4 {ruled * 1e3:.2f} ms")
     assert ruled < 8 * plain
+
+
+@pytest.mark.parametrize("n_groups,N,K,rows", [(160, 18, 4, 256), (160, 288, 3, 64), (40, 18, 4, 64)])
+def test_automatic_items_are_finer_than_a_block_only_where_that_pays(n_groups, N, K, rows):
+    """160 patches of 9^3 want items of less than a block's 256 voxels for an even share;
+    that repeats each row's prologue in the waves that share it, so with few measurements
+    (prologue and epilogue are half of the work at N = 18) they stay whole blocks and with
+    288 they do not, nor where all of them are resident at once.  Either cut matches the
+    oracle."""
+    acq = I.Acquisition(bval=np.where(np.arange(N) % 6 == 0, 0.0, 2.0),
+                        bvec=I.uniform_sphere(N, np.random.default_rng(N)))
+    mask = np.ones((9, 9, 9), dtype=bool)
+    rng = np.random.default_rng(n_groups + N)
+    groups = []
+    for i in range(n_groups):
+        g = I.Group(shape=mask.shape, mask=mask, acq=acq, K=K, mode="nll" if i % 2 else "mse", bias="poly2",
+                    priors=("spatial", "rep", "cal"))
+        g.y = rng.uniform(0.1, 1.0, size=(N, g.n_vox)).astype(np.float32)
+        g.theta = I.perturb_theta(I.init_theta(g.n_vox, K, N, 10, rng, sigma_init=0.1), rng, scale=0.3)
+        groups.append(g)
+    r = run_gpu(groups, [g.theta for g in groups], launch=dict(vox_per_lane=1, n_split=0, item_vox=0, persistent=1))
+    assert r["prob"].plan_info()["items"] == n_groups * -(-729 // rows)
+    assert r["status"] == 0
+    for i in (0, n_groups // 2, n_groups - 1):
+        out, grad, _ = run_oracle(groups[i], groups[i].theta)
+        assert_parity(f"cut {n_groups} N={N}/{i}", r["loss"][i], merged_grad(r["gmicro"][i], r["gcal"][i]), out, grad)
