@@ -56,19 +56,6 @@ __device__ __forceinline__ void store_row_f32(float* row, uint32_t nbytes, uint3
   __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(row, (short)0, (int)nbytes, 0x00020000);
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, off, 0, 0);
 }
-// VL = 1 or 2 consecutive floats of a row (4-byte aligned; all inside the row)
-template <int VL>
-__device__ __forceinline__ void store_row_vec(float* row, uint32_t nbytes, uint32_t off, const float (&x)[VL]) {
-  static_assert(VL == 1 || VL == 2, "one or two floats");
-  if constexpr (VL == 1) {
-    store_row_f32(row, nbytes, off, x[0]);
-  } else {
-    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-    const u2 t = {__builtin_bit_cast(uint32_t, x[0]), __builtin_bit_cast(uint32_t, x[1])};
-    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(row, (short)0, (int)nbytes, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b64(t, r, off, 0, 0);
-  }
-}
 __device__ __forceinline__ int32_t load_row_i32(const int32_t* row, uint32_t nbytes, uint32_t off) {
   __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int32_t*>(row), (short)0, (int)nbytes, 0x00020000);

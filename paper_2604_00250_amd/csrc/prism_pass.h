@@ -1130,52 +1130,16 @@ __device__ __forceinline__ float synth_pair(const Vox<K, LD>& x, const float4 a,
   return fmaf(c.x, S, c.y);
 }
 
-// One work item: lane l of a wave has the voxels VL l .. VL l + VL - 1 of the wave's row
-// of 64 VL, stored as one vector; the block's four waves take the item's rows, or with
-// fewer rows share each row, every wave with a part of the measurements.  The stores
-// bound it: a row of V floats starts anywhere in a cache line, so each wave's piece of a
-// row has a partial line at either end.  Items in runs per XCD (neighbouring pieces meet
-// in one L2: 323 -> 301 us on 753k voxels, N = 288, K = 3) and two voxels per lane (twice
-// the bytes per piece: 274 us) make fewer of them; four voxels per lane, 278 us.  Without
-// the stores the same kernel takes 224 us, the stores alone as one fill 126 us.
-template <int K, bool LD, int VL>
-__device__ __forceinline__ void synth_item(const PassArgs& A, const GroupDev& g, const ItemDev& it,
-                                           const float4* acq, bool& zero_dir) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int rows = it.nv <= 64 * VL ? 1 : (it.nv <= 128 * VL ? 2 : 4), WN = 4 / rows;
-  const int row = wave / WN, split = wave - row * WN;
-  const int nb = (g.N * split) / WN, ne = (g.N * (split + 1)) / WN;
-  const int64_t V = g.V;
-  const uint32_t rowb = (uint32_t)V * 4u;
-  for (int cb = 64 * VL * row; cb < it.nv; cb += 64 * VL * rows) {
-    const int lv = cb + lane * VL;
-    if (lv >= it.nv) continue;
-    const bool whole = lv + VL <= it.nv;
-    Vox<K, LD> x[VL];
-#pragma unroll
-    for (int j = 0; j < VL; ++j) {
-      Derived dv;
-      load_voxel<K, LD, false>(A, g, it.v0 + min(lv + j, it.nv - 1), x[j], dv, zero_dir);
-    }
-    const uint32_t off = (uint32_t)(it.v0 + lv) * 4u;
-    float* out = A.yhat + g.y_off + (int64_t)nb * V;
-#pragma unroll 4
-    for (int n = nb; n < ne; ++n, out += V) {
-      const float4 a = acq[3 * n], b = acq[3 * n + 1], c = acq[3 * n + 2];
-      float r[VL];
-#pragma unroll
-      for (int j = 0; j < VL; ++j) r[j] = synth_pair<K, LD>(x[j], a, b, c);
-      if (whole) {
-        store_row_vec<VL>(out, rowb, off, r);
-      } else {
-#pragma unroll
-        for (int j = 0; j < VL; ++j)
-          if (lv + j < it.nv) store_row_f32(out, rowb, off + 4u * j, r[j]);
-      }
-    }
-  }
-}
-
+// One work item, a voxel per lane: the block's four waves take the item's rows of 64, or
+// with fewer rows share each row, every wave with a part of the measurements.  Large
+// problems are bound by the stores: a row of V floats starts anywhere in a cache line, so
+// each wave's piece of a row has a partial line at either end; items in runs per XCD let
+// neighbouring pieces meet in one L2 (753k voxels, N = 288, K = 3: 327 -> 262 us; without
+// the stores 224, the stores alone as one fill 126).  Two voxels per lane and one vector
+// store for both make longer pieces but fewer waves and more registers (270 us there):
+// 749995 voxels, K = 3, N = 288 / 96 / 33 / 12 take 258 / 105 / 39.0 / 24.6 us this way and
+// 270 / 116 / 48.7 / 29.7 that way, 129595 voxels 52.7 / 22.8 / 11.6 / 8.3 and 55.6 / 26.0 /
+// 14.5 / 9.6.
 template <int K, bool LD>
 __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
   extern __shared__ float4 smem4[];
@@ -1184,13 +1148,23 @@ __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
   float4* acq = smem4;
   stage_acquisition(A, g, acq, false);
   __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int rows = it.nv <= 64 ? 1 : (it.nv <= 128 ? 2 : 4), WN = 4 / rows;
+  const int row = wave / WN, split = wave - row * WN;
+  const int nb = (g.N * split) / WN, ne = (g.N * (split + 1)) / WN;
+  const int64_t V = g.V;
+  const uint32_t rowb = (uint32_t)V * 4u;
   bool zero_dir = false;
-  // items of up to two rows (the cut of small and middling problems): one voxel per lane
-  // gives each row its own waves (128k voxels, N = 288: 26.3 us, two per lane 30.3)
-  if (it.nv > 128)
-    synth_item<K, LD, 2>(A, g, it, acq, zero_dir);
-  else
-    synth_item<K, LD, 1>(A, g, it, acq, zero_dir);
+  for (int lv = 64 * row + lane; lv < it.nv; lv += 64 * rows) {
+    Vox<K, LD> x;
+    Derived dv;
+    load_voxel<K, LD, false>(A, g, it.v0 + lv, x, dv, zero_dir);
+    const uint32_t off = (uint32_t)(it.v0 + lv) * 4u;
+    float* out = A.yhat + g.y_off + (int64_t)nb * V;
+#pragma unroll 4
+    for (int n = nb; n < ne; ++n, out += V)
+      store_row_f32(out, rowb, off, synth_pair<K, LD>(x, acq[3 * n], acq[3 * n + 1], acq[3 * n + 2]));
+  }
   if (zero_dir && A.status) atomicOr(A.status, (uint32_t)kStZeroDir);
 }
 

@@ -12,7 +12,7 @@ import pytest
 import oracle as O
 from paper_2604_00250_amd import inputs as I
 
-from gpu_helpers import (LOSS_RTOL, assert_parity, masked_group, merged_grad, run_gpu, run_oracle, say,
+from gpu_helpers import (LOSS_RTOL, assert_parity, masked_group, merged_grad, oracle_problem, run_gpu, run_oracle, say,
                          theta32, with_theta)
 
 pytestmark = pytest.mark.gpu
@@ -112,6 +112,31 @@ def test_empty_group_contributes_only_calibration_prior():
     assert np.allclose(r["gcal"][1]["alpha"], 0.02 * cal["alpha"], rtol=1e-5, atol=1e-9)
     out0, grad0, _ = run_oracle(g0, g0.theta)
     assert_parity("nonempty-beside-empty", r["loss"][0], merged_grad(r["gmicro"][0], r["gcal"][0]), out0, grad0)
+
+
+@pytest.mark.parametrize("V", [1, 63, 64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("N", [1, 3, 34])
+def test_forward_model_at_the_edges_of_its_rows(V, N):
+    """Items of one, two and four rows of 64 voxels, the last row short, with fewer and with
+    more measurements than the waves that share a row; nothing written past the last voxel."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(V + 1000 * N)
+    shape = (2, -(-V // 20), 10)
+    mask = np.zeros(20 * shape[1], dtype=bool)
+    mask[:V] = True
+    acq = I.Acquisition(bval=rng.integers(0, 4, size=N).astype(np.float64), bvec=I.uniform_sphere(N, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=2, mode="mse", bias="poly2")
+    g.theta = I.perturb_theta(I.init_theta(V, 2, N, 10, rng), rng, scale=0.3)
+    prob = Problem([g], launch=dict(vox_per_lane=1, n_split=1))
+    st = DeviceState(prob, thetas=[g.theta])
+    out = torch.full((st.n_y + 64,), -7.0, device=st.device)
+    st.synthesize(out)
+    torch.cuda.synchronize()
+    ref = O.synthesize(oracle_problem(g), theta32(g.theta))
+    got = out[:st.n_y].cpu().numpy().reshape(N, V)
+    assert np.abs(got - ref).max() < 2e-6 * np.abs(ref).max()
+    assert bool((out[st.n_y:] == -7.0).all())
 
 
 def test_synthesize_matches_oracle_forward():
