@@ -83,7 +83,8 @@ struct prism_problem {
   std::vector<Bucket> buckets;
   std::vector<SynthLaunch> synth;
   std::vector<TileDev> tiles;
-  std::vector<int32_t> tri_groups;
+  std::vector<int32_t> tri_groups;  // the first n_tri_wide: a block per control point, then a wave
+  int n_tri_wide = 0;
   std::vector<int32_t> acq_off;
   int n_tiles = 0;      // the first of `tiles`: k_reduce's; the rest: k_reduce_rows'
   int max_records = 0;  // most records of a group that k_reduce reads
@@ -984,6 +985,18 @@ int32_t prism_problem_create(prism_problem** out, const prism_group_desc* groups
     dc.mask = nullptr;
     h->desc.push_back(dc);
   }
+  // A control point of the bias grid sums about (2 (n_a - 1) / 7 + 1) positions per axis.  A
+  // wave takes 256 at a time, so a block is not needed for fewer, nor for up to four times
+  // that where the groups' blocks of four waves are more than the device holds at once:
+  // there one wave per point saves waves that find little to do (300 groups of up to 13^3,
+  // N = 26, K = 4, Rician: 248 -> 150 us per gradient).
+  auto wide = [&](int32_t gi) {
+    const GroupDev& g = h->groups[gi];
+    double at = 1.0;
+    for (int n : {g.nx, g.ny, g.nz}) at *= std::min<double>(n, 2.0 * (n - 1) / 7.0 + 1.0);
+    return at > (h->tri_groups.size() > 4 ? 1024.0 : 256.0);
+  };
+  h->n_tri_wide = (int)(std::stable_partition(h->tri_groups.begin(), h->tri_groups.end(), wide) - h->tri_groups.begin());
   h->n_vox = vox;
   h->n_micro = micro;
   h->n_cal = cal;
@@ -1298,6 +1311,7 @@ int run_pass(const prism_problem* h, const float* y, const float* theta_micro, c
   r.n_tiles = h->n_tiles;
   r.tri_groups = h->d_tri;
   r.n_tri = (int)h->tri_groups.size();
+  r.n_tri_wide = h->n_tri_wide;
   r.row_tiles = h->d_tiles + h->n_tiles;
   r.n_row_tiles = (int)h->tiles.size() - h->n_tiles;
   r.n_groups = (int)h->groups.size();

@@ -157,8 +157,9 @@ struct PassArgs {
 struct ReduceArgs {
   const GroupDev* groups;
   const TileDev* tiles;
-  const int32_t* tri_groups; // groups with voxels and a trilinear bias grid, 512 blocks each after the tiles
-  int32_t n_tri;
+  const int32_t* tri_groups; // groups with voxels and a trilinear bias grid: after the tiles 512 blocks for each
+                             // of the first n_tri_wide, then a wave for each of the others' 512 points
+  int32_t n_tri, n_tri_wide;
   const TileDev* row_tiles;  // of k_reduce_rows
   int32_t n_row_tiles;
   double* rec;

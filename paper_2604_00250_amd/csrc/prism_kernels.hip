@@ -285,11 +285,11 @@ __device__ __forceinline__ void cal_entry(const ReduceArgs& R, const GroupDev& g
 // ---------------------------------------------------------------------------
 // trilinear 8^3 log-bias gradient: dL/db(c) = sum_x w_c(x) dL/dlogB(x)
 // ---------------------------------------------------------------------------
-// Control point cp of one group by one block of k_reduce's launch (it reads none of what
-// the tiles write: as a launch after them it took 12 us more for 30k voxels).  red: one
-// value per wave.
-__device__ void bias_tri_point(const ReduceArgs& R, const GroupDev& g, int cp, double* red) {
-  const int nt = blockDim.x;
+// Control point cp of one group by thread t of nt in k_reduce's launch (it reads none of
+// what the tiles write: as a launch after them it took 12 us more for 30k voxels): a whole
+// block, or for small boxes one wave (see prism_host.cpp).  red: one value per wave.
+template <bool WAVE>
+__device__ void bias_tri_point(const ReduceArgs& R, const GroupDev& g, int cp, int t, int nt, double* red) {
   const int cidx[3] = {cp >> 6, (cp >> 3) & 7, cp & 7};
   const int nn[3] = {g.nx, g.ny, g.nz};
   int lo[3], hi[3];
@@ -311,7 +311,7 @@ __device__ void bias_tri_point(const ReduceArgs& R, const GroupDev& g, int cp, d
     const int32_t* grid = R.grid + g.grid_off;
     const float* glb = R.wsp + g.glb_off;
     // four positions per round: their voxels, then those voxels' adjoints
-    for (int64_t q0 = threadIdx.x; q0 < tot; q0 += 4 * nt) {
+    for (int64_t q0 = t; q0 < tot; q0 += 4 * nt) {
       float w[4];
       int v[4];
 #pragma unroll
@@ -337,11 +337,16 @@ __device__ void bias_tri_point(const ReduceArgs& R, const GroupDev& g, int cp, d
     }
   }
   acc = wave_sum_f64(acc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < nt / 64; ++i) s += red[i];
+  if (!WAVE) {
+    if ((t & 63) == 0) red[t >> 6] = acc;
+    __syncthreads();
+  }
+  if (t == 0) {
+    double s = acc;
+    if (!WAVE) {
+      s = 0.0;
+      for (int i = 0; i < nt / 64; ++i) s += red[i];
+    }
     const float* cal = R.th_cal + g.cal_off;
     const bool cal_on = (g.priors & kPriorCal) != 0;
     cal_entry(R, g, cp, (float)(s + (cal_on ? 2.0 * (double)R.model.lam_bias * cal[cp] : 0.0)));
@@ -390,8 +395,14 @@ __global__ __launch_bounds__(kReduceWide) void k_reduce(ReduceArgs R) {
   __shared__ double part[kReduceWide];
   __shared__ double sq[3][kReduceWide / 64];
   if ((int)blockIdx.x >= R.n_tiles) {
-    const int q = blockIdx.x - R.n_tiles;
-    bias_tri_point(R, R.groups[R.tri_groups[q / 512]], q % 512, sq[0]);
+    const int q = blockIdx.x - R.n_tiles, past = q - 512 * R.n_tri_wide;
+    if (past < 0) {
+      bias_tri_point<false>(R, R.groups[R.tri_groups[q / 512]], q % 512, threadIdx.x, blockDim.x, sq[0]);
+    } else {
+      const int per = blockDim.x >> 6, blocks = 512 / per;   // points of a block, blocks of a group
+      bias_tri_point<true>(R, R.groups[R.tri_groups[R.n_tri_wide + past / blocks]],
+                           past % blocks * per + (threadIdx.x >> 6), threadIdx.x & 63, 64, nullptr);
+    }
     return;
   }
   const TileDev t = R.tiles[blockIdx.x];
@@ -684,7 +695,8 @@ hipError_t launch_reduce(const ReduceArgs& a, int max_records, hipStream_t s) {
   // narrow tiles of up to 256 records: one round of loads with 32 threads a column; of
   // more: 128 threads a column
   const int block = max_records > 256 ? kReduceWide : kReduceBlock;
-  hipLaunchKernelGGL(k_reduce, dim3(a.n_tiles + 512 * a.n_tri), dim3(block), 0, s, a);
+  const int tri = 512 * a.n_tri_wide + 512 / (block / 64) * (a.n_tri - a.n_tri_wide);
+  hipLaunchKernelGGL(k_reduce, dim3(a.n_tiles + tri), dim3(block), 0, s, a);
   return hipGetLastError();
 }
 

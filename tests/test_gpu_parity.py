@@ -114,6 +114,37 @@ def test_empty_group_contributes_only_calibration_prior():
     assert_parity("nonempty-beside-empty", r["loss"][0], merged_grad(r["gmicro"][0], r["gcal"][0]), out0, grad0)
 
 
+@pytest.mark.parametrize("edges", [[(5, 1, 9)], [(17, 17, 17)], [(23, 22, 21)], [(33, 34, 35)],
+                                   [(23, 22, 21), (9, 9, 9), (33, 34, 35), (12, 1, 1), (21, 21, 21), (8, 7, 30)]])
+@pytest.mark.parametrize("nll", [False, True])
+def test_bias_grid_gradient_by_waves_and_by_blocks(edges, nll):
+    """Control points of the 8^3 grid whose boxes a wave takes in one round, in several
+    (more than four such groups) and whose boxes take a block, one axis a single voxel;
+    the fused iteration bit for bit the separate steps."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(len(edges) + edges[0][0])
+    acq = I.Acquisition(bval=np.array([0.0, 1.0, 2.0, 2.0]), bvec=I.uniform_sphere(4, rng))
+    groups = []
+    for e in edges:
+        mask = rng.random(e) < 0.9
+        g = I.Group(shape=e, mask=mask, acq=acq, K=1, mode="nll" if nll else "mse", bias="trilinear8",
+                    priors=("rep", "cal", "tv"))
+        g.y = rng.uniform(0.1, 1.0, size=(4, g.n_vox)).astype(np.float32)
+        g = with_theta(g, I.perturb_theta(I.init_theta(g.n_vox, 1, 4, 512, rng, sigma_init=0.1), rng, scale=0.2))
+        groups.append(g)
+    _check_groups(f"grid {edges}", groups)
+    states = []
+    for fused in (True, False):
+        st = DeviceState(Problem(groups), ys=[g.y for g in groups], thetas=[g.theta for g in groups])
+        for _ in range(2):
+            st.iteration(lr=1e-2) if fused else st.iteration_unfused(lr=1e-2)
+        torch.cuda.synchronize()
+        states.append(st)
+    for a in ("params", "m", "v", "step", "loss"):
+        assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
+
+
 @pytest.mark.parametrize("V", [1, 63, 64, 65, 128, 129, 256, 257])
 @pytest.mark.parametrize("N", [1, 3, 34])
 def test_forward_model_at_the_edges_of_its_rows(V, N):
