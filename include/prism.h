@@ -168,7 +168,9 @@ typedef struct {
 
 /* Launch shape of the fused pass (set by prism_problem_tune). */
 typedef struct {
-  int32_t vox_per_lane; /* 1 or 2 voxels per lane (the persistent launch uses 1) */
+  int32_t vox_per_lane; /* 1 or 2 voxels per lane (the persistent launch uses 1; where
+                           two would halve a kernel's waves per SIMD they are
+                           taken one after the other) */
   int32_t n_split;      /* 1, 2 or 4 waves sharing one voxel row (each over a part of
                            the measurements); 0 = chosen per work item from its size */
   int32_t item_vox;     /* voxels per work item (one thread block at a time), a

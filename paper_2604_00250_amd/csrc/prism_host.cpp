@@ -550,7 +550,7 @@ int plan(prism_problem* h) {
       it.kind = ((g.K - 1) * 2 + g.mode) * 2 + g.learn_d;
       per_group[gi].push_back((int)items.size());
       items.push_back(it);
-      item_vpl.push_back(Lg.vox_per_lane);
+      item_vpl.push_back(pass_two_voxels(g.K, g.mode, g.learn_d != 0) ? Lg.vox_per_lane : 1);
       item_ls.push_back(ls);
       v0 += it.nv;
     }

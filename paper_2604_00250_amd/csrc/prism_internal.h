@@ -200,6 +200,16 @@ struct StitchArgs {
   int64_t n_out;
 };
 
+// Whether the fused pass has a kernel with two voxels per lane for a variant.  The Rician
+// variants of three fibres, or two with learned diffusivities, need more than 256 registers
+// for it, one wave per SIMD: items of such a launch shape are run by the kernel with one,
+// a row of 64 voxels after the other (the shape vox_per_lane 2, n_split 4, 181888 voxels, N =
+// 222, K = 4: 345 us with two per lane, 227 this way; 93150 voxels, N = 59, K = 6, n_split 2
+// 159 and 89).
+constexpr bool pass_two_voxels(int K, int mode, bool learn_d) {
+  return mode != 1 || K < 2 || (K == 2 && !learn_d);
+}
+
 // launchers (prism_kernels.hip)
 // spatial_c: the C shared by every group with the Eq. 7 prior (0: none, or they differ)
 // max_nv: voxels of the largest work item; from_logits: one launch, no stored fractions

@@ -1204,7 +1204,11 @@ template <int K>
 hipError_t launch_pass_k(const PassArgs& a, int mode, int ld, int vpl, int maxN, hipStream_t s) {
   if (vpl == 2) {
     if (mode == kMSE) return ld ? launch_pass_t<K, kMSE, true, 2>(a, s, maxN) : launch_pass_t<K, kMSE, false, 2>(a, s, maxN);
-    return ld ? launch_pass_t<K, kNLL, true, 2>(a, s, maxN) : launch_pass_t<K, kNLL, false, 2>(a, s, maxN);
+    if constexpr (pass_two_voxels(K, kNLL, true))
+      if (ld) return launch_pass_t<K, kNLL, true, 2>(a, s, maxN);
+    if constexpr (pass_two_voxels(K, kNLL, false))
+      if (!ld) return launch_pass_t<K, kNLL, false, 2>(a, s, maxN);
+    return hipErrorInvalidValue;   // the plan has none
   }
   if (mode == kMSE) return ld ? launch_pass_t<K, kMSE, true, 1>(a, s, maxN) : launch_pass_t<K, kMSE, false, 1>(a, s, maxN);
   return ld ? launch_pass_t<K, kNLL, true, 1>(a, s, maxN) : launch_pass_t<K, kNLL, false, 1>(a, s, maxN);

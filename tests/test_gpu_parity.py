@@ -145,6 +145,37 @@ def test_bias_grid_gradient_by_waves_and_by_blocks(edges, nll):
         assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
 
 
+@pytest.mark.parametrize("n_split", [1, 2, 4])
+@pytest.mark.parametrize("K,learn_d", [(2, False), (2, True), (3, False), (6, True)])
+def test_rician_items_of_two_voxels_per_lane(K, learn_d, n_split):
+    """Rician variants with and without a kernel of two voxels per lane in that launch
+    shape: rows of 128 voxels one row of 64 after the other, the last ones short (640 + 65
+    voxels), against the oracle and the fused step bit for bit the separate ones."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(10 * K + n_split)
+    shape, V, N = (5, 15, 10), 705, 21
+    mask = np.zeros(750, dtype=bool)
+    mask[:V] = True
+    acq = I.Acquisition(bval=np.sort(rng.integers(0, 4, size=N)).astype(np.float64), bvec=I.uniform_sphere(N, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=K, mode="nll", bias="poly2", learn_diffusivity=learn_d)
+    g.y = rng.uniform(0.05, 1.0, size=(N, V)).astype(np.float32)
+    g = with_theta(g, I.perturb_theta(I.init_theta(V, K, N, 10, rng, sigma_init=0.1, learn_diffusivity=learn_d), rng,
+                                      scale=0.3))
+    launch = dict(vox_per_lane=2, n_split=n_split)
+    r = _check_groups(f"two per lane K={K} {learn_d} split {n_split}", [g], launch=launch)
+    assert r["prob"].plan_info()["items"] == -(-V // (512 // n_split))
+    states = []
+    for fused in (True, False):
+        st = DeviceState(Problem([g], launch=launch), ys=[g.y], thetas=[g.theta])
+        for _ in range(2):
+            st.iteration(lr=1e-2) if fused else st.iteration_unfused(lr=1e-2)
+        torch.cuda.synchronize()
+        states.append(st)
+    for a in ("params", "m", "v", "step", "loss"):
+        assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
+
+
 @pytest.mark.parametrize("V", [1, 63, 64, 65, 128, 129, 256, 257])
 @pytest.mark.parametrize("N", [1, 3, 34])
 def test_forward_model_at_the_edges_of_its_rows(V, N):
