@@ -1050,7 +1050,17 @@ int32_t prism_problem_info(const prism_problem* h, prism_problem_info_t* info) {
   info->n_cal = h->n_cal;
   info->n_y = h->n_y;
   info->n_groups = (int32_t)h->groups.size();
-  info->n_buckets = (int32_t)h->buckets.size();
+  // launches of one variant that differ in the split kernel's rows alone count once
+  info->n_buckets = 0;
+  for (size_t i = 0; i < h->buckets.size(); ++i) {
+    const Bucket& b = h->buckets[i];
+    bool seen = false;
+    for (size_t j = 0; j < i && !h->launch.persistent; ++j) {
+      const Bucket& c = h->buckets[j];
+      seen = seen || (c.K == b.K && c.mode == b.mode && c.learn_d == b.learn_d && c.vpl == b.vpl);
+    }
+    info->n_buckets += !seen;
+  }
   return PRISM_OK;
 }
 

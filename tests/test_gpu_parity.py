@@ -176,6 +176,19 @@ def test_rician_items_of_two_voxels_per_lane(K, learn_d, n_split):
         assert torch.equal(getattr(states[0], a), getattr(states[1], a)), a
 
 
+def test_variant_count_does_not_depend_on_the_rows():
+    """Two groups of one variant whose N give the split kernel rows of different length are
+    two launches but one variant."""
+    from paper_2604_00250_amd.problem import Problem
+    rng = np.random.default_rng(3)
+    mask = np.ones((15, 20, 20), dtype=bool)
+    groups = [I.Group(shape=mask.shape, mask=mask, K=1, mode="mse", priors=("rep",),
+                      acq=I.Acquisition(bval=np.ones(n), bvec=I.uniform_sphere(n, rng))) for n in (33, 288)]
+    prob = Problem(groups)
+    assert prob.plan_info()["launches"] == 2
+    assert prob.info.n_buckets == 1
+
+
 @pytest.mark.parametrize("V", [1, 63, 64, 65, 128, 129, 256, 257])
 @pytest.mark.parametrize("N", [1, 3, 34])
 def test_forward_model_at_the_edges_of_its_rows(V, N):
