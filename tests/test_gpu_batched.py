@@ -304,3 +304,63 @@ def test_automatic_items_are_finer_than_a_block_only_where_that_pays(n_groups, N
     for i in (0, n_groups // 2, n_groups - 1):
         out, grad, _ = run_oracle(groups[i], groups[i].theta)
         assert_parity(f"cut {n_groups} N={N}/{i}", r["loss"][i], merged_grad(r["gmicro"][i], r["gcal"][i]), out, grad)
+
+
+def test_concurrent_launches_share_the_streams_evenly():
+    """Thirteen variants of few blocks each, one of them of many voxels: every launch takes
+    about its longest block's time, so no stream gets more than five of them.  The longest
+    chain of kernels in the captured call is that stream's and the reduction."""
+    import ctypes
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(4)
+    acq = I.Acquisition(bval=np.full(64, 1.0), bvec=I.uniform_sphere(64, rng))
+    groups = []
+    variants = [(K, m, ld) for K in (1, 2, 3, 4) for m in ("mse", "nll") for ld in (False, True)][:13]
+    for i, (K, mode, ld) in enumerate(variants):
+        e = (16, 16, 16) if i == 5 else (14, 14, 14) if i == 9 else (4, 4, 5)
+        groups.append(I.Group(shape=e, mask=np.ones(e, dtype=bool), acq=acq, K=K, mode=mode, bias="none",
+                              learn_diffusivity=ld, neighbourhood=0, priors=("rep",)))
+    prob = Problem(groups)
+    assert prob.plan_info()["launches"] == 13
+    st = DeviceState(prob)
+    st.params[:st.n_micro].normal_()
+    st.y.uniform_(0.1, 1.0)
+    st.loss_grad()
+    torch.cuda.synchronize()
+    want = st.loss.clone()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        st.loss_grad()
+    hip = ctypes.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    m = ctypes.c_size_t()
+    assert hip.hipGraphGetEdges(raw, None, None, ctypes.byref(m)) == 0
+    src, dst = (ctypes.c_void_p * m.value)(), (ctypes.c_void_p * m.value)()
+    assert hip.hipGraphGetEdges(raw, src, dst, ctypes.byref(m)) == 0
+
+    def kernel(node):
+        t = ctypes.c_int()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(t)) == 0
+        return t.value == 0
+    before = {}
+    for a, b in zip(src, dst):
+        before.setdefault(b, []).append(a)
+    depth = {}
+
+    def chain(node):
+        if node not in depth:
+            depth[node] = kernel(node) + max((chain(p) for p in before.get(node, [])), default=0)
+        return depth[node]
+    longest = max(chain(v) for v in nodes)
+    say(f"[streams] {n.value} nodes, {m.value} edges, longest chain of kernels {longest}")
+    assert longest <= 6
+    graph.instantiate()
+    for _ in range(3):
+        st.loss.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(st.loss, want)
