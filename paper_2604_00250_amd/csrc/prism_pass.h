@@ -36,13 +36,17 @@ static_assert(kTile % kPf == 0, "tile must be a multiple of the prefetch depth")
 // measurement at a time.  Otherwise three for the variants that fit 168
 // registers without spilling (one voxel per lane, at most two fibres, or three
 // with fixed diffusivities), letting the scheduler interleave two measurements
-// at a time (sched_span 2); else PRISM_PASS_MIN_WAVES, one measurement at a time.
+// at a time (sched_span 2); else PRISM_PASS_MIN_WAVES, one measurement at a time.  The
+// largest variant (K = 6, Rician, learned diffusivities), whose 274 registers would leave
+// it one wave, is held to two (41 spilled; 309741 voxels, N = 123 464 -> 303 us, 132651
+// voxels, N = 237, continuity over 26 neighbours 708 -> 469).
 constexpr bool pass_four_waves(int K, int MODE, bool LD, int VL) {
   return PRISM_FOUR_WAVES && VL == 1 && MODE == 0 && !LD && K <= 3;
 }
 constexpr int pass_min_waves(int K, int MODE, bool LD, int VL) {
   return pass_four_waves(K, MODE, LD, VL) ? 4
-         : VL == 1 && (K <= 2 || (K == 3 && !LD)) ? 3 : PRISM_PASS_MIN_WAVES;
+         : VL == 1 && (K <= 2 || (K == 3 && !LD)) ? 3
+         : VL == 1 && K == 6 && MODE == 1 && LD ? std::max(2, PRISM_PASS_MIN_WAVES) : PRISM_PASS_MIN_WAVES;
 }
 constexpr int sched_span(int K, int MODE, bool LD, int VL) {
   return pass_min_waves(K, MODE, LD, VL) == 3 ? 2 : 1;
