@@ -1135,8 +1135,11 @@ __device__ __forceinline__ float synth_pair(const Vox<K, LD>& x, const float4 a,
 }
 
 // One work item, a voxel per lane: the block's four waves take the item's rows of 64, or
-// with fewer rows share each row, every wave with a part of the measurements.  Large
-// problems are bound by the stores: a row of V floats starts anywhere in a cache line, so
+// with fewer rows share each row, every wave with a part of the measurements, unless that
+// is less than eight each and there are blocks enough to fill the device: every wave
+// repeats its row's transforms (689216 voxels in items of 64, N = 12, K = 3: 36.2 us shared,
+// 24.9 not; with few blocks the shorter chain counts, 392 voxels, N = 19, K = 6: 7.0 and
+// 8.0).  Large problems are bound by the stores: a row of V floats starts anywhere in a cache line, so
 // each wave's piece of a row has a partial line at either end; items in runs per XCD let
 // neighbouring pieces meet in one L2 (753k voxels, N = 288, K = 3: 327 -> 262 us; without
 // the stores 224, the stores alone as one fill 126).  Two voxels per lane and one vector
@@ -1153,7 +1156,9 @@ __global__ __launch_bounds__(kBlock) void k_synth(PassArgs A) {
   stage_acquisition(A, g, acq, false);
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int rows = it.nv <= 64 ? 1 : (it.nv <= 128 ? 2 : 4), WN = 4 / rows;
+  int rows = it.nv <= 64 ? 1 : (it.nv <= 128 ? 2 : 4);
+  if (gridDim.x > 1024 && g.N < 8 * (4 / rows)) rows = 4;
+  const int WN = 4 / rows;
   const int row = wave / WN, split = wave - row * WN;
   const int nb = (g.N * split) / WN, ne = (g.N * (split + 1)) / WN;
   const int64_t V = g.V;

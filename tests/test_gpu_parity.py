@@ -214,6 +214,31 @@ def test_forward_model_at_the_edges_of_its_rows(V, N):
     assert bool((out[st.n_y:] == -7.0).all())
 
 
+@pytest.mark.parametrize("n_split,N", [(4, 31), (4, 32), (2, 15), (2, 16)])
+def test_forward_model_of_many_short_items(n_split, N):
+    """More blocks than fill the device, of one or two rows: waves share a row from eight
+    measurements each up, else take one each."""
+    import torch
+    from paper_2604_00250_amd.problem import DeviceState, Problem
+    rng = np.random.default_rng(N)
+    rows = 256 // n_split
+    V = rows * 1025 + rows - 9
+    shape = (10, -(-V // 1000), 100)
+    mask = np.zeros(1000 * shape[1], dtype=bool)
+    mask[:V] = True
+    acq = I.Acquisition(bval=rng.integers(0, 4, size=N).astype(np.float64), bvec=I.uniform_sphere(N, rng))
+    g = I.Group(shape=shape, mask=mask.reshape(shape), acq=acq, K=1, mode="mse")
+    g.theta = I.perturb_theta(I.init_theta(V, 1, N, 0, rng), rng, scale=0.3)
+    prob = Problem([g], launch=dict(vox_per_lane=1, n_split=n_split))
+    assert prob.plan_info()["items"] == 1026
+    st = DeviceState(prob, thetas=[g.theta])
+    out = torch.full((st.n_y,), -7.0, device=st.device)
+    st.synthesize(out)
+    torch.cuda.synchronize()
+    ref = O.synthesize(oracle_problem(g), theta32(g.theta))
+    assert np.abs(out.cpu().numpy().reshape(N, V) - ref).max() < 2e-6 * np.abs(ref).max()
+
+
 def test_synthesize_matches_oracle_forward():
     import torch
     from paper_2604_00250_amd.problem import DeviceState, Problem
