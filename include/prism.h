@@ -175,8 +175,10 @@ typedef struct {
                            the measurements); 0 = chosen per work item from its size */
   int32_t item_vox;     /* voxels per work item (one thread block at a time), a
                            multiple of 64 * vox_per_lane * 4 / n_split; 0 = automatic:
-                           one block chunk (that multiple) with a fixed n_split, else
-                           about six blocks per compute unit over the problem */
+                           one block chunk (that multiple) with a fixed n_split, or
+                           with n_split 4 on a problem too small to fill the device
+                           64, 32 or 16 voxels; with n_split 0 about a third of a
+                           resident block's share of the problem's work */
   int32_t persistent;   /* 0: one launch per kernel variant (K, mode, learned D,
                            voxels per lane); 1: persistent launches over all work
                            items, one per register class (K <= 2, compiled for three

@@ -187,7 +187,7 @@ __device__ __forceinline__ void row_scatter_group(RowScatter& s, bool here) {
 // does the same for two measurements and the rows of each half, and a select with the row
 // mirror for the two pairs and the halves of each row.  Four swaps, four additions; two and
 // two; three; then three additions of mirrored operands: 18 operations per group for both
-// values, where the reduce-scatter within rows below takes 25.  (The swaps are inline asm
+// values, where the reduce-scatter within rows above takes 25.  (The swaps are inline asm
 // because this compiler's builtins return the first result for both outputs.  A swap needs
 // two wait states after the operation that wrote its operands, which the compiler does not
 // count into inline asm: the s_nop.)

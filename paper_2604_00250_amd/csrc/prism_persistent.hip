@@ -64,8 +64,8 @@ hipError_t launch_counter_reset(int32_t* counters, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The two register classes of the persistent launch: items with K <= 3 in a
-// kernel held to three waves per SIMD, K >= 4 in one held to two (one kernel
+// The two register classes of the persistent launch: items with K <= 2 in a
+// kernel held to three waves per SIMD, K >= 3 in one held to two (one kernel
 // for all would hold every item to the largest variant's registers).
 int persistent_class(int K) { return K <= 2 ? 0 : 1; }
 
