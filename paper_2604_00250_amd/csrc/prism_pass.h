@@ -758,11 +758,18 @@ __device__ __forceinline__ void chain_rule(const PassArgs& A, const GroupDev& g,
       const int u = nbr[(int64_t)q * V + v];
       if (u < 0) continue;
       const float w = sc2 * (ax + ninv[u]);
+      // From four fibres up, short of vector registers, the rows through descriptors: one
+      // 32-bit offset for all of them, where 64-bit addresses take two registers per row
+      // (K = 6, Rician, learned diffusivities, N = 58, 201840 voxels, 26 neighbours: 275 ->
+      // 221 us per gradient).  Below, the scalar registers that this takes are the scarcer
+      // kind (slabs at K = 2, N = 96, without this prior 207 -> 220).
+      RowCursor<const float> urows(vd, V);
+      const uint32_t uoff = (uint32_t)u * 4u;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const float ux = vd[(int64_t)(3 * k) * V + u];
-        const float uy = vd[(int64_t)(3 * k + 1) * V + u];
-        const float uz = vd[(int64_t)(3 * k + 2) * V + u];
+        const float ux = K >= 4 ? load_row_f32(urows.next(), vrowb, uoff) : vd[(int64_t)(3 * k) * V + u];
+        const float uy = K >= 4 ? load_row_f32(urows.next(), vrowb, uoff) : vd[(int64_t)(3 * k + 1) * V + u];
+        const float uz = K >= 4 ? load_row_f32(urows.next(), vrowb, uoff) : vd[(int64_t)(3 * k + 2) * V + u];
         const float n2 = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
         const float in = n2 > 0.0f ? rsq(n2) : 0.0f;
         const float dx = ux * in, dy = uy * in, dz = uz * in;
